@@ -17,7 +17,7 @@
 #include <thread>
 #include <vector>
 
-#include "mfwf_internal.h"
+#include "leg_core.h"
 
 struct mfwf_plan_s {
     mfwf::Plan p;
@@ -161,17 +161,23 @@ static void build_recurrence(int lmax, std::vector<double2> &ab, std::vector<dou
     }
 }
 
-// For every (m, pair): first l with |lambda_lm(z)| >= 2^-100 and (mu_{l-1}, mu_l) there.
+// For every (m, pair): first l with |lambda_lm(z)| >= 2^-100 and (mu_{l-1}, mu_l) there; and the
+// block of kLegBlock values of l from m that holds it, with the recurrence's state entering
+// that block (its values below the threshold are representable: the block's growth is far
+// from the 2^-922 that separates the threshold from the smallest double).
 // lambda_mm = (-1)^m sqrt(1/4pi) prod_{k<=m} sqrt((2k+1)/(2k)) sin(theta) is carried as a
 // mantissa and a power-of-two exponent (it underflows double long before m = lmax near
 // the poles); the l-recurrence runs in the same scaled form until the threshold.
 static void build_seeds(int lmax, int npair, const std::vector<RingGeom> &geo,
                         const std::vector<double2> &ab, const std::vector<double> &c,
                         const std::vector<long> &mofs, std::vector<int> &lstart,
-                        std::vector<double2> &seed) {
+                        std::vector<double2> &seed, std::vector<int> &kstart,
+                        std::vector<double2> &entry) {
     const int nm = lmax + 1;
     lstart.assign((size_t)nm * npair, lmax + 1);
     seed.assign((size_t)nm * npair, make_double2(0.0, 0.0));
+    kstart.assign((size_t)nm * npair, (lmax + kLegBlock) / kLegBlock);
+    entry.assign((size_t)nm * npair, make_double2(0.0, 0.0));
     auto work = [&](int p0, int p1) {
         for (int p = p0; p < p1; p++) {
             const double z = geo[p].z, sth = geo[p].sth;
@@ -194,7 +200,16 @@ static void build_seeds(int lmax, int npair, const std::vector<RingGeom> &geo,
                 const double2 *abm = ab.data() + mofs[m] - m;
                 const double *cm = c.data() + mofs[m] - m;
                 const size_t slot = (size_t)m * npair + p;
+                double b1 = 0.0, b2 = 0.0;  // lambda_{l0-1}, lambda_{l0-2} entering block l0
+                long be = e;
+                int l0 = m;
                 for (int l = m;; l++) {
+                    if (l > m && (l - m) % kLegBlock == 0) {
+                        b1 = p1v;
+                        b2 = p2v;
+                        be = e;
+                        l0 = l;
+                    }
                     if (l > m) {
                         const double2 cc = abm[l];
                         const double cur = cc.x * (z * p1v) - cc.y * p2v;
@@ -212,6 +227,11 @@ static void build_seeds(int lmax, int npair, const std::vector<RingGeom> &geo,
                         const double lam_prev = std::ldexp(p2v, (int)e);
                         const double lam = std::ldexp(p1v, (int)e);
                         seed[slot] = make_double2(l > m ? lam_prev / cm[l - 1] : 0.0, lam / cm[l]);
+                        kstart[slot] = (l0 - m) / kLegBlock;
+                        // at l0 = m the recurrence (A_mm = 0) gives mu_m = -u2
+                        entry[slot] = l0 == m ? make_double2(0.0, -std::ldexp(rmm, (int)emm))
+                                              : make_double2(std::ldexp(b1, (int)be) / cm[l0 - 1],
+                                                             std::ldexp(b2, (int)be) / cm[l0 - 2]);
                         break;
                     }
                     if (l == lmax) break;
@@ -231,7 +251,7 @@ static void build_seeds(int lmax, int npair, const std::vector<RingGeom> &geo,
 }
 
 static void free_plan(Plan &p) {
-    void *ptrs[] = {p.d_z,    p.d_A,    p.d_c,     p.d_lstart, p.d_seed,  p.d_pfft, p.d_plist,
+    void *ptrs[] = {p.d_z,    p.d_A,    p.d_c,     p.d_lstart, p.d_seed, p.d_kstart, p.d_entry, p.d_pfft, p.d_plist,
                     p.d_tw,   p.d_twlo, p.d_twhi, p.d_chirp, p.d_bhat, p.d_mofs,   p.d_cl,    p.d_M, p.d_pc, p.d_tau,
                     p.d_rho,  p.d_t,    p.d_smap,  p.d_phase,  p.d_apart, p.d_salm,
                     p.d_salm_prev, p.d_sp, p.d_red, p.d_diag, p.d_lam, p.d_lck, p.d_segoff, p.d_loff, p.d_Lp,
@@ -262,8 +282,8 @@ static int device_name(std::string &name) {
 // Kernel shapes the plan chooses by timing (none changes what a result is, only how the work
 // is laid out; the Legendre variants of the FP64 path also change the order in which the
 // ring pairs' partial sums are added):
-//   synth, ana  FP64 Legendre kernels: ring pairs per lane 1/2/4, coefficient block 4/8,
-//               prefetch of the next block (9 synthesis, 6 analysis variants)
+//   synth, ana  FP64 Legendre kernels: ring pairs per lane 1/2/4, rows of m per wave 1/2,
+//               coefficients per scalar load block 4/8 (9 synthesis, 6 analysis variants)
 //   g0, g1      maps per workgroup of the batched form's ring step, short-transform class
 //               and longest-transform class (1, 2 or 4; as LDS and 1024 threads allow)
 //   cta, cts    largest column tile of the analysis / synthesis GEMMs, x 64 columns (1 or 2)
@@ -483,12 +503,10 @@ static int autotune(Plan &p, const std::string &devname) {
 }
 
 static void default_variants(Plan &p) {
-    // pairs per lane 4 / 2 / 1 by problem size, prefetched 8-wide blocks
+    // pairs per lane 4 / 2 / 1 by problem size; one row of m per wave (plans too small to be
+    // timed have few waves)
     const int P = p.npair >= 1024 ? 4 : (p.npair >= 512 ? 2 : 1);
-    for (int v = 0; v < leg_synth_variants(); v++)
-        if (leg_synth_pairs_per_lane(v) == P && v >= 3 && v < 6) p.synth_variant = v;
-    for (int v = 0; v < leg_analysis_variants(); v++)
-        if (leg_analysis_pairs_per_lane(v) == P && v >= 3) p.ana_variant = v;
+    p.synth_variant = p.ana_variant = P == 4 ? 5 : (P == 2 ? 4 : 3);
 }
 
 // Batched FP32 form: lambda table (filled on the device from the FP64 recurrence), skip
@@ -703,8 +721,9 @@ static int create(int nside, int lmax, int spin, int dtype, int max_batch, void 
     std::vector<long> mofs;
     build_recurrence(lmax, ab, Atab, ctab, mofs);
     std::vector<int> lstart;
-    std::vector<double2> seed;
-    build_seeds(lmax, p.npair, geo, ab, ctab, mofs, lstart, seed);
+    std::vector<double2> seed, entry;
+    std::vector<int> kstart;
+    build_seeds(lmax, p.npair, geo, ab, ctab, mofs, lstart, seed, kstart, entry);
     p.work_tuples = 0.0;
     for (int ls : lstart) p.work_tuples += (ls <= lmax) ? (double)(lmax - ls + 1) : 0.0;
 
@@ -826,8 +845,13 @@ static int create(int nside, int lmax, int spin, int dtype, int max_batch, void 
     MFWF_TRY(dalloc(&p.d_A, Atab.size(), "recurrence A"));
     MFWF_TRY(dalloc(&p.d_c, ctab.size(), "recurrence scale"));
     MFWF_TRY(dalloc(&p.d_mofs, mofs.size(), "m offsets"));
-    MFWF_TRY(dalloc(&p.d_lstart, lstart.size(), "l start"));
-    MFWF_TRY(dalloc(&p.d_seed, seed.size(), "seeds"));
+    if (f32) {  // the FP32 form's tables start at each pair's own l, the FP64 kernels at its block
+        MFWF_TRY(dalloc(&p.d_lstart, lstart.size(), "l start"));
+        MFWF_TRY(dalloc(&p.d_seed, seed.size(), "seeds"));
+    } else {
+        MFWF_TRY(dalloc(&p.d_kstart, kstart.size(), "first blocks"));
+        MFWF_TRY(dalloc(&p.d_entry, entry.size(), "entry states"));
+    }
     MFWF_TRY(dalloc(&p.d_pfft, pf.size(), "fft plan"));
     MFWF_TRY(dalloc(&p.d_plist, plist.size(), "fft pair list"));
     MFWF_TRY(dalloc(&p.d_tw, tw.size(), "twiddles"));
@@ -872,8 +896,13 @@ static int create(int nside, int lmax, int spin, int dtype, int max_batch, void 
     MFWF_TRY(upload(p.d_A, Atab, p.stream));
     MFWF_TRY(upload(p.d_c, ctab, p.stream));
     MFWF_TRY(upload(p.d_mofs, mofs, p.stream));
-    MFWF_TRY(upload(p.d_lstart, lstart, p.stream));
-    MFWF_TRY(upload(p.d_seed, seed, p.stream));
+    if (f32) {
+        MFWF_TRY(upload(p.d_lstart, lstart, p.stream));
+        MFWF_TRY(upload(p.d_seed, seed, p.stream));
+    } else {
+        MFWF_TRY(upload(p.d_kstart, kstart, p.stream));
+        MFWF_TRY(upload(p.d_entry, entry, p.stream));
+    }
     MFWF_TRY(upload(p.d_pfft, pf, p.stream));
     MFWF_TRY(upload(p.d_plist, plist, p.stream));
     MFWF_TRY(upload(p.d_tw, tw, p.stream));

@@ -1,6 +1,6 @@
 // Per-lane state of the rescaled Legendre recurrence shared by the temperature and the
 // polarization kernels: mu_l = A_lm z mu_{l-1} - mu_{l-2}, lambda_lm = c_lm mu_lm, started
-// at each (m, ring pair)'s first non-negligible l from two stored values.
+// at the block of l that holds each (m, ring pair)'s first non-negligible value.
 #pragma once
 
 #include "mfwf_internal.h"
@@ -18,57 +18,83 @@ __device__ __forceinline__ int wave_max_uniform(int v) {
     return __builtin_amdgcn_readfirstlane(v);
 }
 
+// A row of one m is walked in blocks of kLegBlock values of l from l = m.  A pair enters it at
+// the block that holds its first l with |lambda_lm| >= 2^-100, from the state
+// (mu_{l0-1}, mu_{l0-2}) at that block's first value l0 (0, -mu_m at l0 = m, where A_lm = 0), so
+// a start is a load of two registers between blocks and no value of l inside a block tests
+// for one: with a test and four selects at every l the blocks that can hold a start cost 9
+// vector instructions per (l, pair) instead of 4.
+static constexpr int kLegBlock = 16;
+
 template <int P>
 struct PairState {
     double z[P], u1[P], u2[P];  // mu_{l-1}, mu_{l-2}
-    double2 sd[P];              // (mu_{l_s - 1}, mu_{l_s})
-    int ls[P];
-    int lo, hi;  // wave-uniform: smallest start, largest start <= lmax (m if none)
+    double2 ent[P];             // state at the pair's first block
+    int kb[P];                  // its first block
+    int klo, khi;               // wave-uniform: smallest first block, largest one of the row's
 
-    __device__ __forceinline__ void load(int m, int g, int npair, int lmax,
+    __device__ __forceinline__ void load(int m, int g, int npair, int nblk,
                                          const double *__restrict__ zp,
-                                         const int *__restrict__ lstart,
-                                         const double2 *__restrict__ seed) {
-        int mylo = lmax + 1, myhi = m;
+                                         const int *__restrict__ kstart,
+                                         const double2 *__restrict__ entry) {
+        int mylo = nblk, myhi = -1;
 #pragma unroll
         for (int k = 0; k < P; k++) {
             const int p = g * kW * P + k * kW + (int)threadIdx.x;
             const bool valid = p < npair;
             z[k] = valid ? zp[p] : 0.0;
-            ls[k] = valid ? lstart[(long)m * npair + p] : lmax + 1;
-            sd[k] = valid ? seed[(long)m * npair + p] : make_double2(0.0, 0.0);
+            kb[k] = valid ? kstart[(long)m * npair + p] : nblk;
+            ent[k] = valid ? entry[(long)m * npair + p] : make_double2(0.0, 0.0);
             u1[k] = 0.0;
             u2[k] = 0.0;
-            mylo = min(mylo, ls[k]);
-            if (ls[k] <= lmax) myhi = max(myhi, ls[k]);
+            mylo = min(mylo, kb[k]);
+            if (kb[k] < nblk) myhi = max(myhi, kb[k]);
         }
-        lo = wave_min_uniform(mylo);
-        hi = wave_max_uniform(myhi);
+        klo = wave_min_uniform(mylo);
+        khi = wave_max_uniform(myhi);
     }
 
-    // mu_l for every pair, injecting the seeds at each pair's own start.  The two forms
-    // associate A z mu differently on purpose: the blocks with and without injection then
-    // share no subexpression, so the compiler cannot hoist a whole block's A z products
-    // above the branch (that costs 2 U P registers and halves occupancy).
-    template <bool INJ>
-    __device__ __forceinline__ void step(int l, double A, double (&cur)[P]) {
+    // at the start of block k: the pairs whose first block it is take their state
+    __device__ __forceinline__ void enter(int blk) {
+        if (blk > khi) return;  // uniform
+#pragma unroll
+        for (int k = 0; k < P; k++)
+            if (kb[k] == blk) {
+                u1[k] = ent[k].x;
+                u2[k] = ent[k].y;
+            }
+    }
+
+    // mu_l for every pair (0 before the pair's first block)
+    __device__ __forceinline__ void step(double A, double (&cur)[P]) {
 #pragma unroll
         for (int k = 0; k < P; k++) {
-            double v;
-            if (INJ) {
-                v = fma(A * z[k], u1[k], -u2[k]);
-                const bool start = (l == ls[k]);
-                v = start ? sd[k].y : v;
-                u1[k] = start ? sd[k].x : u1[k];
-            } else {
-                v = fma(A, z[k] * u1[k], -u2[k]);
-            }
+            const double v = fma(A, z[k] * u1[k], -u2[k]);
             u2[k] = u1[k];
             u1[k] = v;
             cur[k] = v;
         }
     }
 };
+
+// Workgroup L of an FP64 Legendre launch of ngrp pair groups x nmi rows (or row pairs).
+// Workgroup L runs on XCD L mod 8; every XCD takes whole chunks of 8 adjacent m (a 128-byte
+// line of a ring's coefficients, so that a line meets in one L2) from all pair groups, the
+// equatorial groups (whose pairs start first and carry the most values of l) before the
+// polar ones.  With the group as the fastest index instead, 8 groups put all rows of one
+// group on one XCD and the equatorial one finished last by a third.
+struct LegItem {
+    int g, mi;
+};
+__host__ __device__ __forceinline__ int leg_items_per_group(int nmi) { return (((nmi + 7) / 8 + 7) / 8) * 8; }
+__device__ __forceinline__ LegItem leg_item(int ngrp, int nmi) {
+    const int L = blockIdx.x, x = L & 7, s = L >> 3, w = leg_items_per_group(nmi);
+    const int q = s / w, t = s - q * w;
+    return LegItem{ngrp - 1 - q, ((t >> 3) * 8 + x) * 8 + (t & 7)};
+}
+static inline dim3 leg_grid(int ngrp, int nmi, int nb) {
+    return dim3(8 * leg_items_per_group(nmi) * ngrp, nb);
+}
 
 // (x, y) of every lane after exchanging lanes 32..63 of x with lanes 0..31 of y (SWAP32),
 // or the odd 16-lane rows of x with the even rows of y (v_permlane{32,16}_swap, one 32-bit

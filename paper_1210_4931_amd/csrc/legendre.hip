@@ -17,16 +17,15 @@
 // from two host-computed values (mu_{l_s - 1}, mu_{l_s}); earlier terms are below 2^-100 and
 // are dropped, and a pair carries mu = 0 (no contribution) before its start.
 //
-// Work split: one 64-lane wave per (pair group g, m-pair); lane L handles ring pairs
-// g*64*P + k*64 + L, k < P (adjacent lanes = adjacent latitudes, so start indices are
-// close).  Each wave processes m and lmax - m, so every wave walks lmax + 2 values of l.
+// Work split: one 64-lane wave per (pair group g, m) or (pair group g, m and lmax - m);
+// lane L handles ring pairs g*64*P + k*64 + L, k < P (adjacent lanes = adjacent latitudes, so
+// first blocks are close).  Two rows per wave balance the triangle (every wave walks lmax + 2
+// values of l), one row per wave gives twice the waves where there are few.
 // The l loop is wave-uniform: its bounds come through readfirstlane, so it runs on the
-// scalar unit and A_lm and the coefficients of each l are scalar loads, fetched U values of
-// l at a time (optionally one block ahead).  Blocks start at even l + m, so the even/odd
-// split is fixed at compile time inside a block.  Lanes inject their seeds only in blocks
-// that can contain a start index.
-// The analysis reduces over the wave's lanes every C values of l through LDS (transpose
-// and sum, fixed order, deterministic).
+// scalar unit and A_lm and the coefficients of each l are scalar loads.  Blocks of kLegBlock
+// values of l start at l = m, so the even/odd split is fixed at compile time inside a block
+// and pairs start between blocks.  The analysis reduces over the wave's lanes once per block
+// (fixed order, deterministic).
 #include <type_traits>
 
 #include "leg_core.h"
@@ -62,321 +61,248 @@ struct SynthAcc {
     }
 };
 
-template <int NB, int U>
-struct SynthBlockData {
-    double A[U];
-    double2 a[U][NB];
-    __device__ __forceinline__ void fetch(int l, const double *__restrict__ Am,
-                                          const double2 *const (&am)[NB]) {
-#pragma unroll
-        for (int u = 0; u < U; u++) {
-            A[u] = Am[l + u];
-#pragma unroll
-            for (int j = 0; j < NB; j++) a[u][j] = am[j][l + u];
-        }
-    }
-};
-
-template <int NB, int P, int U, bool INJ>
-__device__ __forceinline__ void synth_block(int l, PairState<P> &st, SynthAcc<NB, P> &acc,
-                                            const SynthBlockData<NB, U> &bd) {
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-        double cur[P];
-        st.template step<INJ>(l + u, bd.A[u], cur);
-        if (u & 1)
-            acc.template add<true>(cur, bd.a[u]);
-        else
-            acc.template add<false>(cur, bd.a[u]);
-    }
-}
-
-template <int NB, int P, int U, bool PF>
+template <int P, int U>
 __device__ __forceinline__ void synth_one_m(int m, int g, const double2 *__restrict__ alm,
-                                            long nalm, const double *__restrict__ Atab,
+                                            const double *__restrict__ Atab,
                                             const long *__restrict__ mofs,
-                                            const int *__restrict__ lstart,
-                                            const double2 *__restrict__ seed,
+                                            const int *__restrict__ kstart,
+                                            const double2 *__restrict__ entry,
                                             const double *__restrict__ zp,
                                             double2 *__restrict__ phase, int lmax, int npair,
-                                            int nring, int nm, int b0) {
+                                            int nring, int nm) {
     PairState<P> st;
-    st.load(m, g, npair, lmax, zp, lstart, seed);
-    const long off = mofs[m] - m;  // packed index of (l, m) = off + l
+    const int nblk = (lmax - m + kLegBlock) / kLegBlock;
+    st.load(m, g, npair, nblk, zp, kstart, entry);
+    const long off = mofs[m];
     const double *Am = Atab + off;
-    const double2 *am[NB];
-#pragma unroll
-    for (int j = 0; j < NB; j++) am[j] = alm + (long)(b0 + j) * nalm + off;
-    SynthAcc<NB, P> acc;
+    const double2 *am = alm + off;
+    SynthAcc<1, P> acc;
     acc.zero();
-
-    int l = st.lo - ((st.lo + m) & 1);  // even l + m; mu = 0 there for every lane
-    if (PF) {
-        SynthBlockData<NB, U> cur, nxt;
-        if (l + U - 1 <= lmax) cur.fetch(l, Am, am);
-        for (; l + U - 1 <= lmax; l += U) {
-            const bool more = l + 2 * U - 1 <= lmax;
-            if (more) nxt.fetch(l + U, Am, am);
-            if (l <= st.hi)
-                synth_block<NB, P, U, true>(l, st, acc, cur);
-            else
-                synth_block<NB, P, U, false>(l, st, acc, cur);
-            if (more) cur = nxt;
-        }
-    } else {
-        for (; l + U - 1 <= lmax; l += U) {
-            SynthBlockData<NB, U> cur;
-            cur.fetch(l, Am, am);
-            if (l <= st.hi)
-                synth_block<NB, P, U, true>(l, st, acc, cur);
-            else
-                synth_block<NB, P, U, false>(l, st, acc, cur);
-        }
-    }
-    for (; l <= lmax; l++) {  // tail: fewer than U values of l
-        double2 a[NB];
+    const int nl = lmax - m + 1;  // values of l, from r = l - m = 0
+    int r = st.klo * kLegBlock;
+    for (; r + kLegBlock <= nl; r += kLegBlock) {
+        st.enter(r / kLegBlock);
 #pragma unroll
-        for (int j = 0; j < NB; j++) a[j] = am[j][l];
-        double cur[P];
-        st.template step<true>(l, Am[l], cur);
-        if ((l + m) & 1)
-            acc.template add<true>(cur, a);
-        else
-            acc.template add<false>(cur, a);
+        for (int h = 0; h < kLegBlock; h += U) {
+            double A[U];
+            double2 a[U];
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                A[u] = Am[r + h + u];
+                a[u] = am[r + h + u];
+            }
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                double cur[P];
+                const double2 au[1] = {a[u]};
+                st.step(A[u], cur);
+                if (u & 1) acc.template add<true>(cur, au);
+                else acc.template add<false>(cur, au);
+            }
+        }
     }
-
+    if (r < nl) st.enter(r / kLegBlock);
+    for (; r < nl; r++) {  // the last, partial block
+        double cur[P];
+        const double2 au[1] = {am[r]};
+        st.step(Am[r], cur);
+        if (r & 1) acc.template add<true>(cur, au);
+        else acc.template add<false>(cur, au);
+    }
 #pragma unroll
     for (int k = 0; k < P; k++) {
         const int p = g * kW * P + k * kW + (int)threadIdx.x;
         if (p >= npair) continue;
         const int rN = p, rS = nring - 1 - p;
-#pragma unroll
-        for (int j = 0; j < NB; j++) {
-            // ring-Fourier layout [map][ring][m]
-            double2 *out = phase + (long)(b0 + j) * nm * nring + m;
-            out[(long)rN * nm] = make_double2(acc.Er[k][j] + acc.Or[k][j], acc.Ei[k][j] + acc.Oi[k][j]);
-            if (rS != rN)
-                out[(long)rS * nm] = make_double2(acc.Er[k][j] - acc.Or[k][j], acc.Ei[k][j] - acc.Oi[k][j]);
-        }
+        double2 *out = phase + m;  // ring-Fourier layout [map][ring][m]
+        out[(long)rN * nm] = make_double2(acc.Er[k][0] + acc.Or[k][0], acc.Ei[k][0] + acc.Oi[k][0]);
+        if (rS != rN)
+            out[(long)rS * nm] = make_double2(acc.Er[k][0] - acc.Or[k][0], acc.Ei[k][0] - acc.Oi[k][0]);
     }
 }
 
-template <int NB, int P, int U, bool PF>
+// ROWS: values of m per wave (2: m and lmax - m)
+template <int P, int U, int ROWS>
 __global__ void __launch_bounds__(kW)
 k_leg_synth(const double2 *__restrict__ alm, long nalm, const double *__restrict__ Atab,
-            const long *__restrict__ mofs, const int *__restrict__ lstart,
-            const double2 *__restrict__ seed, const double *__restrict__ zp,
-            double2 *__restrict__ phase, int lmax, int npair, int nring, int nm) {
-    const int g = blockIdx.x, mi = blockIdx.y, b0 = blockIdx.z * NB;
-    const int npass = (lmax - mi > mi) ? 2 : 1;
+            const long *__restrict__ mofs, const int *__restrict__ kstart,
+            const double2 *__restrict__ entry, const double *__restrict__ zp,
+            double2 *__restrict__ phase, int lmax, int npair, int nring, int nm, int ngrp) {
+    const int nmi = ROWS == 2 ? (lmax + 2) / 2 : nm;
+    const LegItem it = leg_item(ngrp, nmi);
+    if (it.mi >= nmi) return;
+    const int b = blockIdx.y;
+    const int npass = (ROWS == 2 && lmax - it.mi > it.mi) ? 2 : 1;
     for (int pass = 0; pass < npass; pass++)
-        synth_one_m<NB, P, U, PF>(pass == 0 ? mi : lmax - mi, g, alm, nalm, Atab, mofs, lstart,
-                                  seed, zp, phase, lmax, npair, nring, nm, b0);
+        synth_one_m<P, U>(pass == 0 ? it.mi : lmax - it.mi, it.g, alm + (long)b * nalm, Atab, mofs,
+                          kstart, entry, zp, phase + (long)b * nm * nring, lmax, npair, nring, nm);
 }
 
 // ---------------------------------------------------------------------------------------
 // Analysis
 // ---------------------------------------------------------------------------------------
-template <int NB>
-struct AnaChunk {
-    static constexpr int C = 16 / NB;      // values of l per reduction
-    static constexpr int V = 2 * NB * C;   // doubles reduced per lane per chunk (= 32)
-    static constexpr int LD = V + 2;       // LDS row stride of the plain transpose-reduce
-    static constexpr int Q = V / 4;        // doubles per lane after the two lane swaps
-};
+static constexpr int kAnaV = 2 * kLegBlock;  // doubles reduced per lane per block (re, im)
+static constexpr int kAnaQ = kAnaV / 4;      // doubles per lane after the two lane swaps
+// LDS slot of a lane's reduced values: 8 doubles of padding after every 8 lanes put the
+// eight (row, half) groups that read at once on four different bank quarters
+__device__ __forceinline__ int ana_slot(int lane) { return (lane + (lane >> 3)) * kAnaQ; }
+static constexpr int kAnaLds = (kW + kW / 8) * kAnaQ;
 
-// acc[2 (c NB + j) + comp] += sum_k mu_{c0+c}(pair k) X_{parity(c)}[k][j]
-template <int NB, int P, bool INJ, bool FULL>
-__device__ __forceinline__ void analysis_chunk(int c0, int lmax, PairState<P> &st,
-                                               const double (&A)[AnaChunk<NB>::C],
-                                               const double2 (&Xe)[P][NB],
-                                               const double2 (&Xo)[P][NB],
-                                               double (&acc)[AnaChunk<NB>::V]) {
-    constexpr int C = AnaChunk<NB>::C;
+// the block's values summed over the wave's 64 lanes: two lane swaps halve the values a lane
+// holds twice (the 16-lane row r = L / 16 then holds values Q r .. Q r + Q - 1, each summed over
+// four lanes), then through LDS lane L sums value L / 2 over half L % 2 of its row
+__device__ __forceinline__ double ana_reduce(double (&acc)[kAnaV], double *red) {
 #pragma unroll
-    for (int c = 0; c < C; c++) {
-        if (!FULL && c0 + c > lmax) break;
-        double cur[P];
-        st.template step<INJ>(c0 + c, A[c], cur);
+    for (int i = 0; i < kAnaV / 2; i++) acc[i] = swap_add<true>(acc[i], acc[i + kAnaV / 2]);
 #pragma unroll
-        for (int j = 0; j < NB; j++)
+    for (int i = 0; i < kAnaQ; i++) acc[i] = swap_add<false>(acc[i], acc[i + kAnaQ]);
+    double *w = red + ana_slot(threadIdx.x);
 #pragma unroll
-            for (int k = 0; k < P; k++) {
-                const double2 X = (c & 1) ? Xo[k][j] : Xe[k][j];
-                acc[2 * (c * NB + j)] = fma(cur[k], X.x, acc[2 * (c * NB + j)]);
-                acc[2 * (c * NB + j) + 1] = fma(cur[k], X.y, acc[2 * (c * NB + j) + 1]);
-            }
-    }
+    for (int i = 0; i < kAnaQ; i += 2)
+        *reinterpret_cast<double2 *>(w + i) = make_double2(acc[i], acc[i + 1]);
+    __syncthreads();
+    const int v = threadIdx.x >> 1, h = threadIdx.x & 1, r = v / kAnaQ, j = v - kAnaQ * r;
+    const double *x = red + ana_slot(16 * r + 8 * h) + j;
+    double s = 0.0;
+#pragma unroll
+    for (int q = 0; q < 8; q++) s += x[q * kAnaQ];
+    s += __shfl_xor(s, 1);
+    __syncthreads();
+    return s;
 }
 
-template <int NB, int P, bool PF>
+template <int P>
 __device__ __forceinline__ void analysis_one_m(int m, int g, const double2 *__restrict__ phase,
                                                int nring, int nm, const double *__restrict__ Atab,
                                                const long *__restrict__ mofs,
-                                               const int *__restrict__ lstart,
-                                               const double2 *__restrict__ seed,
+                                               const int *__restrict__ kstart,
+                                               const double2 *__restrict__ entry,
                                                const double *__restrict__ zp,
-                                               double2 *__restrict__ apart, long nalm,
-                                               int nb_total, int lmax, int npair, int b0,
+                                               double2 *__restrict__ apart, int lmax, int npair,
                                                double *red) {
-    constexpr int C = AnaChunk<NB>::C, V = AnaChunk<NB>::V, LD = AnaChunk<NB>::LD, Q = AnaChunk<NB>::Q;
-    static_assert(V == 32, "reduction assumes 32 values per lane");
     PairState<P> st;
-    st.load(m, g, npair, lmax, zp, lstart, seed);
-    const long off = mofs[m] - m;
+    const int nl = lmax - m + 1, nblk = (nl + kLegBlock - 1) / kLegBlock;
+    st.load(m, g, npair, nblk, zp, kstart, entry);
+    const long off = mofs[m];
     const double *Am = Atab + off;
+    double2 *out = apart + off;
     // X_even = G_N + G_S (l + m even), X_odd = G_N - G_S; the equator ring counts once.
-    double2 Xe[P][NB], Xo[P][NB];
+    double2 X[2][P];
 #pragma unroll
     for (int k = 0; k < P; k++) {
         const int p = g * kW * P + k * kW + (int)threadIdx.x;
         const bool valid = p < npair;
         const int rN = p, rS = nring - 1 - p;
-#pragma unroll
-        for (int j = 0; j < NB; j++) {
-            const double2 *G = phase + (long)(b0 + j) * nm * nring + m;  // [map][ring][m]
-            double2 gN = valid ? G[(long)rN * nm] : make_double2(0.0, 0.0);
-            double2 gS = (valid && rS != rN) ? G[(long)rS * nm] : make_double2(0.0, 0.0);
-            Xe[k][j] = make_double2(gN.x + gS.x, gN.y + gS.y);
-            Xo[k][j] = make_double2(gN.x - gS.x, gN.y - gS.y);
-        }
+        const double2 *G = phase + m;  // [ring][m]
+        const double2 gN = valid ? G[(long)rN * nm] : make_double2(0.0, 0.0);
+        const double2 gS = (valid && rS != rN) ? G[(long)rS * nm] : make_double2(0.0, 0.0);
+        X[0][k] = make_double2(gN.x + gS.x, gN.y + gS.y);
+        X[1][k] = make_double2(gN.x - gS.x, gN.y - gS.y);
     }
-    double2 *outg = apart + (long)g * nb_total * nalm;
-    // l in [m, lo) receive no contribution from any pair of this group
-    const int lo = st.lo - ((st.lo + m) & 1);  // chunks start at even l + m
-    for (int l = m + (int)threadIdx.x; l < min(lo, lmax + 1); l += kW)
+    // values of l before the group's first block receive no contribution
+    for (int r = threadIdx.x; r < min(st.klo * kLegBlock, nl); r += kW) out[r] = make_double2(0.0, 0.0);
+    for (int blk = st.klo; blk < nblk; blk++) {
+        const int r0 = blk * kLegBlock;
+        st.enter(blk);
+        double acc[kAnaV];
+        auto row = [&](int c, double A) __attribute__((always_inline)) {
+            double cur[P];
+            st.step(A, cur);
+            double x = 0.0, y = 0.0;
 #pragma unroll
-        for (int j = 0; j < NB; j++) outg[(long)(b0 + j) * nalm + off + l] = make_double2(0.0, 0.0);
-
-    double Acur[C], Anxt[C];
-    if (PF && lo + C - 1 <= lmax) {
-#pragma unroll
-        for (int c = 0; c < C; c++) Acur[c] = Am[lo + c];
-    }
-    for (int c0 = lo; c0 <= lmax; c0 += C) {
-        double acc[V];
-#pragma unroll
-        for (int v = 0; v < V; v++) acc[v] = 0.0;
-        const bool inj = c0 <= st.hi;
-        if (c0 + C - 1 <= lmax) {
-            if (PF) {
-                if (c0 + 2 * C - 1 <= lmax) {
-#pragma unroll
-                    for (int c = 0; c < C; c++) Anxt[c] = Am[c0 + C + c];
-                }
-            } else {
-#pragma unroll
-                for (int c = 0; c < C; c++) Acur[c] = Am[c0 + c];
+            for (int k = 0; k < P; k++) {
+                const double2 q = X[c & 1][k];
+                x = k ? fma(cur[k], q.x, x) : cur[k] * q.x;
+                y = k ? fma(cur[k], q.y, y) : cur[k] * q.y;
             }
-            if (inj)
-                analysis_chunk<NB, P, true, true>(c0, lmax, st, Acur, Xe, Xo, acc);
-            else
-                analysis_chunk<NB, P, false, true>(c0, lmax, st, Acur, Xe, Xo, acc);
-            if (PF) {
+            acc[2 * c] = x;
+            acc[2 * c + 1] = y;
+        };
+        if (r0 + kLegBlock <= nl) {
+            double A[kLegBlock];
 #pragma unroll
-                for (int c = 0; c < C; c++) Acur[c] = Anxt[c];
-            }
+            for (int c = 0; c < kLegBlock; c++) A[c] = Am[r0 + c];
+#pragma unroll
+            for (int c = 0; c < kLegBlock; c++) row(c, A[c]);
         } else {
 #pragma unroll
-            for (int c = 0; c < C; c++) Acur[c] = (c0 + c <= lmax) ? Am[c0 + c] : 0.0;
-            analysis_chunk<NB, P, true, false>(c0, lmax, st, Acur, Xe, Xo, acc);
+            for (int c = 0; c < kLegBlock; c++) {
+                acc[2 * c] = acc[2 * c + 1] = 0.0;
+                if (r0 + c < nl) row(c, Am[r0 + c]);
+            }
         }
-        // sum over the 64 lanes.  P < 4: two lane swaps halve the values a lane holds twice
-        // (the 16-lane row r = L / 16 then holds values Q r .. Q r + Q - 1, each summed over
-        // four lanes), then through LDS lane L sums value v = L / 2 over half L % 2 of its
-        // row.  P = 4 (whose registers the swaps would exceed): all values through LDS, lane
-        // L summing value L / 2 over half L % 2 of the wave.
-        const int v = threadIdx.x >> 1, h = threadIdx.x & 1;
-        double s = 0.0;
-        if constexpr (P < 4) {
-            double h1[V / 2], h2[Q];
-#pragma unroll
-            for (int i = 0; i < V / 2; i++) h1[i] = swap_add<true>(acc[i], acc[i + V / 2]);
-#pragma unroll
-            for (int i = 0; i < Q; i++) h2[i] = swap_add<false>(h1[i], h1[i + Q]);
-#pragma unroll
-            for (int i = 0; i < Q; i += 2)
-                *reinterpret_cast<double2 *>(&red[threadIdx.x * Q + i]) = make_double2(h2[i], h2[i + 1]);
-            __syncthreads();
-            const int r = v / Q, jq = v - Q * r;
-#pragma unroll
-            for (int q = 0; q < 8; q++) s += red[(16 * r + 8 * h + q) * Q + jq];
-        } else {
-#pragma unroll
-            for (int i = 0; i < V; i += 2)
-                *reinterpret_cast<double2 *>(&red[threadIdx.x * LD + i]) = make_double2(acc[i], acc[i + 1]);
-            __syncthreads();
-#pragma unroll 8
-            for (int q = 0; q < 32; q++) s += red[(h * 32 + q) * LD + v];
-        }
-        s += __shfl_xor(s, 1);
-        __syncthreads();
-        // v = 2 (c NB + j) + comp
-        const int comp = v & 1, cj = v >> 1, c = cj / NB, j = cj - c * NB;
-        const int l = c0 + c;
-        if (h == 0 && l <= lmax)
-            reinterpret_cast<double *>(outg + (long)(b0 + j) * nalm + off + l)[comp] = s;
+        const double s = ana_reduce(acc, red);
+        // lane 2 v holds value v = 2 c + (0 re, 1 im): the block's coefficients in order
+        const int v = threadIdx.x >> 1;
+        if ((threadIdx.x & 1) == 0 && r0 + (v >> 1) < nl) reinterpret_cast<double *>(out + r0)[v] = s;
     }
 }
 
-template <int NB, int P, bool PF>
+template <int P, int ROWS>
 __global__ void __launch_bounds__(kW)
 k_leg_analysis(const double2 *__restrict__ phase, int nring, int nm,
                const double *__restrict__ Atab, const long *__restrict__ mofs,
-               const int *__restrict__ lstart, const double2 *__restrict__ seed,
-               const double *__restrict__ zp, double2 *__restrict__ apart, long nalm,
-               int nb_total, int lmax, int npair) {
-    __shared__ __align__(16) double red[kW * (P < 4 ? AnaChunk<NB>::Q : AnaChunk<NB>::LD)];
-    const int g = blockIdx.x, mi = blockIdx.y, b0 = blockIdx.z * NB;
-    const int npass = (lmax - mi > mi) ? 2 : 1;
+               const int *__restrict__ kstart, const double2 *__restrict__ entry,
+               const double *__restrict__ zp, double2 *__restrict__ apart, long nalm, int lmax,
+               int npair, int ngrp) {
+    __shared__ __align__(16) double red[kAnaLds];
+    const int nmi = ROWS == 2 ? (lmax + 2) / 2 : nm;
+    const LegItem it = leg_item(ngrp, nmi);
+    if (it.mi >= nmi) return;
+    const int b = blockIdx.y;
+    const int npass = (ROWS == 2 && lmax - it.mi > it.mi) ? 2 : 1;
     for (int pass = 0; pass < npass; pass++)
-        analysis_one_m<NB, P, PF>(pass == 0 ? mi : lmax - mi, g, phase, nring, nm, Atab, mofs,
-                                  lstart, seed, zp, apart, nalm, nb_total, lmax, npair, b0, red);
+        analysis_one_m<P>(pass == 0 ? it.mi : lmax - it.mi, it.g, phase + (long)b * nm * nring, nring,
+                          nm, Atab, mofs, kstart, entry, zp,
+                          apart + ((long)it.g * gridDim.y + b) * nalm, lmax, npair, red);
 }
 
 // ---------------------------------------------------------------------------------------
 // Variant tables: index = tuning choice stored in the plan.
 // ---------------------------------------------------------------------------------------
 using SynthFn = void (*)(const double2 *, long, const double *, const long *, const int *,
-                         const double2 *, const double *, double2 *, int, int, int, int);
+                         const double2 *, const double *, double2 *, int, int, int, int, int);
 using AnaFn = void (*)(const double2 *, int, int, const double *, const long *, const int *,
                        const double2 *, const double *, double2 *, long, int, int, int);
 
+struct LegVariant {
+    int pairs, rows;  // ring pairs per lane, values of m per wave
+};
 static const SynthFn kSynth[] = {
-    k_leg_synth<1, 1, 8, false>, k_leg_synth<1, 2, 8, false>, k_leg_synth<1, 4, 8, false>,
-    k_leg_synth<1, 1, 8, true>,  k_leg_synth<1, 2, 8, true>,  k_leg_synth<1, 4, 8, true>,
-    k_leg_synth<1, 1, 4, true>,  k_leg_synth<1, 2, 4, true>,  k_leg_synth<1, 4, 4, true>,
+    k_leg_synth<1, 8, 2>, k_leg_synth<2, 8, 2>, k_leg_synth<4, 8, 2>,
+    k_leg_synth<1, 8, 1>, k_leg_synth<2, 8, 1>, k_leg_synth<4, 8, 1>,
+    k_leg_synth<1, 4, 1>, k_leg_synth<2, 4, 1>, k_leg_synth<4, 4, 1>,
 };
-static const int kSynthP[] = {1, 2, 4, 1, 2, 4, 1, 2, 4};
+static const LegVariant kSynthVar[] = {{1, 2}, {2, 2}, {4, 2}, {1, 1}, {2, 1}, {4, 1}, {1, 1}, {2, 1}, {4, 1}};
 static const AnaFn kAna[] = {
-    k_leg_analysis<1, 1, false>, k_leg_analysis<1, 2, false>, k_leg_analysis<1, 4, false>,
-    k_leg_analysis<1, 1, true>,  k_leg_analysis<1, 2, true>,  k_leg_analysis<1, 4, true>,
+    k_leg_analysis<1, 2>, k_leg_analysis<2, 2>, k_leg_analysis<4, 2>,
+    k_leg_analysis<1, 1>, k_leg_analysis<2, 1>, k_leg_analysis<4, 1>,
 };
-static const int kAnaP[] = {1, 2, 4, 1, 2, 4};
+static const LegVariant kAnaVar[] = {{1, 2}, {2, 2}, {4, 2}, {1, 1}, {2, 1}, {4, 1}};
 
 int leg_synth_variants() { return (int)(sizeof(kSynth) / sizeof(kSynth[0])); }
 int leg_analysis_variants() { return (int)(sizeof(kAna) / sizeof(kAna[0])); }
-int leg_synth_pairs_per_lane(int v) { return kSynthP[v]; }
-int leg_analysis_pairs_per_lane(int v) { return kAnaP[v]; }
+int leg_synth_pairs_per_lane(int v) { return kSynthVar[v].pairs; }
+int leg_analysis_pairs_per_lane(int v) { return kAnaVar[v].pairs; }
 
 static int groups(int npair, int P) { return (npair + 64 * P - 1) / (64 * P); }
 
 int launch_leg_synth(const Plan &p, const double2 *alm_scaled, double2 *phase, int nb) {
-    const int v = p.synth_variant;
-    dim3 grid(groups(p.npair, kSynthP[v]), (p.lmax + 2) / 2, nb);
-    hipLaunchKernelGGL(kSynth[v], grid, dim3(kW), 0, p.stream, alm_scaled, p.nalm, p.d_A,
-                       p.d_mofs, p.d_lstart, p.d_seed, p.d_z, phase, p.lmax, p.npair, p.nring,
-                       p.nm);
+    const LegVariant v = kSynthVar[p.synth_variant];
+    const int ngrp = groups(p.npair, v.pairs);
+    hipLaunchKernelGGL(kSynth[p.synth_variant], leg_grid(ngrp, v.rows == 2 ? (p.lmax + 2) / 2 : p.nm, nb),
+                       dim3(kW), 0, p.stream, alm_scaled, p.nalm, p.d_A, p.d_mofs, p.d_kstart,
+                       p.d_entry, p.d_z, phase, p.lmax, p.npair, p.nring, p.nm, ngrp);
     MFWF_HIP(hipGetLastError());
     return MFWF_OK;
 }
 
 int launch_leg_analysis(const Plan &p, const double2 *phase, double2 *apart, int nb) {
-    const int v = p.ana_variant;
-    dim3 grid(groups(p.npair, kAnaP[v]), (p.lmax + 2) / 2, nb);
-    hipLaunchKernelGGL(kAna[v], grid, dim3(kW), 0, p.stream, phase, p.nring, p.nm, p.d_A,
-                       p.d_mofs, p.d_lstart, p.d_seed, p.d_z, apart, p.nalm, nb, p.lmax,
-                       p.npair);
+    const LegVariant v = kAnaVar[p.ana_variant];
+    const int ngrp = groups(p.npair, v.pairs);
+    hipLaunchKernelGGL(kAna[p.ana_variant], leg_grid(ngrp, v.rows == 2 ? (p.lmax + 2) / 2 : p.nm, nb),
+                       dim3(kW), 0, p.stream, phase, p.nring, p.nm, p.d_A, p.d_mofs, p.d_kstart,
+                       p.d_entry, p.d_z, apart, p.nalm, p.lmax, p.npair, ngrp);
     MFWF_HIP(hipGetLastError());
     return MFWF_OK;
 }

@@ -68,8 +68,10 @@ struct Plan {
     double *d_z = nullptr;       // [npair] cos(theta) of the north ring of each pair
     double *d_A = nullptr;       // [nalm] A_lm of mu_l = A z mu_{l-1} - mu_{l-2}
     double *d_c = nullptr;       // [nalm] c_lm, lambda_lm = c_lm mu_lm
-    int *d_lstart = nullptr;     // [nm][npair]
-    double2 *d_seed = nullptr;   // [nm][npair] (mu_{l_s - 1}, mu_{l_s})
+    int *d_lstart = nullptr;     // [nm][npair] first l (FP32 form's tables)
+    double2 *d_seed = nullptr;   // [nm][npair] (mu_{l_s - 1}, mu_{l_s}) (FP32 form's tables)
+    int *d_kstart = nullptr;     // [nm][npair] first block of kLegBlock values of l (FP64 kernels)
+    double2 *d_entry = nullptr;  // [nm][npair] recurrence state entering it (FP64 kernels)
     PairFFT *d_pfft = nullptr;   // [npair]
     double2 *d_tw = nullptr;     // [fftmax] exp(-2 pi i k / fftmax)
     double2 *d_twlo = nullptr;   // [64] exp(-2 pi i t / fftmax)

@@ -39,13 +39,13 @@ __device__ __forceinline__ void cfma(double2 &acc, double f, double2 a) {
     acc.y = fma(f, a.y, acc.y);
 }
 
-template <bool INJ, int PAR, int P>
-__device__ __forceinline__ void pol_synth_step(int l, PairState<P> &st, const double (&zz)[P],
+template <int PAR, int P>
+__device__ __forceinline__ void pol_synth_step(PairState<P> &st, const double (&zz)[P],
                                                double A, const double *__restrict__ pc,
                                                double2 aT, double2 aE, double2 aB,
                                                PolSynthAcc (&acc)[P]) {
     double cur[P];
-    st.template step<INJ>(l, A, cur);
+    st.step(A, cur);
 #pragma unroll
     for (int k = 0; k < P; k++) {
         const double mu = cur[k], mup = st.u2[k], z = st.z[k];
@@ -65,17 +65,17 @@ __device__ __forceinline__ void pol_synth_one_m(int m, int g, int b, const doubl
                                                 long nalm, const double *__restrict__ Atab,
                                                 const double *__restrict__ pctab,
                                                 const long *__restrict__ mofs,
-                                                const int *__restrict__ lstart,
-                                                const double2 *__restrict__ seed,
+                                                const int *__restrict__ kstart,
+                                                const double2 *__restrict__ entry,
                                                 const double *__restrict__ zp,
                                                 double2 *__restrict__ phase, int lmax,
                                                 int npair, int nring, int nm) {
     PairState<P> st;
-    st.load(m, g, npair, lmax, zp, lstart, seed);
+    st.load(m, g, npair, (lmax - m + kLegBlock) / kLegBlock, zp, kstart, entry);
     double zz[P];
 #pragma unroll
     for (int k = 0; k < P; k++) zz[k] = st.z[k] * st.z[k];
-    const long off = mofs[m] - m;
+    const long off = mofs[m];
     const double *Am = Atab + off;
     const double *pcm = pctab + 5 * off;
     const double2 *aT = alm + (3L * b + 0) * nalm + off;
@@ -88,24 +88,21 @@ __device__ __forceinline__ void pol_synth_one_m(int m, int g, int b, const doubl
         for (int q = 0; q < 2; q++)
             acc[k].T[q] = acc[k].P[q] = acc[k].R[q] = acc[k].X[q] = acc[k].Y[q] = make_double2(0.0, 0.0);
 
-    int l = st.lo - ((st.lo + m) & 1);  // blocks start at even l + m
-    for (; l + U - 1 <= lmax; l += U) {
-        const bool inj = l <= st.hi;
+    const int nl = lmax - m + 1;  // values of l, from r = l - m = 0
+    int r = st.klo * kLegBlock;
+    for (; r + U <= nl; r += U) {
+        if (r % kLegBlock == 0) st.enter(r / kLegBlock);
 #pragma unroll
-        for (int u = 0; u < U; u++) {
-            const int lu = l + u;
-            if (inj) {
-                if (u & 1) pol_synth_step<true, 1>(lu, st, zz, Am[lu], pcm + 5 * lu, aT[lu], aE[lu], aB[lu], acc);
-                else pol_synth_step<true, 0>(lu, st, zz, Am[lu], pcm + 5 * lu, aT[lu], aE[lu], aB[lu], acc);
-            } else {
-                if (u & 1) pol_synth_step<false, 1>(lu, st, zz, Am[lu], pcm + 5 * lu, aT[lu], aE[lu], aB[lu], acc);
-                else pol_synth_step<false, 0>(lu, st, zz, Am[lu], pcm + 5 * lu, aT[lu], aE[lu], aB[lu], acc);
-            }
+        for (int u = 0; u < U; u += 2) {
+            pol_synth_step<0>(st, zz, Am[r + u], pcm + 5 * (r + u), aT[r + u], aE[r + u], aB[r + u], acc);
+            pol_synth_step<1>(st, zz, Am[r + u + 1], pcm + 5 * (r + u + 1), aT[r + u + 1], aE[r + u + 1],
+                              aB[r + u + 1], acc);
         }
     }
-    for (; l <= lmax; l++) {
-        if ((l + m) & 1) pol_synth_step<true, 1>(l, st, zz, Am[l], pcm + 5 * l, aT[l], aE[l], aB[l], acc);
-        else pol_synth_step<true, 0>(l, st, zz, Am[l], pcm + 5 * l, aT[l], aE[l], aB[l], acc);
+    if (r < nl && r % kLegBlock == 0) st.enter(r / kLegBlock);
+    for (; r < nl; r++) {
+        if (r & 1) pol_synth_step<1>(st, zz, Am[r], pcm + 5 * r, aT[r], aE[r], aB[r], acc);
+        else pol_synth_step<0>(st, zz, Am[r], pcm + 5 * r, aT[r], aE[r], aB[r], acc);
     }
 
 #pragma unroll
@@ -143,14 +140,17 @@ template <int U, int P>
 __global__ void __launch_bounds__(kW)
 k_leg_synth_pol(const double2 *__restrict__ alm, long nalm, const double *__restrict__ Atab,
                 const double *__restrict__ pctab, const long *__restrict__ mofs,
-                const int *__restrict__ lstart, const double2 *__restrict__ seed,
+                const int *__restrict__ kstart, const double2 *__restrict__ entry,
                 const double *__restrict__ zp, double2 *__restrict__ phase, int lmax, int npair,
-                int nring, int nm) {
-    const int g = blockIdx.x, mi = blockIdx.y, b = blockIdx.z;
+                int nring, int nm, int ngrp) {
+    const int nmi = (lmax + 2) / 2;
+    const LegItem it = leg_item(ngrp, nmi);
+    if (it.mi >= nmi) return;
+    const int g = it.g, mi = it.mi, b = blockIdx.y;
     const int npass = (lmax - mi > mi) ? 2 : 1;
     for (int pass = 0; pass < npass; pass++)
-        pol_synth_one_m<U, P>(pass == 0 ? mi : lmax - mi, g, b, alm, nalm, Atab, pctab, mofs, lstart,
-                              seed, zp, phase, lmax, npair, nring, nm);
+        pol_synth_one_m<U, P>(pass == 0 ? mi : lmax - mi, g, b, alm, nalm, Atab, pctab, mofs, kstart,
+                              entry, zp, phase, lmax, npair, nring, nm);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -167,12 +167,12 @@ struct PolAnaIn {
     double2 QP, QM, UP, UM;  // (G_N +- G_S) / s^2 for Q and U
 };
 
-template <bool INJ, int PAR, int P>
-__device__ __forceinline__ void pol_ana_step(int l, int c, PairState<P> &st, const double (&zz)[P],
+template <int PAR, int P>
+__device__ __forceinline__ void pol_ana_step(int c, PairState<P> &st, const double (&zz)[P],
                                              double A, const double *__restrict__ pc,
                                              const PolAnaIn (&in)[P], double (&acc)[kPV]) {
     double cur[P];
-    st.template step<INJ>(l, A, cur);
+    st.step(A, cur);
     double *a = acc + 6 * c;
 #pragma unroll
     for (int k = 0; k < P; k++) {  // the lane's pairs, summed in order
@@ -199,14 +199,14 @@ __device__ __forceinline__ void pol_analysis_one_m(int m, int g, int b,
                                                    int nm, const double *__restrict__ Atab,
                                                    const double *__restrict__ pctab,
                                                    const long *__restrict__ mofs,
-                                                   const int *__restrict__ lstart,
-                                                   const double2 *__restrict__ seed,
+                                                   const int *__restrict__ kstart,
+                                                   const double2 *__restrict__ entry,
                                                    const double *__restrict__ zp,
                                                    double2 *__restrict__ apart, long nalm,
                                                    int nb_total, int lmax, int npair,
                                                    double *red) {
     PairState<P> st;
-    st.load(m, g, npair, lmax, zp, lstart, seed);
+    st.load(m, g, npair, (lmax - m + kLegBlock) / kLegBlock, zp, kstart, entry);
     double zz[P];
 #pragma unroll
     for (int k = 0; k < P; k++) zz[k] = st.z[k] * st.z[k];
@@ -236,7 +236,7 @@ __device__ __forceinline__ void pol_analysis_one_m(int m, int g, int b,
         in[k].UM = make_double2(is2 * (uN.x - uS.x), is2 * (uN.y - uS.y));
     }
     double2 *outg = apart + (long)g * nb_total * 3 * nalm;
-    const int lo = st.lo - ((st.lo + m) & 1);
+    const int lo = m + st.klo * kLegBlock;
     for (int l = m + (int)threadIdx.x; l < min(lo, lmax + 1); l += kW)
         for (int c = 0; c < 3; c++) outg[(3L * b + c) * nalm + off + l] = make_double2(0.0, 0.0);
 
@@ -261,19 +261,19 @@ __device__ __forceinline__ void pol_analysis_one_m(int m, int g, int b,
         double acc[kPV];
 #pragma unroll
         for (int v = 0; v < kPV; v++) acc[v] = 0.0;
-        const bool inj = c0 <= st.hi;
-        if (c0 + kPC - 1 <= lmax && !inj) {
+        if ((c0 - m) % kLegBlock == 0) st.enter((c0 - m) / kLegBlock);
+        if (c0 + kPC - 1 <= lmax) {
 #pragma unroll
             for (int c = 0; c < kPC; c++) {
-                if (c & 1) pol_ana_step<false, 1>(c0 + c, c, st, zz, cf[c].A, cf[c].pc, in, acc);
-                else pol_ana_step<false, 0>(c0 + c, c, st, zz, cf[c].A, cf[c].pc, in, acc);
+                if (c & 1) pol_ana_step<1>(c, st, zz, cf[c].A, cf[c].pc, in, acc);
+                else pol_ana_step<0>(c, st, zz, cf[c].A, cf[c].pc, in, acc);
             }
         } else {
 #pragma unroll
             for (int c = 0; c < kPC; c++) {
                 if (c0 + c > lmax) break;
-                if (c & 1) pol_ana_step<true, 1>(c0 + c, c, st, zz, cf[c].A, cf[c].pc, in, acc);
-                else pol_ana_step<true, 0>(c0 + c, c, st, zz, cf[c].A, cf[c].pc, in, acc);
+                if (c & 1) pol_ana_step<1>(c, st, zz, cf[c].A, cf[c].pc, in, acc);
+                else pol_ana_step<0>(c, st, zz, cf[c].A, cf[c].pc, in, acc);
             }
         }
         // sum over the 64 lanes: two lane swaps halve the values a lane holds twice (the
@@ -317,15 +317,19 @@ template <int P>
 __global__ void __launch_bounds__(kW)
 k_leg_analysis_pol(const double2 *__restrict__ phase, int nring, int nm,
                    const double *__restrict__ Atab, const double *__restrict__ pctab,
-                   const long *__restrict__ mofs, const int *__restrict__ lstart,
-                   const double2 *__restrict__ seed, const double *__restrict__ zp,
-                   double2 *__restrict__ apart, long nalm, int nb_total, int lmax, int npair) {
+                   const long *__restrict__ mofs, const int *__restrict__ kstart,
+                   const double2 *__restrict__ entry, const double *__restrict__ zp,
+                   double2 *__restrict__ apart, long nalm, int nb_total, int lmax, int npair,
+                   int ngrp) {
     __shared__ __align__(16) double red[kW * kPQ];
-    const int g = blockIdx.x, mi = blockIdx.y, b = blockIdx.z;
+    const int nmi = (lmax + 2) / 2;
+    const LegItem it = leg_item(ngrp, nmi);
+    if (it.mi >= nmi) return;
+    const int g = it.g, mi = it.mi, b = blockIdx.y;
     const int npass = (lmax - mi > mi) ? 2 : 1;
     for (int pass = 0; pass < npass; pass++)
         pol_analysis_one_m<P>(pass == 0 ? mi : lmax - mi, g, b, phase, nring, nm, Atab, pctab, mofs,
-                              lstart, seed, zp, apart, nalm, nb_total, lmax, npair, red);
+                              kstart, entry, zp, apart, nalm, nb_total, lmax, npair, red);
 }
 
 // ring pairs per lane of the analysis: two where there are pairs for more than one wave
@@ -341,11 +345,12 @@ int launch_leg_synth_pol(const Plan &p, const double2 *alm_scaled, double2 *phas
     // two ring pairs per lane where there are pairs for more than one wave: each value of l's
     // coefficients and harmonics (wave-uniform loads) then serve twice the arithmetic
     const int P = p.npair > kW ? 2 : 1;
-    dim3 grid((p.npair + kW * P - 1) / (kW * P), (p.lmax + 2) / 2, nb);
+    const int ngrp = (p.npair + kW * P - 1) / (kW * P);
+    const dim3 grid = leg_grid(ngrp, (p.lmax + 2) / 2, nb);
 #define MFWF_SYNPOL(PP)                                                                          \
     hipLaunchKernelGGL((k_leg_synth_pol<4, PP>), grid, dim3(kW), 0, p.stream, alm_scaled, p.nalm,   \
-                       p.d_A, p.d_pc, p.d_mofs, p.d_lstart, p.d_seed, p.d_z, phase, p.lmax,         \
-                       p.npair, p.nring, p.nm)
+                       p.d_A, p.d_pc, p.d_mofs, p.d_kstart, p.d_entry, p.d_z, phase, p.lmax,        \
+                       p.npair, p.nring, p.nm, ngrp)
     if (P == 2) MFWF_SYNPOL(2);
     else MFWF_SYNPOL(1);
 #undef MFWF_SYNPOL
@@ -354,15 +359,16 @@ int launch_leg_synth_pol(const Plan &p, const double2 *alm_scaled, double2 *phas
 }
 
 int launch_leg_analysis_pol(const Plan &p, const double2 *phase, double2 *apart, int nb) {
-    dim3 grid(pol_ana_groups(p), (p.lmax + 2) / 2, nb);
+    const int ngrp = pol_ana_groups(p);
+    const dim3 grid = leg_grid(ngrp, (p.lmax + 2) / 2, nb);
     if (pol_ana_pairs(p) == 2)
         hipLaunchKernelGGL(k_leg_analysis_pol<2>, grid, dim3(kW), 0, p.stream, phase, p.nring, p.nm,
-                           p.d_A, p.d_pc, p.d_mofs, p.d_lstart, p.d_seed, p.d_z, apart, p.nalm, nb,
-                           p.lmax, p.npair);
+                           p.d_A, p.d_pc, p.d_mofs, p.d_kstart, p.d_entry, p.d_z, apart, p.nalm, nb,
+                           p.lmax, p.npair, ngrp);
     else
         hipLaunchKernelGGL(k_leg_analysis_pol<1>, grid, dim3(kW), 0, p.stream, phase, p.nring, p.nm,
-                           p.d_A, p.d_pc, p.d_mofs, p.d_lstart, p.d_seed, p.d_z, apart, p.nalm, nb,
-                           p.lmax, p.npair);
+                           p.d_A, p.d_pc, p.d_mofs, p.d_kstart, p.d_entry, p.d_z, apart, p.nalm, nb,
+                           p.lmax, p.npair, ngrp);
     MFWF_HIP(hipGetLastError());
     return MFWF_OK;
 }
