@@ -1065,15 +1065,19 @@ int plan_set_cl(Plan &p, const double *cl) {
     return upload(p.d_cl, c, p.stream);
 }
 
-// One captured iteration of a stage, replayed as often as needed.
+// One captured iteration of a stage, replayed as often as needed.  Its launches read the
+// executable graph while they run, so it waits for them before it goes.
 struct StageGraph {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
+    hipStream_t stream = nullptr;
     ~StageGraph() {
+        if (exec) (void)hipStreamSynchronize(stream);
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
     }
     int capture(Plan &p, const double *rho, int nb, double lam) {
+        stream = p.stream;
         MFWF_HIP(hipStreamBeginCapture(p.stream, hipStreamCaptureModeThreadLocal));
         int st = iteration(p, rho, nb, lam, false);
         hipError_t e = hipStreamEndCapture(p.stream, &graph);
@@ -1173,13 +1177,16 @@ static int solve_chunk(Plan &p, const double *input, int nb, double *s_alm_out,
     // in diag[b][6..7] on the device (no host wait)
     long chk_last = -1, chk_prev = -1;
     bool stopped = false;
+    // every stage's graph until the results are in: destroyed between two stages, a graph
+    // would go while its launches still run
+    std::vector<std::unique_ptr<StageGraph>> graphs;
     for (size_t s = 0; s < lam.size() && !stopped; s++) {
         long remaining = its[s];
         if (remaining <= 0) continue;
         last_lam = lam[s];
         prev_at = -1;
         chk_last = chk_prev = -1;
-        std::unique_ptr<StageGraph> sg;
+        StageGraph *sg = nullptr;
         while (remaining > 0) {
             // run up to the next check point: a multiple of n_check, or the last iteration
             const long next = nchk ? std::min(total, (done / nchk + 1) * nchk) : total;
@@ -1188,7 +1195,8 @@ static int solve_chunk(Plan &p, const double *input, int nb, double *s_alm_out,
             const long plain = check ? run - 1 : run;
             if (graph && plain >= 2) {
                 if (!sg) {
-                    sg.reset(new StageGraph());
+                    graphs.push_back(std::make_unique<StageGraph>());
+                    sg = graphs.back().get();
                     MFWF_TRY(sg->capture(p, rho, nb, lam[s]));
                 }
                 MFWF_TRY(sg->launch(p, (int)plain));
