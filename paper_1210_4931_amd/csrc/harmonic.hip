@@ -7,7 +7,7 @@
 // The Legendre kernels work with lambda_lm = c_lm mu_lm: partial analysis sums are
 // multiplied by c_lm here, and the synthesis input is written pre-multiplied by c_lm.
 // Grid (m, map): one block per m row of the packed alm, threads over l.
-#include "mfwf_internal.h"
+#include "reduce.h"
 
 namespace mfwf {
 
@@ -90,20 +90,19 @@ k_harm_diag(const double2 *__restrict__ s, const double2 *__restrict__ prev, lon
     if (threadIdx.x < 3) partial[((long)b * nm + m) * 3 + threadIdx.x] = w * sh[threadIdx.x][0];
 }
 
-// diag[b][1..3] = sums over m in fixed order
-__global__ void k_harm_diag_final(const double *__restrict__ partial, int nm, int nb,
-                                  double *__restrict__ diag) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nb) return;
-    double h = 0.0, d = 0.0, n = 0.0;
-    for (int m = 0; m < nm; m++) {
-        h += partial[((long)b * nm + m) * 3 + 0];
-        d += partial[((long)b * nm + m) * 3 + 1];
-        n += partial[((long)b * nm + m) * 3 + 2];
-    }
-    diag[8 * b + 1] = h;
-    diag[8 * b + 2] = d;
-    diag[8 * b + 3] = n;
+// diag[b][1..3] = sums over m
+__global__ void __launch_bounds__(kSumT)
+k_harm_diag_final(const double *__restrict__ partial, int nm, double *__restrict__ diag) {
+    const int b = blockIdx.x;
+    double s[3];
+    sum_strided<3>(partial + 3L * b * nm, nm, s);
+    if (threadIdx.x < 3) diag[8 * b + 1 + threadIdx.x] = s[threadIdx.x];
+}
+
+int launch_harm_diag_final(const double *partial, int nm, int nb, double *diag, hipStream_t st) {
+    hipLaunchKernelGGL(k_harm_diag_final, dim3(nb), dim3(kSumT), 0, st, partial, nm, diag);
+    MFWF_HIP(hipGetLastError());
+    return MFWF_OK;
 }
 
 int launch_harm_diag(const Plan &p, const double2 *salm, const double2 *salm_prev, int nb,
@@ -111,10 +110,7 @@ int launch_harm_diag(const Plan &p, const double2 *salm, const double2 *salm_pre
     hipLaunchKernelGGL(k_harm_diag, dim3(p.nm, nb), dim3(kHT), 0, p.stream, salm, salm_prev,
                        p.nalm, p.d_mofs, p.d_cl, p.lmax, p.nm, partial);
     MFWF_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_harm_diag_final, dim3((nb + 63) / 64), dim3(64), 0, p.stream, partial,
-                       p.nm, nb, diag);
-    MFWF_HIP(hipGetLastError());
-    return MFWF_OK;
+    return launch_harm_diag_final(partial, p.nm, nb, diag, p.stream);
 }
 
 // Coefficients of rows (maps x components) from the packing of one band limit to another:

@@ -171,6 +171,8 @@ int fail(int status, const std::string &msg);
 int launch_fill(double *x, long n, double v, hipStream_t s);
 int launch_mask_product(const double *ninv, const uint8_t *mask, double *M, long npix,
                         hipStream_t s);
+// out3 = (max, sum, sum) over nblocks triples
+int launch_max_count_final(const double *partial, int nblocks, double *out3, hipStream_t s);
 int launch_reduce_max_count(const double *M, long npix, double *partial, int nblocks,
                             double *out2, hipStream_t s);
 int launch_rho_from_data(const double *d, const double *M, double *rho, long npix, int nb,
@@ -178,6 +180,9 @@ int launch_rho_from_data(const double *d, const double *M, double *rho, long npi
 // out[0] = number of non-finite entries of x[0..n) (partial: nblocks doubles)
 int launch_count_nonfinite(const double *x, long n, double *partial, int nblocks, double *out,
                            hipStream_t s);
+// diag[b][slot] = sum over nblocks of partial[b][block]
+int launch_sum_partials(const double *partial, int nblocks, int nb, double *diag, int slot,
+                        hipStream_t s);
 int launch_chi2_pix(const double *rho, const double *M, const double *smap, long npix, int nb,
                     double lam, double tau, double *partial, int nblocks, double *diag,
                     hipStream_t s);
@@ -297,6 +302,8 @@ enum HarmMode { kHarmWiener = 0, kHarmAnalysis = 1, kHarmInvSqrtC = 2, kHarmCopy
 int launch_harmonic(const Plan &p, const double2 *in, int ngroup, double scale, double lto,
                     int mode, double2 *out_s, double2 *out_sp, double2 *prev, int nb,
                     double lto_per_tau = 0.0);
+// diag[b][1..3] = sums over m of partial[b][m][0..2]
+int launch_harm_diag_final(const double *partial, int nm, int nb, double *diag, hipStream_t st);
 int launch_harm_diag(const Plan &p, const double2 *salm, const double2 *salm_prev, int nb,
                      double *partial, double *diag);
 // coefficients of `rows` maps/components from src's band-limit packing to dst's (zeros above

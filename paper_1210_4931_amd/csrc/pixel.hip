@@ -2,7 +2,7 @@
 // covariance set-up and the pixel part of the fluctuation source of Eq. (9).
 // All of them stream RING-ordered [nb][npix] double arrays: HBM-bound, grid-stride loops
 // with coalesced 8-byte accesses, FP64 reductions in a fixed order (deterministic).
-#include "mfwf_internal.h"
+#include "reduce.h"
 
 namespace mfwf {
 
@@ -88,27 +88,36 @@ __global__ void k_max_count(const double *__restrict__ M, long npix, double *__r
     }
 }
 
-__global__ void k_max_count_final(const double *__restrict__ partial, int nblocks,
-                                  double *__restrict__ out) {
-    if (threadIdx.x != 0) return;
-    double mx = 0.0, cnt = 0.0, bad = 0.0;
-    for (int b = 0; b < nblocks; b++) {
-        mx = fmax(mx, partial[3 * b]);
-        cnt += partial[3 * b + 1];
-        bad += partial[3 * b + 2];
+__global__ void __launch_bounds__(kSumT)
+k_max_count_final(const double *__restrict__ partial, int nblocks, double *__restrict__ out) {
+    __shared__ double sh[kSumT];
+    double mx = 0.0, s[3];
+    for (int b = threadIdx.x; b < nblocks; b += kSumT) mx = fmax(mx, partial[3 * b]);
+    sh[threadIdx.x] = mx;
+    __syncthreads();
+    for (int w = kSumT / 2; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + w]);
+        __syncthreads();
     }
-    out[0] = mx;
-    out[1] = cnt;
-    out[2] = bad;
+    sum_strided<3>(partial, nblocks, s);
+    if (threadIdx.x == 0) {
+        out[0] = sh[0];
+        out[1] = s[1];
+        out[2] = s[2];
+    }
+}
+
+int launch_max_count_final(const double *partial, int nblocks, double *out3, hipStream_t s) {
+    hipLaunchKernelGGL(k_max_count_final, dim3(1), dim3(kSumT), 0, s, partial, nblocks, out3);
+    MFWF_HIP(hipGetLastError());
+    return MFWF_OK;
 }
 
 int launch_reduce_max_count(const double *M, long npix, double *partial, int nblocks,
                             double *out3, hipStream_t s) {
     hipLaunchKernelGGL(k_max_count, dim3(nblocks), dim3(kThreads), 0, s, M, npix, partial);
     MFWF_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_max_count_final, dim3(1), dim3(64), 0, s, partial, nblocks, out3);
-    MFWF_HIP(hipGetLastError());
-    return MFWF_OK;
+    return launch_max_count_final(partial, nblocks, out3, s);
 }
 
 // Non-finite entries of x[0..n) per block (a solve's source rho: data on masked pixels has
@@ -128,18 +137,18 @@ __global__ void k_count_nonfinite(const double *__restrict__ x, long n, double *
     if (threadIdx.x == 0) partial[blockIdx.x] = sh[0];
 }
 
-__global__ void k_sum_final(const double *__restrict__ partial, int nblocks, double *__restrict__ out) {
-    if (threadIdx.x != 0) return;
-    double s = 0.0;
-    for (int b = 0; b < nblocks; b++) s += partial[b];
-    out[0] = s;
+__global__ void __launch_bounds__(kSumT)
+k_sum_final(const double *__restrict__ partial, int nblocks, double *__restrict__ out) {
+    double s[1];
+    sum_strided<1>(partial, nblocks, s);
+    if (threadIdx.x == 0) out[0] = s[0];
 }
 
 int launch_count_nonfinite(const double *x, long n, double *partial, int nblocks, double *out,
                            hipStream_t s) {
     hipLaunchKernelGGL(k_count_nonfinite, dim3(nblocks), dim3(kThreads), 0, s, x, n, partial);
     MFWF_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(64), 0, s, partial, nblocks, out);
+    hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(kSumT), 0, s, partial, nblocks, out);
     MFWF_HIP(hipGetLastError());
     return MFWF_OK;
 }
@@ -184,14 +193,20 @@ __global__ void k_chi2_pix(const double *__restrict__ rho, const double *__restr
     if (threadIdx.x == 0) partial[(long)blockIdx.y * gridDim.x + blockIdx.x] = acc[0];
 }
 
-// diag[b][0] = sum_block partial[b][block]  (one thread per map, fixed order)
-__global__ void k_sum_partials(const double *__restrict__ partial, int nblocks, int nb,
-                               double *__restrict__ diag, int slot) {
-    int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nb) return;
-    double acc = 0.0;
-    for (int k = 0; k < nblocks; k++) acc += partial[(long)b * nblocks + k];
-    diag[8 * b + slot] = acc;
+// diag[b][slot] = sum_block partial[b][block]
+__global__ void __launch_bounds__(kSumT)
+k_sum_partials(const double *__restrict__ partial, int nblocks, double *__restrict__ diag, int slot) {
+    const int b = blockIdx.x;
+    double s[1];
+    sum_strided<1>(partial + (long)b * nblocks, nblocks, s);
+    if (threadIdx.x == 0) diag[8 * b + slot] = s[0];
+}
+
+int launch_sum_partials(const double *partial, int nblocks, int nb, double *diag, int slot,
+                        hipStream_t s) {
+    hipLaunchKernelGGL(k_sum_partials, dim3(nb), dim3(kSumT), 0, s, partial, nblocks, diag, slot);
+    MFWF_HIP(hipGetLastError());
+    return MFWF_OK;
 }
 
 int launch_chi2_pix(const double *rho, const double *M, const double *smap, long npix, int nb,
@@ -200,10 +215,7 @@ int launch_chi2_pix(const double *rho, const double *M, const double *smap, long
     hipLaunchKernelGGL(k_chi2_pix, dim3(nblocks, nb), dim3(kThreads), 0, s, rho, M, smap, npix,
                        lam, tau, partial);
     MFWF_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_sum_partials, dim3((nb + 63) / 64), dim3(64), 0, s, partial, nblocks,
-                       nb, diag, 0);
-    MFWF_HIP(hipGetLastError());
-    return MFWF_OK;
+    return launch_sum_partials(partial, nblocks, nb, diag, 0, s);
 }
 
 // Pixel term of chi^2(lambda, s) (Eq. 6) and its derivative in lambda, for the error-bound
@@ -234,21 +246,16 @@ __global__ void k_chi2_pix_dlam(const double *__restrict__ rho, const double *__
     }
 }
 
-__global__ void k_sum_pairs(const double *__restrict__ partial, int nblocks, int nb,
-                            double *__restrict__ out) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nb) return;
-    double a = 0.0, c = 0.0;
-    for (int k = 0; k < nblocks; k++) {
-        a += partial[((long)b * nblocks + k) * 2];
-        c += partial[((long)b * nblocks + k) * 2 + 1];
-    }
-    out[2 * b] = a;
-    out[2 * b + 1] = c;
+__global__ void __launch_bounds__(kSumT)
+k_sum_pairs(const double *__restrict__ partial, int nblocks, double *__restrict__ out) {
+    const int b = blockIdx.x;
+    double s[2];
+    sum_strided<2>(partial + 2L * b * nblocks, nblocks, s);
+    if (threadIdx.x < 2) out[2 * b + threadIdx.x] = s[threadIdx.x];
 }
 
 int launch_sum_pairs(const double *partial, int nblocks, int nb, double *out2, hipStream_t s) {
-    hipLaunchKernelGGL(k_sum_pairs, dim3((nb + 63) / 64), dim3(64), 0, s, partial, nblocks, nb, out2);
+    hipLaunchKernelGGL(k_sum_pairs, dim3(nb), dim3(kSumT), 0, s, partial, nblocks, out2);
     MFWF_HIP(hipGetLastError());
     return MFWF_OK;
 }

@@ -556,20 +556,6 @@ k_pol_stats(const double *__restrict__ M6, long npix, double *__restrict__ parti
         for (int k = 0; k < 3; k++) partial[3 * blockIdx.x + k] = sh[k][0];
 }
 
-__global__ void k_pol_stats_final(const double *__restrict__ partial, int nblocks,
-                                  double *__restrict__ out) {
-    if (threadIdx.x != 0) return;
-    double mx = 0.0, cnt = 0.0, bad = 0.0;
-    for (int b = 0; b < nblocks; b++) {
-        mx = fmax(mx, partial[3 * b]);
-        cnt += partial[3 * b + 1];
-        bad += partial[3 * b + 2];
-    }
-    out[0] = mx;
-    out[1] = cnt;
-    out[2] = bad;
-}
-
 int launch_pol_covariance(const double *ninv6, const uint8_t *mask, double *M6, long npix,
                           double *partial, int nblocks, double *out3, hipStream_t s) {
     hipLaunchKernelGGL(k_mask_product_pol, dim3(pgrid(6 * npix)), dim3(kPT), 0, s, ninv6, mask, M6,
@@ -577,9 +563,7 @@ int launch_pol_covariance(const double *ninv6, const uint8_t *mask, double *M6, 
     MFWF_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_pol_stats, dim3(nblocks), dim3(kPT), 0, s, M6, npix, partial);
     MFWF_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_pol_stats_final, dim3(1), dim3(64), 0, s, partial, nblocks, out3);
-    MFWF_HIP(hipGetLastError());
-    return MFWF_OK;
+    return launch_max_count_final(partial, nblocks, out3, s);
 }
 
 // rho = M d per pixel (masked pixels: 0)
@@ -667,25 +651,13 @@ k_chi2_pix_pol(const double *__restrict__ rho, const double *__restrict__ M6,
     if (threadIdx.x == 0) partial[(long)blockIdx.y * gridDim.x + blockIdx.x] = sh[0];
 }
 
-__global__ void k_sum_partials_pol(const double *__restrict__ partial, int nblocks, int nb,
-                                   double *__restrict__ diag) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nb) return;
-    double acc = 0.0;
-    for (int k = 0; k < nblocks; k++) acc += partial[(long)b * nblocks + k];
-    diag[8 * b + 0] = acc;
-}
-
 int launch_chi2_pix_pol(const double *rho, const double *M6, const double *smap, long npix,
                         int nb, double lam, double tau, double *partial, int nblocks,
                         double *diag, hipStream_t s) {
     hipLaunchKernelGGL(k_chi2_pix_pol, dim3(nblocks, nb), dim3(kPT), 0, s, rho, M6, smap, npix,
                        lam, tau, partial);
     MFWF_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_sum_partials_pol, dim3((nb + 63) / 64), dim3(64), 0, s, partial, nblocks,
-                       nb, diag);
-    MFWF_HIP(hipGetLastError());
-    return MFWF_OK;
+    return launch_sum_partials(partial, nblocks, nb, diag, 0, s);
 }
 
 // Pixel term of chi^2(lambda, s) for T, Q, U and its derivative in lambda (the error-bound
@@ -796,30 +768,12 @@ k_harm_diag_pol(const double2 *__restrict__ s, const double2 *__restrict__ prev,
     if (threadIdx.x < 3) partial[((long)b * nm + m) * 3 + threadIdx.x] = w * sh[threadIdx.x][0];
 }
 
-__global__ void k_harm_diag_pol_final(const double *__restrict__ partial, int nm, int nb,
-                                      double *__restrict__ diag) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nb) return;
-    double h = 0.0, d = 0.0, n = 0.0;
-    for (int m = 0; m < nm; m++) {
-        h += partial[((long)b * nm + m) * 3 + 0];
-        d += partial[((long)b * nm + m) * 3 + 1];
-        n += partial[((long)b * nm + m) * 3 + 2];
-    }
-    diag[8 * b + 1] = h;
-    diag[8 * b + 2] = d;
-    diag[8 * b + 3] = n;
-}
-
 int launch_harm_diag_pol(const Plan &p, const double2 *salm, const double2 *salm_prev, int nb,
                          double *partial, double *diag) {
     hipLaunchKernelGGL(k_harm_diag_pol, dim3(p.nm, nb), dim3(kHP), 0, p.stream, salm, salm_prev,
                        p.nalm, p.d_mofs, p.d_cl, p.lmax, p.nm, partial);
     MFWF_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_harm_diag_pol_final, dim3((nb + 63) / 64), dim3(64), 0, p.stream, partial,
-                       p.nm, nb, diag);
-    MFWF_HIP(hipGetLastError());
-    return MFWF_OK;
+    return launch_harm_diag_final(partial, p.nm, nb, diag, p.stream);
 }
 
 // Fluctuation source with blocks: rho = L_p g1 + Omega Y(K h), M_p = L_p L_p^T (Cholesky;
