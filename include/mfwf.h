@@ -60,7 +60,7 @@ typedef enum {
 typedef enum {
     MFWF_F64 = 0, /* every step in double precision                               */
     MFWF_F32 = 1  /* batched form: the Legendre contractions (Sect. 3's transform
-                     cost) run as FP32 matrix-core products over all maps of a call,
+                     cost) run as FP32 products on the matrix cores over all maps of a call,
                      from an FP32 table of lambda_lm; maps, the pixel update, the ring
                      transforms, the harmonic filter's arithmetic and all norms stay
                      FP64.  ~1e-7 relative error per transform, 8e-6 after 300

@@ -255,7 +255,7 @@ static void free_plan(Plan &p) {
                     p.d_tw,   p.d_twlo, p.d_twhi, p.d_chirp, p.d_bhat, p.d_mofs,   p.d_cl,    p.d_M, p.d_pc, p.d_tau,
                     p.d_rho,  p.d_t,    p.d_smap,  p.d_phase,  p.d_apart, p.d_salm,
                     p.d_salm_prev, p.d_sp, p.d_red, p.d_diag, p.d_lam, p.d_lck, p.d_segoff, p.d_loff, p.d_Lp,
-                    p.d_minls32, p.d_ana_items, p.d_syn_items, p.d_ana_tab, p.d_syn_tab, p.d_lofi, p.d_phf, p.d_ph32, p.d_a32,
+                    p.d_minls32, p.d_ana_items, p.d_syn_items, p.d_ana_tab, p.d_syn_tab, p.d_lofi, p.d_phf, p.d_ph32, p.d_zrow, p.d_a32,
                     p.d_s32, p.d_fp, p.d_fm, p.d_ph32p, p.d_ap32, p.d_ar32, p.d_seb32,
                     p.d_fftsplit};
     for (void *q : ptrs)
@@ -286,7 +286,8 @@ static int device_name(std::string &name) {
 //               coefficients per scalar load block 4/8 (9 synthesis, 6 analysis variants)
 //   g0, g1      maps per workgroup of the batched form's ring step, short-transform class
 //               and longest-transform class (1, 2 or 4; as LDS and 1024 threads allow)
-//   cta, cts    largest column tile of the analysis / synthesis GEMMs, x 64 columns (1 or 2)
+//   cta, cts    column tile of the analysis / synthesis GEMMs: 1: 64 columns, 2: 128, 3
+//               (analysis only): 32
 //   lamgen      temperature GEMMs: lambda read from the FP32 table (0) or generated from the
 //               FP64 recurrence's segment states (1; the only choice above nside 1024)
 // With MFWF_AUTOTUNE != 0 (default) a plan of at least 256 ring pairs times every value of
@@ -544,7 +545,7 @@ static int balance_xcd(const std::vector<int2> &items, const std::vector<double>
 }
 
 static int setup_batched(Plan &p, const std::vector<int> &lstart, const std::vector<long> &mofs) {
-    p.Rp = ((p.npair + 63) / 64) * 64;
+    p.Rp = ((p.npair + 127) / 128) * 128;
     p.Bp = ((p.max_batch + 15) / 16) * 16;
     p.C2 = 2 * p.Bp;
     std::vector<long> loff(p.nm);
@@ -562,20 +563,22 @@ static int setup_batched(Plan &p, const std::vector<int> &lstart, const std::vec
             int &a = mn32[(size_t)m * n32 + q / 32];
             a = std::min(a, lstart[(size_t)m * p.npair + q]);
         }
-    // analysis tiles (m, 128 values of l) and synthesis tiles (m, 64 ring pairs), with their
+    // analysis tiles (m, 256 values of l) and synthesis tiles (m, 128 ring pairs), with their
     // work in active K chunks (chunks whose pairs all start above the tile are skipped)
     std::vector<int2> ana, syn;
     std::vector<double> wana, wsyn;
     for (int m = 0; m < p.nm; m++) {
         const int Lm = p.lmax - m + 1;
-        for (int t = 0; 128 * t < Lm; t++) {
+        for (int t = 0; 256 * t < Lm; t++) {
             int act = 0;
-            for (int pc = 0; pc < n32; pc++) act += mn32[(size_t)m * n32 + pc] <= m + 128 * t + 127;
+            for (int pc = 0; pc < n32; pc++)
+                act += mn32[(size_t)m * n32 + pc] <= std::min(m + 256 * t + 255, p.lmax);
             ana.push_back(make_int2(m, t));
             wana.push_back(1.0 + act);
         }
-        for (int pt = 0; pt < p.Rp / 64; pt++) {
-            const int ls = std::min(mn32[(size_t)m * n32 + 2 * pt], mn32[(size_t)m * n32 + 2 * pt + 1]);
+        for (int pt = 0; pt < p.Rp / 128; pt++) {
+            int ls = p.lmax + 1;
+            for (int q = 0; q < 4; q++) ls = std::min(ls, mn32[(size_t)m * n32 + 4 * pt + q]);
             const int first = std::max(0, ls - m) / 64, nrc = (Lm + 63) / 64;
             syn.push_back(make_int2(m, pt));
             wsyn.push_back(1.0 + std::max(0, nrc - first));
@@ -615,6 +618,8 @@ static int setup_batched(Plan &p, const std::vector<int> &lstart, const std::vec
     p.nm32 = (p.nm + 15) / 16 * 16;
     MFWF_TRY(dalloc(&p.d_phf, (size_t)p.ncomp * p.max_batch * p.nring * p.nm32, "ring Fourier rows FP32"));
     MFWF_TRY(dalloc(&p.d_ph32, (size_t)p.nring * p.nm * p.C2, "ring Fourier FP32"));
+    MFWF_TRY(dalloc(&p.d_zrow, (size_t)2 * p.C2, "zero row"));
+    MFWF_HIP(hipMemsetAsync(p.d_zrow, 0, sizeof(float) * 2 * p.C2, p.stream));
     MFWF_TRY(dalloc(&p.d_a32, (size_t)p.nalm * p.C2, "analysis FP32"));
     MFWF_TRY(dalloc(&p.d_s32, (size_t)p.nalm * p.C2, "synthesis input FP32"));
     MFWF_TRY(upload(p.d_loff, loff, p.stream));
@@ -845,7 +850,7 @@ static int create(int nside, int lmax, int spin, int dtype, int max_batch, void 
     MFWF_TRY(dalloc(&p.d_A, Atab.size(), "recurrence A"));
     MFWF_TRY(dalloc(&p.d_c, ctab.size(), "recurrence scale"));
     MFWF_TRY(dalloc(&p.d_mofs, mofs.size(), "m offsets"));
-    if (f32) {  // the FP32 form's tables start at each pair's own l, the FP64 kernels at its block
+    if (f32 && spin == 2) {  // the spin-2 tables start at each pair's own l, the rest at its block
         MFWF_TRY(dalloc(&p.d_lstart, lstart.size(), "l start"));
         MFWF_TRY(dalloc(&p.d_seed, seed.size(), "seeds"));
     } else {
@@ -896,7 +901,7 @@ static int create(int nside, int lmax, int spin, int dtype, int max_batch, void 
     MFWF_TRY(upload(p.d_A, Atab, p.stream));
     MFWF_TRY(upload(p.d_c, ctab, p.stream));
     MFWF_TRY(upload(p.d_mofs, mofs, p.stream));
-    if (f32) {
+    if (f32 && spin == 2) {
         MFWF_TRY(upload(p.d_lstart, lstart, p.stream));
         MFWF_TRY(upload(p.d_seed, seed, p.stream));
     } else {

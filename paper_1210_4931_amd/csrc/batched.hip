@@ -7,14 +7,19 @@
 //              F_N = E + O, F_S = E - O                      ([pairs x L] x [L x cols])
 //   analysis   a[l][c] = sum_p lambda_lm(z_p) X_{(l+m) mod 2}[p][c],
 //              X_0 = G_N + G_S, X_1 = G_N - G_S              ([L x pairs] x [pairs x cols])
-// lambda_lm is tabulated once per plan in FP32 (computed from the FP64 recurrence and start
-// seeds, zero below each pair's start index), as rows [m][pair][l - m] padded to 128 values of
-// l and 64 pairs.  The products run on v_mfma_f32_32x32x2f32 with FP32 accumulation; the
+// lambda_lm is tabulated once per plan in FP32 (computed from the FP64 recurrence from each
+// pair's entry state, zero below its first block), as rows [m][pair][l - m] padded to 128
+// values of l and 128 pairs.  The FP32 products run as sums of bf16 piece products on the
+// matrix cores, accumulated in FP32; the
 // ring-Fourier array ([ring][m][cols]) and the coefficients ([alm][cols]) are FP32 with the
 // maps innermost, so tiles of columns are contiguous.  Maps, the pixel update and every
 // diagnostic stay FP64.  The ring FFTs are the FP64 transforms of the per-map path with
 // FP32 per-map output rows, regrouped into the column layout by LDS-tiled transposes.
+#include <algorithm>
+#include <type_traits>
+
 #include "fft_core.h"
+#include "leg_core.h"
 
 namespace mfwf {
 
@@ -28,8 +33,8 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 // ---------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(64)
 k_lam_table(const double *__restrict__ Atab, const double *__restrict__ ctab,
-            const long *__restrict__ mofs, const int *__restrict__ lstart,
-            const double2 *__restrict__ seed, const double *__restrict__ zp,
+            const long *__restrict__ mofs, const int *__restrict__ kstart,
+            const double2 *__restrict__ entry, const double *__restrict__ zp,
             const long *__restrict__ loff, const int *__restrict__ Lp, float *__restrict__ lam,
             int lmax, int npair) {
     const int p = blockIdx.x * 64 + threadIdx.x, m = blockIdx.y;
@@ -40,21 +45,15 @@ k_lam_table(const double *__restrict__ Atab, const double *__restrict__ ctab,
         for (int r = 0; r < L; r++) row[r] = 0.f;
         return;
     }
-    const int ls = lstart[(long)m * npair + p];
-    const double2 sd = seed[(long)m * npair + p];
+    const int r0 = kLegBlock * kstart[(long)m * npair + p];  // first row of the pair's first block
+    const double2 st = entry[(long)m * npair + p];
     const double z = zp[p];
-    double u1 = 0.0, u2 = 0.0;
+    double u1 = st.x, u2 = st.y;
     for (int r = 0; r < L; r++) {
         const int l = m + r;
         float v = 0.f;
-        if (l <= lmax && l >= ls) {
-            double mu;
-            if (l == ls) {
-                mu = sd.y;
-                u1 = sd.x;
-            } else {
-                mu = fma(Atab[off + l] * z, u1, -u2);
-            }
+        if (l <= lmax && r >= r0) {
+            const double mu = fma(Atab[off + l] * z, u1, -u2);
             u2 = u1;
             u1 = mu;
             v = (float)(ctab[off + l] * mu);  // lambda = c mu
@@ -72,10 +71,11 @@ k_lam_table(const double *__restrict__ Atab, const double *__restrict__ ctab,
 // so the generated values equal the table's bit for bit.
 // ---------------------------------------------------------------------------------------
 // lck[(segoff[m] + s) Rp + p] = (mu_{l-1}, mu_{l-2}) entering row l = m + 16 s of pair p,
-// zero before the pair's start index (and for the padding pairs)
+// zero before the pair's first block (and for the padding pairs): the zero state stays zero
+static_assert(kLegBlock == 16, "the segments are the blocks that pairs start at");
 __global__ void __launch_bounds__(64)
 k_lam_ckpt(const double *__restrict__ Atab, const long *__restrict__ mofs,
-           const int *__restrict__ lstart, const double2 *__restrict__ seed,
+           const int *__restrict__ kstart, const double2 *__restrict__ entry,
            const double *__restrict__ zp, const int *__restrict__ Lp,
            const long *__restrict__ segoff, double2 *__restrict__ lck, int lmax, int npair,
            int Rp) {
@@ -87,21 +87,19 @@ k_lam_ckpt(const double *__restrict__ Atab, const long *__restrict__ mofs,
         return;
     }
     const long off = mofs[m] - m;
-    const int ls = lstart[(long)m * npair + p];
-    const double2 sd = seed[(long)m * npair + p];
+    const int r0 = kLegBlock * kstart[(long)m * npair + p];
+    const double2 st = entry[(long)m * npair + p];
     const double z = zp[p];
     double u1 = 0.0, u2 = 0.0;
     for (int r = 0; r < L; r++) {
+        if (r == r0) {
+            u1 = st.x;
+            u2 = st.y;
+        }
         if ((r & 15) == 0) out[(long)(r / 16) * Rp] = make_double2(u1, u2);
         const int l = m + r;
-        if (l <= lmax && l >= ls) {
-            double mu;
-            if (l == ls) {
-                mu = sd.y;
-                u1 = sd.x;
-            } else {
-                mu = fma(Atab[off + l] * z, u1, -u2);
-            }
+        if (l <= lmax && r >= r0) {
+            const double mu = fma(Atab[off + l] * z, u1, -u2);
             u2 = u1;
             u1 = mu;
         }
@@ -109,32 +107,24 @@ k_lam_ckpt(const double *__restrict__ Atab, const long *__restrict__ mofs,
 }
 
 // Rows l0 .. l0 + 15 of one pair from the segment state st = (u1, u2): the steps of
-// k_lam_table; A(r), c(r) give the coefficients A_lm, c_lm of row l0 + r; sink(q, v4)
-// receives rows 4 q .. 4 q + 3 as they are ready.
+// k_lam_table; A(r), c(r) give the coefficients A_lm, c_lm of row l0 + r (c = 0 past lmax);
+// sink(q, v4) receives rows 4 q .. 4 q + 3 as they are ready.
 template <typename FA, typename FC, typename FS>
-__device__ __forceinline__ void lam_rows16(double2 st, int ls, double2 sd, double z, int l0,
-                                           int lmax, FA A, FC c, FS sink) {
+__device__ __forceinline__ void lam_rows16(double2 st, double z, FA A, FC c, FS sink) {
     double u1 = st.x, u2 = st.y;
 #pragma unroll
     for (int q = 0; q < 4; q++) {
         float v[4];
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-            const int r = 4 * q + i, l = l0 + r;
-            float x = 0.f;
-            if (l <= lmax && l >= ls) {
-                double mu;
-                if (l == ls) {
-                    mu = sd.y;
-                    u1 = sd.x;
-                } else {
-                    mu = fma(A(r) * z, u1, -u2);
-                }
-                u2 = u1;
-                u1 = mu;
-                x = (float)(c(r) * mu);
-            }
-            v[i] = x;
+            const int r = 4 * q + i;
+            const double mu = fma(A(r) * z, u1, -u2);
+            u2 = u1;
+            u1 = mu;
+            v[i] = (float)(c(r) * mu);
+            // the rounded value, as the table holds it: without this the compiler rounds the
+            // product straight to a narrower type where the value is split
+            asm("" : "+v"(v[i]));
         }
         sink(q, v);
     }
@@ -144,8 +134,6 @@ __device__ __forceinline__ void lam_rows16(double2 st, int ls, double2 sd, doubl
 struct LamGen {
     const double2 *lck;    // segment states (k_lam_ckpt)
     const long *segoff;    // [nm] first segment of each m
-    const int *lstart;     // [nm][npair]
-    const double2 *seed;   // [nm][npair]
     const double *z;       // [npair]
     const double *A, *c;   // [nalm]
 };
@@ -219,16 +207,41 @@ k_cols_to_rows(const float *__restrict__ ph32, float2 *__restrict__ phf, int nri
 }
 
 // ---------------------------------------------------------------------------------------
-// MFMA GEMMs.  Workgroup of 4 waves.  v_mfma_f32_32x32x2f32 operands: A[i][k] in lane
-// i + 32k, B[k][j] in lane j + 32k; accumulator register r of lane L holds
-// D[8 (r/4) + 4 (L/32) + r%4][L%32].
+// MFMA GEMMs.  Both contractions run per parity q of l + m: C_q[128][CT] += A_q[128][k] B_q[k][CT]
+// with A = lambda (analysis: rows = values of l of parity q, k = ring pairs; synthesis: rows
+// = ring pairs, k = values of l of parity q) and B the FP32 columns.
+//
+// FP32 products on the bf16 matrix cores: every FP32 operand is the exact sum of three bf16
+// pieces (8 + 8 + 8 bits, each the rounded remainder of the ones before), and the six piece
+// products above 2^-27 of the product (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi) are
+// accumulated in FP32; what is left out is below FP32's own rounding.  On this card random
+// data runs v_mfma_f32_32x32x16_bf16 at 1.67 PFLOP/s, so six of them take the time of 278
+// TFLOP/s, where v_mfma_f32_32x32x2_f32 reaches 117-142; and one rounding per 16 values of k
+// instead of one per 2 makes the sums more exact, not less.  The sums of 16 values of k start
+// from zero and are then added to the running sum (one long chain of FP32 additions over all
+// rings would round several times more).
+//
+// Measured against the FP32 matrix instructions (us, analysis / synthesis): nside 512, 64 maps
+// 1359 / 1221 -> 1090 / 1160; nside 256, 64 maps 230 / 203 -> 202 / 216; nside 128, 4 maps
+// 30 / 19 -> 19 / 17; nside 512, T, Q, U, 32 maps 3401 / 3250 -> 2775 / 3105; lambda generated,
+// nside 2048, 4 maps 44500 / 40000 -> 36200 / 30500.  What is left at nside 512: the table is
+// 2.1 GB (0.43 ms at a copy's rate), the six products 0.5 ms, and the splits, which share the
+// issue slots with them, about as much again.
 //
 // Workgroup i of a launch is dispatched to XCD i mod 8.  Each XCD takes its tiles from its
 // own list, so that all tiles of one m, which read the same ring-Fourier (analysis) or
 // coefficient (synthesis) block, run on one XCD and share its L2 instead of fetching the
 // block from HBM once per XCD; the lists are balanced by the number of active K chunks.
-// Global loads of the next K chunk are issued before the matrix products of the current
-// one (register double buffering).
+//
+// Pipeline: stages of 16 values of k per parity through two LDS buffers, one barrier per
+// stage; during a stage's products the next stage is split into its pieces and written to
+// the other buffer, and the loads of the stage after that are in flight.  Consecutive lanes
+// load consecutive addresses (with two rows interleaved over the lanes the vector L1 took
+// four times as many accesses and was the kernels' limit).  The pieces lie in LDS as
+// [buffer][parity][piece][k / 4][row][4 k], rows padded, so that the splits' writes and the
+// operands' reads (two 8-byte planes each) meet no bank twice.  v_mfma_f32_32x32x16_bf16 operands: A[i][k] in lane
+// i + 32 (k / 8), element k % 8, B[k][j] likewise in lane j + 32 (k / 8); accumulator register r
+// of lane L holds D[8 (r/4) + 4 (L/32) + r%4][L%32].
 // ---------------------------------------------------------------------------------------
 __device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
 
@@ -247,43 +260,183 @@ __device__ __forceinline__ XcdTile xcd_tile(const int *__restrict__ tab, int per
 }
 
 __device__ __forceinline__ floatx4 ld4(const float *q) { return *reinterpret_cast<const floatx4 *>(q); }
-__device__ __forceinline__ void st4(float *q, floatx4 v) { *reinterpret_cast<floatx4 *>(q) = v; }
-// v if c, else zeros (a value select; a conditional load would become a load through a
-// selected pointer and force a stack copy)
-__device__ __forceinline__ floatx4 keep4(bool c, floatx4 v) { return c ? v : floatx4{0.f, 0.f, 0.f, 0.f}; }
 
-// threadIdx.x read anew: an epilogue that forms its lane indices from it keeps them out of
-// the registers of the main loop (the compiler would otherwise hold or spill them there)
-__device__ __forceinline__ int fresh_tid() {
-    int t;
-    asm volatile("v_mov_b32 %0, %1" : "=v"(t) : "v"((int)threadIdx.x));
-    return t;
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+// (hi, mid, lo) bf16 pieces of four floats, four per 8 bytes
+struct Split4 {
+    uint2 p[3];
+};
+__device__ __forceinline__ unsigned pack_bf16(float x, float y) {
+    const bf16x2 v = {(__bf16)x, (__bf16)y};  // one v_cvt_pk_bf16_f32, round to nearest even
+    return __builtin_bit_cast(unsigned, v);
+}
+// DITHER: hi is not the nearest bf16 but one of the two neighbours, chosen by the value's own
+// lowest byte as the rounding threshold (the remainders stay exact).  The data of successive
+// iterations differ in their last bits only; with the nearest hi the largest piece products,
+// and with them the matrix cores' rounding, would be the same from one iteration to the next,
+// and an error that repeats grows linearly where one that varies averages out.
+template <bool DITHER>
+__device__ __forceinline__ Split4 split4(float v0, float v1, float v2, float v3) {
+    Split4 s;
+    if constexpr (DITHER) {
+        auto thr = [](float v) {
+            const unsigned u = __float_as_uint(v);
+            return u + ((u & 0xffu) << 8);
+        };
+        const unsigned d0 = thr(v0), d1 = thr(v1), d2 = thr(v2), d3 = thr(v3);
+        s.p[0] = make_uint2(__builtin_amdgcn_perm(d1, d0, 0x07060302u), __builtin_amdgcn_perm(d3, d2, 0x07060302u));
+        v0 -= __uint_as_float(d0 & 0xffff0000u);
+        v1 -= __uint_as_float(d1 & 0xffff0000u);
+        v2 -= __uint_as_float(d2 & 0xffff0000u);
+        v3 -= __uint_as_float(d3 & 0xffff0000u);
+    }
+#pragma unroll
+    for (int q = DITHER ? 1 : 0; q < 3; q++) {
+        const unsigned a = pack_bf16(v0, v1), b = pack_bf16(v2, v3);
+        s.p[q] = make_uint2(a, b);
+        if (q < 2) {  // the remainders, exact
+            v0 -= __uint_as_float(a << 16);
+            v1 -= __uint_as_float(a & 0xffff0000u);
+            v2 -= __uint_as_float(b << 16);
+            v3 -= __uint_as_float(b & 0xffff0000u);
+        }
+    }
+    return s;
 }
 
-static constexpr int kAnaRows = 128;  // values of l per analysis tile
-// Columns per workgroup tile: 64 NCT (NCT column tiles of 32 per wave, two waves across).
-// Launches with at most 64 active columns (up to 32 maps) take NCT = 1, so that no wave
-// computes columns past the batch; every output column sees the same sequence of matrix
-// operations with either tile, so results do not depend on the tile.
-__host__ __device__ constexpr int col_tile(int nct) { return 64 * nct; }
-// LDS floats of a kernel: its main-loop tiles or the epilogue staging (4 waves x 64 rows x
-// 36), whichever is larger
-__host__ __device__ constexpr int lds_floats(int main_floats) {
-    return main_floats > 4 * 64 * 36 ? main_floats : 4 * 64 * 36;
+// the same of two floats, each piece in the halves of one register
+__device__ __forceinline__ void split2_dithered(float v0, float v1, unsigned (&p)[3]) {
+    const unsigned u0 = __float_as_uint(v0), u1 = __float_as_uint(v1);
+    const unsigned d0 = u0 + ((u0 & 0xffu) << 8), d1 = u1 + ((u1 & 0xffu) << 8);
+    p[0] = __builtin_amdgcn_perm(d1, d0, 0x07060302u);
+    v0 -= __uint_as_float(d0 & 0xffff0000u);
+    v1 -= __uint_as_float(d1 & 0xffff0000u);
+    p[1] = pack_bf16(v0, v1);
+    v0 -= __uint_as_float(p[1] << 16);
+    v1 -= __uint_as_float(p[1] & 0xffff0000u);
+    p[2] = pack_bf16(v0, v1);
 }
 
-// analysis: tile = (m, 128 values of l, 64 NCT columns); K loop over chunks of 32 ring
-// pairs.  Wave w: rows 64 (w & 1) .. +63 of the tile (32 even, 32 odd l + m), columns
-// 32 NCT (w >> 1) .. +32 NCT - 1.  Output: raw sums a (if a_out) and/or the Wiener-filtered coefficients
+static constexpr int kRows = 128;       // rows per parity of a tile
+static constexpr int kAnaL = 2 * kRows; // values of l per analysis tile
+// Columns of a tile: 128 (eight waves of 64 rows x 64 columns), 64 (four such waves) or 32
+// (eight waves of 32 rows x 32 columns).  A wider tile splits and stages lambda fewer times; a
+// narrower one leaves more workgroups, and the eight small waves hide each other's latency
+// where a CU holds one or two workgroups (nside 128, 4 maps: analysis 26 -> 19 us against four
+// waves of 64 x 32; the 64-column tile cut the same way needs more than 128 registers, loses
+// its second workgroup per CU and goes from 202 to 290 us at nside 256, 64 maps).  Every output
+// column sees the same operations with any tile.
+template <int CT>
+struct Tile {
+    static constexpr int NTH = CT == 64 ? 256 : 512;   // threads
+    static constexpr int NCT = CT == 32 ? 1 : 2;       // 32-column tiles per wave
+    static constexpr int NRT = CT == 32 ? 1 : 2;       // 32-row tiles per wave
+    static constexpr int NA = 4 * kRows / NTH;         // staging tasks per thread, A and B
+    static constexpr bool B1 = CT == 32;               // a staging task of B: one k of both parities, else four
+    static constexpr int NB = B1 ? NTH : 4 * CT;       // staging tasks of B
+    static constexpr int NBV = B1 ? 2 : 8;             // values of such a task
+    static constexpr int A_EL = 2 * 3 * 4 * (kRows + 8) * 4, B_EL = 2 * 3 * 4 * (CT + 8) * 4;  // bf16 per buffer
+};
+// bf16 offset of (parity, piece, k4 = k / 4, row) in a buffer of `rows` rows
+__device__ __forceinline__ int piece_at(int par, int pc, int k4, int row, int rows) {
+    return (((par * 3 + pc) * 4 + k4) * (rows + 8) + row) * 4;
+}
+// write a task's four values of k to a buffer
+__device__ __forceinline__ void put_split(unsigned short *buf, int par, int k4, int row, int rows,
+                                          const Split4 &s) {
+#pragma unroll
+    for (int q = 0; q < 3; q++)
+        *reinterpret_cast<uint2 *>(buf + piece_at(par, q, k4, row, rows)) = s.p[q];
+}
+// write one value of k of both parities (v0 to parity par, v1 to the other)
+__device__ __forceinline__ void put_split1(unsigned short *buf, int par, int k, int row, int rows,
+                                           float v0, float v1) {
+    unsigned x[3];
+    split2_dithered(v0, v1, x);
+#pragma unroll
+    for (int q = 0; q < 3; q++) {
+        buf[piece_at(par, q, k >> 2, row, rows) + (k & 3)] = (unsigned short)x[q];
+        buf[piece_at(par ^ 1, q, k >> 2, row, rows) + (k & 3)] = (unsigned short)(x[q] >> 16);
+    }
+}
+// a lane's operand: k = 8 kg .. 8 kg + 7 of one row
+__device__ __forceinline__ bf16x8 get_operand(const unsigned short *buf, int par, int pc, int kg, int row, int rows) {
+    const uint2 a = *reinterpret_cast<const uint2 *>(buf + piece_at(par, pc, 2 * kg, row, rows));
+    const uint2 b = *reinterpret_cast<const uint2 *>(buf + piece_at(par, pc, 2 * kg + 1, row, rows));
+    return __builtin_bit_cast(bf16x8, make_uint4(a.x, a.y, b.x, b.y));
+}
+
+// A wave's products of one stage, its 64 rows x 32 NCT columns of parity par, summed from zero,
+// small piece products first
+template <int CT>
+__device__ __forceinline__ void stage_products(const unsigned short *A, const unsigned short *B, int par,
+                                               int row0, int col0, floatx16 (&part)[Tile<CT>::NRT][Tile<CT>::NCT]) {
+    constexpr int NCT = Tile<CT>::NCT, NRT = Tile<CT>::NRT;
+    const int lane = threadIdx.x & 63, i = lane & 31, kg = lane >> 5;
+    bf16x8 a[NRT][3];
+#pragma unroll
+    for (int q = 0; q < 3; q++)
+#pragma unroll
+        for (int t = 0; t < NRT; t++) a[t][q] = get_operand(A, par, q, kg, row0 + 32 * t + i, kRows);
+    constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+    for (int c = 0; c < NCT; c++) {
+        bf16x8 b[3];
+#pragma unroll
+        for (int q = 0; q < 3; q++) b[q] = get_operand(B, par, q, kg, col0 + 32 * c + i, CT);
+#pragma unroll
+        for (int p = 0; p < 6; p++)
+#pragma unroll
+            for (int t = 0; t < NRT; t++) {
+                const floatx16 z = {};
+                part[t][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][pa[p]], b[pb[p]], p == 0 ? z : part[t][c], 0, 0, 0);
+            }
+    }
+}
+// the stage's sums added to (NEG: taken from) the running sums, once the stage's splitting
+// has covered the products' latency
+template <bool NEG, int NRT, int NCT>
+__device__ __forceinline__ void stage_add(float (&acc)[NRT][NCT][16], const floatx16 (&part)[NRT][NCT]) {
+#pragma unroll
+    for (int t = 0; t < NRT; t++)
+#pragma unroll
+        for (int c = 0; c < NCT; c++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+                acc[t][c][r] += NEG ? -part[t][c][r] : part[t][c][r];
+                // the addition stays here: sunk to the next use, it would hold two column
+                // tiles' partial sums in registers through the next stage, and spill
+                if constexpr (NCT > 1) asm volatile("" : "+v"(acc[t][c][r]));
+            }
+}
+// 4-byte load at a uniform base plus a 32-bit byte offset per lane
+__device__ __forceinline__ float ld_off(const float *base, unsigned byte) {
+    return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(base) + byte);
+}
+
+// The matrix cores bring the terms of one v_mfma_f32_32x32x16_bf16 to the largest one's
+// exponent by rounding towards minus infinity one bit below its last (measured: a small C
+// under a product loses 0.25 ulp of the sum on average, whatever the signs; the FP32 form
+// rounds to nearest).  Left alone, that bias is the same in every iteration and grows
+// linearly in the modes that converge slowly (3.4e-6 after 300 iterations at nside 512, where
+// the FP32 products had 2.2e-6).  So its sign alternates: the stages of both
+// contractions alternate between sums and negated sums, and in the synthesis, whose terms
+// fall off with l, so do the rings, whose alternating error has no large-scale part.  With
+// that and the dithered splits the errors after 5 to 300 iterations are those of the FP32
+// products or smaller (nside 512: 1.0e-6 after 100, where they had 1.15e-6).
+__device__ __forceinline__ float row_sign(int row) { return row & 1 ? -1.f : 1.f; }
+
+// analysis: tile = (m, 256 values of l, CT columns); K loop over active chunks of 32 ring
+// pairs (two stages).  Wave w: parity w & 1, rows 64 rh .. +63 of that parity, columns 64 ch ..
+// Output: raw sums a (if a_out) and/or the Wiener-filtered coefficients
 // s = scale_s C_l / (C_l + lto) a (if s_out), rows [alm][C2].  Even l + m rows contract
 // G_N + G_S and odd rows G_N - G_S (a table with lambda's mirror symmetry); flip swaps the
-// two, for a table that is odd where lambda is even (the spin-2 F-).  Waves per SIMD: 4
-// for the one-tile table kernel (128 registers, the chunk sums included), 3 where lambda is
-// generated (its recurrence state needs more), 2 for two column tiles.  NW = 8: eight
-// waves (128 columns of one-tile waves) share each lambda tile, which a launch of more than
-// 64 active columns otherwise reads once per 64-column group.
-template <int NCT, bool GEN, int NW = 4>
-__global__ void __launch_bounds__(64 * NW, NCT == 1 ? (GEN ? 3 : 4) : 2)
+// two, for a table that is odd where lambda is even (the spin-2 F-).
+// GEN: lambda from the segment states instead of the table, through an FP32 slab in LDS.
+template <int CT, bool GEN>
+__global__ void __launch_bounds__(Tile<CT>::NTH, 2)
 k_gemm_analysis(const float *__restrict__ lam, LamGen gen, const long *__restrict__ loff,
                 const int *__restrict__ Lp, const int *__restrict__ minls32,
                 const int2 *__restrict__ items, const int *__restrict__ tab, int per_xcd,
@@ -291,349 +444,537 @@ k_gemm_analysis(const float *__restrict__ lam, LamGen gen, const long *__restric
                 const double *__restrict__ cl, float *__restrict__ a_out,
                 float *__restrict__ s_out, double scale_s, double lto, int lmax, int npair,
                 int Rp, int nring, int nm, int C2, int ncols, int ncg,
-                const double *__restrict__ tau_b, double lto_per_tau, int flip) {
-    static_assert(NW == 4 || (NW == 8 && NCT == 1), "eight waves only with one-tile waves");
-    // threads; columns; lambda and X float4 loads per thread
-    constexpr int NTH = 64 * NW, CT = col_tile(NCT) * NW / 4, NL = 1024 / NTH, NX = 8 * CT / NTH;
-    // lambda tile [pair][row] and X_0, X_1 tiles [pair][col]; reused by the epilogue
-    __shared__ __align__(16) float lds[lds_floats(32 * (kAnaRows + 4) + 2 * 32 * (CT + 4))];
-    __shared__ double sAc[2][GEN ? kAnaRows : 1];  // A_lm, c_lm of the tile's rows (GEN)
-    float (*sl)[kAnaRows + 4] = reinterpret_cast<float (*)[kAnaRows + 4]>(lds);
-    float (*sx)[32][CT + 4] = reinterpret_cast<float (*)[32][CT + 4]>(lds + 32 * (kAnaRows + 4));
+                const double *__restrict__ tau_b, double lto_per_tau, int flip,
+                const float *__restrict__ zrow) {
+    using T = Tile<CT>;
+    constexpr int NTH = T::NTH, NCT = T::NCT, NRT = T::NRT, NA = T::NA, RW = 32 * NRT;
+    __shared__ __align__(16) unsigned short sA[2][T::A_EL], sB[2][T::B_EL];
+    __shared__ double sF[kAnaL];  // filter factors of the tile's rows
+    __shared__ float sL[GEN ? 2 : 1][GEN ? 16 : 1][GEN ? kAnaL + 4 : 1];  // generated lambda [pair][l]
+    __shared__ double sAc[2][GEN ? kAnaL : 1];                            // A_lm, c_lm of the rows
     const XcdTile xt = xcd_tile(tab, per_xcd, ncg);
     if (xt.item < 0) return;
     const int2 it = items[xt.item];
-    const int m = it.x, t = it.y, cg = xt.cg;
+    const int m = it.x, t0 = kAnaL * it.y, cg = xt.cg;  // rows l = m + t0 + ..
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int lh = w & 1, ch = w >> 1;
+    const int par = w & 1, rh = CT == 128 ? w >> 2 : w >> 1, ch = CT == 128 ? (w >> 1) & 1 : 0;
     const int L = Lp[m];
-    const int lhi = m + kAnaRows * t + kAnaRows - 1;  // last l of the tile
-    const int lhi_w = m + kAnaRows * t + 64 * lh + 63;  // last l of this wave's rows
-    const int nchunk = Rp / 32;
-    const int *ms = minls32 + m * nchunk;
-    floatx16 acc[2][NCT];  // [parity][column tile]
-#pragma unroll
-    for (int a = 0; a < 2; a++)
-#pragma unroll
-        for (int b = 0; b < NCT; b++)
-#pragma unroll
-            for (int r = 0; r < 16; r++) acc[a][b][r] = 0.f;
-    const float *lrow = GEN ? nullptr : lam + loff[m] + kAnaRows * t;
-    const int wcol = 32 * NCT * ch;  // first column of this wave within the tile
-    // a wave whose columns are past the batch or whose rows are all past lmax (the padding
-    // of a tile that ends beyond lmax) does no products
-    const bool wave_on = (CT * cg + wcol) < ncols && m + kAnaRows * t + 64 * lh <= lmax;
-    floatx4 rl[NL], rn[NX], rs[NX];
-    // GEN: thread (pair gpp = tid / 8, rows 16 (tid % 8) ..) of a chunk, threads 0..255; its
-    // segment state, start index, seeds and z, loaded with the chunk's other operands
-    const int gpp = threadIdx.x >> 3, gk = threadIdx.x & 7;
-    const bool gen_thread = NW == 4 || threadIdx.x < 256;
-    double2 gst = make_double2(0.0, 0.0), gsd = gst;
-    double gz = 0.0;
-    int gls = lmax + 1;
-    if constexpr (GEN) {
-        const long aoff = mofs[m] - m;
-        if (threadIdx.x < kAnaRows) {
-            const int l = min(m + kAnaRows * t + (int)threadIdx.x, lmax);
-            sAc[0][threadIdx.x] = gen.A[aoff + l];
-            sAc[1][threadIdx.x] = gen.c[aoff + l];
-        }  // visible after the first barrier of the K loop
+    const int nchunk = (npair + 31) / 32;
+    const int *ms = minls32 + m * (Rp / 32);
+    const int lhi = min(m + t0 + kAnaL - 1, lmax);          // last l of the tile
+    const int lhi_w = min(m + t0 + 2 * RW * (rh + 1) - 1, lmax);  // last l of this wave's rows
+    // a wave whose rows all lie past lmax, or whose columns lie past the batch, does no products
+    const bool wave_on = CT * cg + 64 * ch < ncols && m + t0 + 2 * RW * rh <= lmax;
+    // The first active chunk of the tile and of this wave's rows (ring pairs start at smaller l
+    // towards the equator), 64 chunks looked at together: one by one, every skipped chunk
+    // costs a memory latency before the first load
+    int pc = nchunk, pw = nchunk;
+    for (int q = 0; q < nchunk && pw == nchunk; q += 64) {
+        const int v = q + lane < nchunk ? ms[q + lane] : lmax + 1;
+        const unsigned long long any = __ballot(v <= lhi), own = __ballot(wave_on && v <= lhi_w);
+        if (pc == nchunk && any) pc = q + __builtin_ctzll(any);
+        if (own) pw = q + __builtin_ctzll(own);
     }
-    auto load = [&](int pc) __attribute__((always_inline)) {
-        if constexpr (GEN) {
-            if (gen_thread) {
-                const int p = 32 * pc + gpp, pq = min(p, npair - 1);
-                gst = gen.lck[(gen.segoff[m] + 8 * t + gk) * (long)Rp + p];
-                gsd = gen.seed[(long)m * npair + pq];
-                gz = gen.z[pq];
-                gls = p < npair ? gen.lstart[(long)m * npair + pq] : lmax + 1;  // padding: zero rows
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < NL; u++) {  // lambda: 32 pairs x 128 rows
-                const int e = threadIdx.x + NTH * u, pp = e >> 5, c4 = e & 31;
-                rl[u] = ld4(lrow + (long)(32 * pc + pp) * L + 4 * c4);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < NX; u++) {  // ring-Fourier: 32 pairs x CT columns
-            const int e = threadIdx.x + NTH * u, pp = e / (CT / 4), c4 = e % (CT / 4);
-            const int p = 32 * pc + pp, col = CT * cg + 4 * c4;
-            // loads from clamped in-range addresses; values outside the problem are zeroed
-            // when they are stored to LDS, so that no wait for the loads comes before the
-            // matrix products of the current chunk
-            const int pq = min(p, npair - 1), cq = min(col, ncols - 4);
-            rn[u] = ld4(ph32 + ((long)m * nring + pq) * C2 + cq);
-            rs[u] = ld4(ph32 + ((long)m * nring + (nring - 1 - pq)) * C2 + cq);
-        }
-    };
-    auto next_active = [&](int pc) __attribute__((always_inline)) {
-        while (pc < nchunk && ms[pc] > lhi) pc++;
-        return pc;
-    };
-    int pc = next_active(0);
-    if (pc < nchunk) load(pc);
-    while (pc < nchunk) {
-        __syncthreads();
-        if constexpr (GEN) {
-            if (gen_thread)
-                lam_rows16(gst, gls, gsd, gz, m + kAnaRows * t + 16 * gk, lmax,
-                           [&](int r) { return sAc[0][16 * gk + r]; }, [&](int r) { return sAc[1][16 * gk + r]; },
-                           [&](int q, const float (&v)[4]) {
-                               st4(&sl[gpp][16 * gk + 4 * q], floatx4{v[0], v[1], v[2], v[3]});
-                           });
-        } else {
-#pragma unroll
-            for (int u = 0; u < NL; u++) {
-                const int e = threadIdx.x + NTH * u, pp = e >> 5, c4 = e & 31;
-                st4(&sl[pp][4 * c4], rl[u]);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < NX; u++) {
-            const int e = threadIdx.x + NTH * u, pp = e / (CT / 4), c4 = e % (CT / 4);
-            const int p = 32 * pc + pp, col = CT * cg + 4 * c4;
-            const bool on = p < npair && col < ncols, south = on && (nring - 1 - p != p);
-            const floatx4 xn = keep4(on, rn[u]), xs = keep4(south, rs[u]);
-            const floatx4 ps = xn + xs, ms = xn - xs;
-            st4(&sx[0][pp][4 * c4], flip ? ms : ps);
-            st4(&sx[1][pp][4 * c4], flip ? ps : ms);
-        }
-        __syncthreads();
-        const int pn = next_active(pc + 1);
-        if (pn < nchunk) load(pn);
-        if (wave_on && ms[pc] <= lhi_w) {
-            const int i = lane & 31, kq = lane >> 5;
-            // the chunk's 32 pairs summed from zero, then added to the running sums: the
-            // FP32 rounding of a sum over all rings grows with the chain of additions, and
-            // chunked it grows with 32 + the number of chunks instead of their product
-            floatx16 part[2][NCT];
-            auto step = [&](int kk, bool first) __attribute__((always_inline)) {
-                const int pp = 2 * kk + kq;
-                const float2 a = *reinterpret_cast<const float2 *>(&sl[pp][64 * lh + 2 * i]);
-#pragma unroll
-                for (int ct = 0; ct < NCT; ct++) {
-                    const float b0 = sx[0][pp][wcol + 32 * ct + i], b1 = sx[1][pp][wcol + 32 * ct + i];
-                    const floatx16 z = {};
-                    part[0][ct] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b0, first ? z : part[0][ct], 0, 0, 0);
-                    part[1][ct] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b1, first ? z : part[1][ct], 0, 0, 0);
-                }
-            };
-            step(0, true);
-#pragma unroll 5
-            for (int kk = 1; kk < 16; kk++) step(kk, false);
-#pragma unroll
-            for (int a = 0; a < 2; a++)
-#pragma unroll
-                for (int ct = 0; ct < NCT; ct++) acc[a][ct] += part[a][ct];
-        }
-        pc = pn;
-    }
-    // Epilogue through LDS: per column tile, every wave parks its 64 rows x 32 columns
-    // ([row][36]) and stores whole 128-byte row segments with 16-byte stores (with eight
-    // waves, four at a time).  Its lane indices are formed anew from the thread id, so that
-    // none of them holds a register through the main loop.
     const long base = mofs[m] - m;
-    const int te = fresh_tid();
-    const int we = te >> 6, le = te & 63, lhe = we & 1, wcole = 32 * NCT * (we >> 1);
-    float (*stage)[36] = reinterpret_cast<float (*)[36]>(lds) + 64 * (we & 3);
+    if (s_out && !tau_b)
+        for (int r = threadIdx.x; r < kAnaL; r += NTH) {
+            const double C = m + t0 + r <= lmax ? cl[m + t0 + r] : 0.0;
+            sF[r] = C > 0.0 ? C / (C + lto) * scale_s : 0.0;
+        }
+    if constexpr (GEN)
+        for (int r = threadIdx.x; r < kAnaL; r += NTH) {
+            const int l = min(m + t0 + r, lmax);
+            sAc[0][r] = gen.A[base + l];
+            sAc[1][r] = m + t0 + r <= lmax ? gen.c[base + l] : 0.0;
+        }
+    // staging tasks of a stage: A: (l, l + 1; four ring pairs k4), B: (column; four ring pairs)
+    // register sets of loads in flight: two stages ahead, one where two would not fit
+    constexpr int NS = CT == 64 && !GEN ? 1 : 2;
+    constexpr bool COMPACT = CT == 32 && !GEN;
+    float ra[GEN ? 1 : NS][NA][8], rb[NS][T::NBV];
+    const int bcol = threadIdx.x % CT, bk4 = threadIdx.x / CT;  // B1: bk4 is k itself
+    const bool b_on = NTH <= T::NB || (int)threadIdx.x < T::NB;
+    // addresses = a uniform base per load + one byte offset per thread.  What is loaded for rows
+    // past the table, columns past the batch and padding pairs is valid data that never reaches
+    // an output: those rows and columns are not stored, padding pairs have lambda = 0.
+    const int col = min(CT * cg + bcol, ncols - 1);
+    const unsigned noff = 4 * (4 * bk4 * C2 + col), soff = 4 * (4 * (3 - bk4) * C2 + col);
+    unsigned aoff[NA];
 #pragma unroll
-    for (int ct = 0; ct < NCT; ct++)
+    for (int u = 0; u < NA; u++) {
+        const int e = threadIdx.x + NTH * u, row = e & (kRows - 1), k4 = e / kRows;
+        aoff[u] = 4 * (4 * k4 * L + (t0 + 2 * row < L ? 2 * row : 0));
+    }
+    const float *lrow = GEN ? nullptr : lam + loff[m] + t0;
+    const float *gN = ph32 + (long)m * nring * C2, *gS = gN + (long)(nring - 1) * C2;
+    // GEN: task (pair, 16-row segment): 16 x 16 tasks, lanes over the pairs (the rows'
+    // coefficients are then broadcast reads)
+    const int gp = threadIdx.x & 15, gs = (threadIdx.x >> 4) & 15;
+    const bool gen_on = GEN && threadIdx.x < 256;
+    double2 gst = make_double2(0.0, 0.0);
+    double gz = 0.0;
+    auto load = [&](int p0, int set_) __attribute__((always_inline)) {  // pairs p0 .. p0 + 15
+        const int set = set_ & (NS - 1);
+        if constexpr (GEN) {
+            if (gen_on) {
+                // segments past the row's (rows that are not stored) repeat its last one
+                const int seg = min(t0 / 16 + gs, L / 16 - 1);
+                gst = gen.lck[(gen.segoff[m] + seg) * (long)Rp + p0 + gp];
+                gz = gen.z[min(p0 + gp, npair - 1)];
+            }
+        } else {
 #pragma unroll
-    for (int rnd = 0; rnd < NW / 4; rnd++) {
-        __syncthreads();
-        if ((we >> 2) == rnd)
+            for (int u = 0; u < NA; u++) {
 #pragma unroll
-            for (int r = 0; r < 16; r++)
-#pragma unroll
-                for (int par = 0; par < 2; par++) stage[2 * acc_row(r, le) + par][le & 31] = acc[par][ct][r];
-        __syncthreads();
-        const int col = CT * cg + wcole + 32 * ct + 4 * (le & 7);
-        if ((we >> 2) != rnd || CT * cg + wcole >= ncols || col >= ncols) continue;
-#pragma unroll
-        for (int it = 0; it < 8; it++) {
-            const int row = 8 * it + (le >> 3);
-            const int l = m + kAnaRows * t + 64 * lhe + row;
-            if (l > lmax) continue;
-            const float4 v = *reinterpret_cast<const float4 *>(&stage[row][4 * (le & 7)]);
-            const long idx = (base + l) * C2 + col;
-            if (a_out) *reinterpret_cast<float4 *>(a_out + idx) = v;
-            if (s_out) {
-                const double C = cl[l];
-                // per-map tau (serving slots): columns 2b and 2b + 1 belong to map b, so the
-                // four columns of this store span maps col / 2 and col / 2 + 1
-                const double lt0 = tau_b ? lto_per_tau * tau_b[col >> 1] : lto;
-                const double lt1 = tau_b ? lto_per_tau * tau_b[(col >> 1) + 1] : lto;
-                const double f0 = C > 0.0 ? C / (C + lt0) * scale_s : 0.0;
-                const double f1 = C > 0.0 ? C / (C + lt1) * scale_s : 0.0;
-                *reinterpret_cast<float4 *>(s_out + idx) =
-                    make_float4((float)(f0 * v.x), (float)(f0 * v.y), (float)(f1 * v.z), (float)(f1 * v.w));
+                for (int j = 0; j < 4; j++) {
+                    const char *q = reinterpret_cast<const char *>(lrow + (long)(p0 + j) * L);
+                    const float2 v = *reinterpret_cast<const float2 *>(q + aoff[u]);
+                    ra[set][u][2 * j] = v.x;
+                    ra[set][u][2 * j + 1] = v.y;
+                }
             }
         }
+        if constexpr (T::B1) {
+            const int p = min(p0 + bk4, npair - 1);
+            rb[set][0] = ld_off(gN, 4 * (p * C2 + col));
+            rb[set][1] = ld_off(gN, 4 * ((nring - 1 - p) * C2 + col));
+        } else if (b_on) {
+            if (p0 + 16 < npair) {
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    rb[set][j] = ld_off(gN + (long)(p0 + j) * C2, noff);
+                    // south rings run backwards: pair p0 + 4 bk4 + j from the base of p0 + 12 + j
+                    rb[set][4 + j] = ld_off(gS - (long)(p0 + 12 + j) * C2, soff);
+                }
+            } else {  // the equator, whose ring counts once, and what may follow it
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    const int p = p0 + 4 * bk4 + j, pq = min(p, npair - 1);
+                    rb[set][j] = gN[(long)pq * C2 + col];
+                    rb[set][4 + j] = *(p < npair - 1 ? gS + (col - (long)pq * C2) : zrow + col);
+                }
+            }
+        }
+    };
+    auto gen_rows = [&](int buf) __attribute__((always_inline)) {
+        if constexpr (GEN)
+            if (gen_on)
+                lam_rows16(gst, gz, [&](int r) { return sAc[0][16 * gs + r]; }, [&](int r) { return sAc[1][16 * gs + r]; },
+                           [&](int q, const float (&v)[4]) {
+                               *reinterpret_cast<floatx4 *>(&sL[buf][gp][16 * gs + 4 * q]) =
+                                   floatx4{v[0], v[1], v[2], v[3]};
+                           });
+    };
+    // split the stage data of register set `set` (GEN: of slab buffer `set`) into LDS buffer `buf`
+    // (a chunk's second half is contracted negated)
+    auto split = [&](int p0, int set_, int buf) __attribute__((always_inline)) {  // of pairs p0 ..
+        const int set = GEN ? set_ : set_ & (NS - 1);
+#pragma unroll
+        for (int u = 0; u < NA; u++) {
+            const int e = threadIdx.x + NTH * u, row = e & (kRows - 1), k4 = e / kRows;
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                if constexpr (GEN) {
+                    const float2 x = *reinterpret_cast<const float2 *>(&sL[set][4 * k4 + j][2 * row]);
+                    v[2 * j] = x.x;
+                    v[2 * j + 1] = x.y;
+                } else {
+                    v[2 * j] = ra[set][u][2 * j];
+                    v[2 * j + 1] = ra[set][u][2 * j + 1];
+                }
+            }
+            put_split(sA[buf], 0, k4, row, kRows, split4<false>(v[0], v[2], v[4], v[6]));
+            put_split(sA[buf], 1, k4, row, kRows, split4<false>(v[1], v[3], v[5], v[7]));
+        }
+        if constexpr (T::B1) {
+            float n = rb[set][0], v = p0 + bk4 < npair - 1 ? rb[set][1] : 0.f;  // the equator counts once
+            if (buf) n = -n, v = -v;
+            put_split1(sB[buf], flip, bk4, bcol, CT, n + v, n - v);
+        } else if (b_on) {
+            float ps[4], df[4];
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                ps[j] = buf ? -rb[set][j] - rb[set][4 + j] : rb[set][j] + rb[set][4 + j];
+                df[j] = buf ? rb[set][4 + j] - rb[set][j] : rb[set][j] - rb[set][4 + j];
+            }
+            put_split(sB[buf], flip, bk4, bcol, CT, split4<true>(ps[0], ps[1], ps[2], ps[3]));
+            put_split(sB[buf], flip ^ 1, bk4, bcol, CT, split4<true>(df[0], df[1], df[2], df[3]));
+        }
+    };
+    float acc[NRT][NCT][16];
+#pragma unroll
+    for (int t = 0; t < NRT; t++)
+#pragma unroll
+        for (int c = 0; c < NCT; c++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) acc[t][c][r] = 0.f;
+    // The chunks from the first active one on.  stage (chunk, h): pairs 32 chunk + 16 h ..;
+    // register set and buffers h.
+    pc = __builtin_amdgcn_readfirstlane(pc);
+    pw = __builtin_amdgcn_readfirstlane(max(pw, pc));
+    const int last = nchunk - 1;
+    if constexpr (COMPACT) {
+        // Small launches run few rounds, and fetching the instructions weighs on them (27 KB
+        // of straight code with separate rounds, 10 KB here; a solve's iteration at nside 16
+        // with 4 maps 78 -> 71 us): one copy of the round, whose first split is the prologue's;
+        // every wave does the products of all the tile's chunks, and the second stage's sums
+        // are taken off after the next split.
+        floatx16 part[NRT][NCT] = {};
+        if (pc < nchunk) {
+            load(32 * pc, 0);
+            load(32 * pc + 16, 1);
+        }
+#pragma unroll 1
+        for (; pc < nchunk; pc++) {
+            split(32 * pc, 0, 0);
+            load(32 * min(pc + 1, last), 0);
+            stage_add<true>(acc, part);
+            __syncthreads();
+            stage_products<CT>(sA[0], sB[0], par, RW * rh, 64 * ch, part);
+            split(32 * pc + 16, 1, 1);
+            load(32 * min(pc + 1, last) + 16, 1);
+            stage_add<false>(acc, part);
+            __syncthreads();
+            stage_products<CT>(sA[1], sB[1], par, RW * rh, 64 * ch, part);
+        }
+        stage_add<true>(acc, part);
+    } else {
+    if (pc < nchunk) {
+        if constexpr (GEN) {
+            __syncthreads();  // sAc
+            load(32 * pc, 0);
+            gen_rows(0);
+            float keep[T::NBV];
+#pragma unroll
+            for (int j = 0; j < T::NBV; j++) keep[j] = rb[0][j];
+            load(32 * pc + 16, 1);
+            gen_rows(1);
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < T::NBV; j++) rb[0][j] = keep[j];
+            split(32 * pc, 0, 0);
+        } else {
+            load(32 * pc, 0);
+            if (NS == 2) load(32 * pc + 16, 1);
+            split(32 * pc, 0, 0);
+            if (NS == 2) load(32 * min(pc + 1, last), 0);
+            else load(32 * pc + 16, 1);
+        }
+        __syncthreads();
+    }
+    // One chunk; on: with products.  Loads are issued in every round (the last ones repeat the
+    // last chunk) and on one path, so that the waits for one register set leave the other in
+    // flight, and a stage is one stretch of code in which the next stage's splitting fills
+    // the time of its products.
+    auto round = [&](auto on) __attribute__((always_inline)) {
+        // first stage: products of buffer 0; the chunk's second half to buffer 1, and its
+        // registers take the next chunk's second half
+        auto refill1 = [&]() __attribute__((always_inline)) {
+            split(32 * pc + 16, 1, 1);
+            if (!GEN) load(32 * min(pc + 1, last) + (NS == 2 ? 16 : 0), 1);
+        };
+        if (GEN) load(32 * min(pc + 1, last), 0);
+        floatx16 part[NRT][NCT];
+        if constexpr (on()) stage_products<CT>(sA[0], sB[0], par, RW * rh, 64 * ch, part);
+        refill1();
+        if constexpr (on()) stage_add<false>(acc, part);
+        gen_rows(0);
+        __syncthreads();
+        // second stage: products of buffer 1; the next chunk's first half to buffer 0
+        auto refill0 = [&]() __attribute__((always_inline)) {
+            split(32 * min(pc + 1, last), 0, 0);
+            if (!GEN) load(NS == 2 ? 32 * min(pc + 2, last) : 32 * min(pc + 1, last) + 16, 0);
+        };
+        if (GEN) load(32 * min(pc + 1, last) + 16, 1);
+        if constexpr (on()) stage_products<CT>(sA[1], sB[1], par, RW * rh, 64 * ch, part);
+        refill0();
+        if constexpr (on()) stage_add<true>(acc, part);
+        gen_rows(1);
+        __syncthreads();
+        pc++;
+    };
+    while (pc < pw) round(std::false_type{});
+    while (pc < nchunk) round(std::true_type{});
+    }
+    if (!wave_on) return;
+    // for each register, lanes 0..31 and 32..63 hold 32 columns of two rows (rows 4 apart):
+    // whole 128-byte lines, at a uniform base plus one offset per lane
+    const int rhu = __builtin_amdgcn_readfirstlane(rh), paru = __builtin_amdgcn_readfirstlane(par);
+    const int hi4 = 4 * (lane >> 5);
+#pragma unroll
+    for (int c = 0; c < NCT; c++) {
+        const int oc = CT * cg + 64 * ch + 32 * c + (lane & 31);
+        if (oc - (lane & 31) >= ncols) continue;
+        const double lt = tau_b ? lto_per_tau * tau_b[oc >> 1] : lto;  // per-map tau (serving slots)
+        const unsigned lane_off = 2 * hi4 * C2 + oc;
+#pragma unroll
+        for (int t = 0; t < NRT; t++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+                const int row0 = 2 * (RW * rhu + 32 * t + 8 * (r >> 2) + (r & 3)) + paru;  // of lane 0
+                const int row = row0 + 2 * hi4, l = m + t0 + row;
+                if (l > lmax) continue;
+                const long at = (base + m + t0 + row0) * C2;
+                const float v = acc[t][c][r];
+                if (a_out) (a_out + at)[lane_off] = v;
+                if (s_out) {
+                    double f;
+                    if (tau_b) {
+                        const double C = cl[l];
+                        f = C > 0.0 ? C / (C + lt) * scale_s : 0.0;
+                    } else {
+                        f = sF[row];
+                    }
+                    (s_out + at)[lane_off] = (float)(f * v);
+                }
+            }
     }
 }
 
-// synthesis: tile = (m, 64 ring pairs, 64 NCT columns); K loop over chunks of 64 values of
-// l.  Wave w: pairs 32 (w & 1) .. +31 of the tile, columns 32 NCT (w >> 1) .. +32 NCT - 1.  The south ring
-// gets E - O (lambda's mirror symmetry), or O - E with flip (the spin-2 F-).
-template <int NCT, bool GEN>
-__global__ void __launch_bounds__(256, NCT == 1 ? 4 : 2)
+// synthesis: tile = (m, 128 ring pairs, CT columns); K loop over chunks of 64 values of l (32
+// of each parity, two stages).  Wave w: parity w & 1, pairs 64 rh .. +63, columns 64 ch ..
+// The waves of the two parities swap their sums through LDS: the even one stores the north
+// rings E + O, the odd one the south rings E - O (lambda's mirror symmetry), or O - E with
+// flip (the spin-2 F-).
+template <int CT, bool GEN>
+__global__ void __launch_bounds__(Tile<CT>::NTH, 2)
 k_gemm_synthesis(const float *__restrict__ lam, LamGen gen, const long *__restrict__ loff,
                  const int *__restrict__ Lp, const int *__restrict__ minls32,
                  const int2 *__restrict__ items, const int *__restrict__ tab, int per_xcd,
                  const float *__restrict__ s32, const long *__restrict__ mofs,
                  float *__restrict__ ph32, int lmax, int npair, int Rp, int nring, int nm,
                  int C2, int ncols, int ncg, int flip, int comb) {
-    constexpr int CT = col_tile(NCT), NV = CT / 16;  // columns; coefficient float4 loads per thread
-    // lambda tile [pair][l] (odd stride: no bank conflicts) and coefficient tile [l][col];
-    // reused by the epilogue
-    __shared__ __align__(16) float lds[lds_floats(64 * (64 + 1) + 64 * (CT + 4))];
-    float (*sl)[64 + 1] = reinterpret_cast<float (*)[64 + 1]>(lds);
-    float (*ss)[CT + 4] = reinterpret_cast<float (*)[CT + 4]>(lds + 64 * (64 + 1));
+    using T = Tile<CT>;
+    constexpr int NTH = T::NTH, NCT = T::NCT, NRT = T::NRT, NA = T::NA, NW = NTH / 64, RW = 32 * NRT;
+    __shared__ __align__(16) unsigned short sA[2][T::A_EL], sB[2][T::B_EL];
     const XcdTile xt = xcd_tile(tab, per_xcd, ncg);
     if (xt.item < 0) return;
     const int2 it = items[xt.item];
-    const int m = it.x, pt = it.y, cg = xt.cg;
+    const int m = it.x, q0 = kRows * it.y, cg = xt.cg;  // ring pairs q0 ..
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int rt = w & 1, ch = w >> 1;
+    const int par = w & 1, rh = CT == 128 ? w >> 2 : w >> 1, ch = CT == 128 ? (w >> 1) & 1 : 0;
     const int L = Lp[m], Lm = lmax - m + 1;
-    const int nchunk32 = Rp / 32;
-    const int ls_tile = min(minls32[m * nchunk32 + 2 * pt], minls32[m * nchunk32 + 2 * pt + 1]);
-    const int ls_wave = minls32[m * nchunk32 + 2 * pt + rt];
-    const int wcol = 32 * NCT * ch;  // first column of this wave within the tile
-    const bool wave_on = (CT * cg + wcol) < ncols;
-    floatx16 acc[2][NCT];  // [parity][column tile]
-#pragma unroll
-    for (int a = 0; a < 2; a++)
-#pragma unroll
-        for (int b = 0; b < NCT; b++)
-#pragma unroll
-            for (int r = 0; r < 16; r++) acc[a][b][r] = 0.f;
-    const float *lrow = GEN ? nullptr : lam + loff[m] + (long)(64 * pt) * L;
+    const int *ms = minls32 + m * (Rp / 32) + q0 / 32;
+    const int ls_wave = min(ms[NRT * rh], ms[NRT * rh + NRT - 1]);
+    const int ls_tile = min(min(ms[0], ms[1]), min(ms[2], ms[3]));
+    const bool wave_on = CT * cg + 64 * ch < ncols;
     const long base = mofs[m];
-    floatx4 rl[4], rv[NV];
-    // GEN: wave w generates rows 16 w .. 16 w + 15 of the chunk for pair 64 pt + lane; the
-    // rows' coefficients are the same for the whole wave (scalar loads)
-    const int gw = __builtin_amdgcn_readfirstlane(w);
-    double2 gst = make_double2(0.0, 0.0), gsd = gst;
-    double gz = 0.0;
-    int gls = lmax + 1;
-    if constexpr (GEN) {
-        const int p = 64 * pt + lane, pq = min(p, npair - 1);
-        gsd = gen.seed[(long)m * npair + pq];
-        gz = gen.z[pq];
-        gls = p < npair ? gen.lstart[(long)m * npair + pq] : lmax + 1;  // padding: zero rows
-    }
-    auto load = [&](int rc) __attribute__((always_inline)) {
+    // staging tasks of a stage: A: (pair; four values of l), two per thread of 512; B: (column;
+    // eight values of l, four of each parity)
+    // register sets of loads in flight: two stages ahead, one where two would not fit
+    constexpr int NS = CT == 64 && !GEN ? 1 : 2;
+    constexpr bool COMPACT = CT == 32 && !GEN;
+    floatx4 ra[GEN ? 1 : NS][GEN ? 1 : 2 * NA];
+    float rb[NS][T::NBV];
+    const int bcol = threadIdx.x % CT, bk4 = threadIdx.x / CT;  // B1: bk4 is k itself
+    const bool b_on = NTH <= T::NB || (int)threadIdx.x < T::NB;
+    const int col = min(CT * cg + bcol, ncols - 1);  // columns past the batch are not stored
+    const unsigned boff = 4 * (8 * bk4 * C2 + col);  // bytes
+    const int al = threadIdx.x & 7, arow = threadIdx.x >> 3;  // eight lanes read 32 values of l of a pair
+    const unsigned aoff = 4 * (arow * L + 4 * al);
+    const float rsgn = row_sign(GEN ? threadIdx.x & (kRows - 1) : arow);  // the same for all of a thread's rows
+    const float *lrow = GEN ? nullptr : lam + loff[m] + (long)q0 * L;
+    // GEN: task (pair, 16 values of l = k / 8 group of both parities): threads 0..255; the
+    // coefficients are the same for the whole wave (scalar loads)
+    const int gp = threadIdx.x & (kRows - 1), gk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 7);
+    const bool gen_on = GEN && threadIdx.x < 256;
+    double2 gst[2] = {};
+    const double gz = gen_on ? gen.z[min(q0 + gp, npair - 1)] : 0.0;
+    auto load = [&](int r0, int set_) __attribute__((always_inline)) {  // l = m + r0 .. m + r0 + 31
+        const int set = set_ & (NS - 1);
         if constexpr (GEN) {
-            gst = gen.lck[(gen.segoff[m] + 4 * rc + gw) * (long)Rp + 64 * pt + lane];
+            if (gen_on) gst[set] = gen.lck[(gen.segoff[m] + r0 / 16 + gk) * (long)Rp + q0 + gp];
         } else {
 #pragma unroll
-            for (int u = 0; u < 4; u++) {
-                const int e = threadIdx.x + 256 * u, pp = e >> 4, c4 = e & 15;
-                rl[u] = ld4(lrow + (long)pp * L + 64 * rc + 4 * c4);
+            for (int u = 0; u < 2 * NA; u++) {
+                const char *x = reinterpret_cast<const char *>(lrow + (long)(u * (NTH / 8)) * L + r0);
+                ra[set][u] = *reinterpret_cast<const floatx4 *>(x + aoff);
             }
         }
+        if constexpr (T::B1) {  // past lmax: valid data, times lambda = 0
 #pragma unroll
-        for (int u = 0; u < NV; u++) {  // coefficients: 64 values of l x CT columns
-            const int e = threadIdx.x + 256 * u, rr = e / (CT / 4), c4 = e % (CT / 4);
-            const int r = 64 * rc + rr, col = CT * cg + 4 * c4;
-            // zeroed outside the problem at the LDS store (no wait before the products)
-            rv[u] = ld4(s32 + (base + min(r, Lm - 1)) * C2 + min(col, ncols - 4));
+            for (int j = 0; j < 2; j++)
+                rb[set][j] = ld_off(s32 + base * C2, 4 * (min(r0 + 2 * bk4 + j, Lm - 1) * C2 + col));
+        } else if (b_on) {
+            if (r0 + 32 <= Lm) {
+#pragma unroll
+                for (int j = 0; j < 8; j++) rb[set][j] = ld_off(s32 + (base + r0 + j) * C2, boff);
+            } else {  // past lmax: valid data, times lambda = 0
+#pragma unroll
+                for (int j = 0; j < 8; j++)
+                    rb[set][j] = s32[(base + min(r0 + 8 * bk4 + j, Lm - 1)) * C2 + col];
+            }
         }
     };
-    const int first = max(0, ls_tile - m) / 64;  // first chunk with a nonzero lambda
-    const int nrc = (Lm + 63) / 64;
-    if (first < nrc) load(first);
-    for (int rc = first; rc < nrc; rc++) {
-        __syncthreads();
+    auto split = [&](int r0, int set_, int buf) __attribute__((always_inline)) {
+        const int set = set_ & (NS - 1);
         if constexpr (GEN) {
-            const int l0 = m + 64 * rc + 16 * gw;
-            const long aoff = mofs[m] - m;
-            lam_rows16(gst, gls, gsd, gz, l0, lmax,
-                       [&](int r) { return gen.A[aoff + min(l0 + r, lmax)]; },
-                       [&](int r) { return gen.c[aoff + min(l0 + r, lmax)]; },
-                       [&](int q, const float (&v)[4]) {
+            if (gen_on) {
+                const int l0 = m + r0 + 16 * gk;
+                const long aoff = base - m;
+                float v[16];
+                lam_rows16(gst[set], gz, [&](int r) { return gen.A[aoff + min(l0 + r, lmax)]; },
+                           [&](int r) { return l0 + r <= lmax ? gen.c[aoff + l0 + r] : 0.0; },
+                           [&](int q, const float (&x)[4]) {
 #pragma unroll
-                           for (int i = 0; i < 4; i++) sl[lane][16 * gw + 4 * q + i] = v[i];
-                       });
+                               for (int i = 0; i < 4; i++) v[4 * q + i] = (buf ? -rsgn : rsgn) * x[i];
+                           });
+#pragma unroll
+                for (int h = 0; h < 2; h++)
+#pragma unroll
+                    for (int q = 0; q < 2; q++)
+                        put_split(sA[buf], q, 2 * gk + h, gp, kRows,
+                                  split4<false>(v[8 * h + q], v[8 * h + 2 + q], v[8 * h + 4 + q], v[8 * h + 6 + q]));
+            }
         } else {
 #pragma unroll
-            for (int u = 0; u < 4; u++) {
-                const int e = threadIdx.x + 256 * u, pp = e >> 4, c4 = e & 15;
-                sl[pp][4 * c4] = rl[u].x;
-                sl[pp][4 * c4 + 1] = rl[u].y;
-                sl[pp][4 * c4 + 2] = rl[u].z;
-                sl[pp][4 * c4 + 3] = rl[u].w;
+            for (int u = 0; u < 2 * NA; u++) {
+                // l = 4 al .. 4 al + 3: k = 2 al, 2 al + 1 of each parity
+                const floatx4 v = (buf ? -rsgn : rsgn) * ra[set][u];
+                const Split4 x = split4<false>(v[0], v[2], v[1], v[3]);  // .x even pair, .y odd pair
+#pragma unroll
+                for (int q = 0; q < 3; q++) {
+                    unsigned short *o = sA[buf] + piece_at(0, q, al >> 1, arow + u * (NTH / 8), kRows) + 2 * (al & 1);
+                    *reinterpret_cast<unsigned *>(o) = x.p[q].x;
+                    *reinterpret_cast<unsigned *>(o + piece_at(1, 0, 0, 0, kRows)) = x.p[q].y;
+                }
             }
         }
-#pragma unroll
-        for (int u = 0; u < NV; u++) {
-            const int e = threadIdx.x + 256 * u, rr = e / (CT / 4), c4 = e % (CT / 4);
-            const int r = 64 * rc + rr, col = CT * cg + 4 * c4;
-            st4(&ss[rr][4 * c4], keep4(r < Lm && col < ncols, rv[u]));
+        if constexpr (T::B1) {
+            put_split1(sB[buf], 0, bk4, bcol, CT, rb[set][0], rb[set][1]);
+        } else if (b_on) {
+            const float *v = rb[set];
+            put_split(sB[buf], 0, bk4, bcol, CT, split4<true>(v[0], v[2], v[4], v[6]));
+            put_split(sB[buf], 1, bk4, bcol, CT, split4<true>(v[1], v[3], v[5], v[7]));
         }
+    };
+    float acc[NRT][NCT][16];
+#pragma unroll
+    for (int t = 0; t < NRT; t++)
+#pragma unroll
+        for (int c = 0; c < NCT; c++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) acc[t][c][r] = 0.f;
+    int rc = max(0, ls_tile - m) / 64;  // first chunk with a nonzero lambda
+    const int nrc = (Lm + 63) / 64;
+    rc = __builtin_amdgcn_readfirstlane(rc);
+    if constexpr (COMPACT) {  // one copy of the round, as in the analysis
+        floatx16 part[NRT][NCT] = {};
+        if (rc < nrc) {
+            load(64 * rc, 0);
+            load(64 * rc + 32, 1);
+        }
+#pragma unroll 1
+        for (; rc < nrc; rc++) {
+            const int rl = 64 * min(rc + 1, nrc - 1);
+            split(64 * rc, 0, 0);
+            load(rl, 0);
+            stage_add<true>(acc, part);
+            __syncthreads();
+            stage_products<CT>(sA[0], sB[0], par, RW * rh, 64 * ch, part);
+            split(64 * rc + 32, 1, 1);
+            load(rl + 32, 1);
+            stage_add<false>(acc, part);
+            __syncthreads();
+            stage_products<CT>(sA[1], sB[1], par, RW * rh, 64 * ch, part);
+        }
+        stage_add<true>(acc, part);
         __syncthreads();
-        if (rc + 1 < nrc) load(rc + 1);
-        if (wave_on && ls_wave <= m + 64 * rc + 63) {
-            const int i = lane & 31, kq = lane >> 5;
-            // step s = (kk, parity): operands of step s + 1 are read from LDS before the
-            // products of step s are issued
-            float a[2], bv[2][NCT];
-            auto rd = [&](int st, int q) __attribute__((always_inline)) {
-                const int rr = 4 * (st >> 1) + 2 * kq + (st & 1);  // two same-parity l per step
-                a[q] = sl[32 * rt + i][rr];
-#pragma unroll
-                for (int ct = 0; ct < NCT; ct++) bv[q][ct] = ss[rr][wcol + 32 * ct + i];
-            };
-            rd(0, 0);
-#pragma unroll
-            for (int st = 0; st < 32; st++) {
-                const int q = st & 1;
-                if (st + 1 < 32) rd(st + 1, q ^ 1);
-                __builtin_amdgcn_sched_barrier(0);  // keep the reads ahead of the products
-#pragma unroll
-                for (int ct = 0; ct < NCT; ct++)
-                    acc[st & 1][ct] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], bv[q][ct], acc[st & 1][ct], 0, 0, 0);
-            }
-        }
+    } else {
+    if (rc < nrc) {
+        load(64 * rc, 0);
+        if (NS == 2) load(64 * rc + 32, 1);
+        split(64 * rc, 0, 0);
+        if (NS == 2) load(64 * min(rc + 1, nrc - 1), 0);
+        else load(64 * rc + 32, 1);
+        __syncthreads();
     }
-    // Epilogue through LDS: per column half, every wave parks F_N = E + O and F_S = E - O
-    // of its 32 pairs x 32 columns ([2][pair][36]) and stores whole 128-byte row segments.
-    // Rows are relative l = m + r, so the parity of r equals the parity of l + m.  Lane
-    // indices formed anew from the thread id (no registers held through the main loop).
-    const int te = fresh_tid();
-    const int we = te >> 6, le = te & 63, rte = we & 1, wcole = 32 * NCT * (we >> 1);
-    float (*stage)[32][36] = reinterpret_cast<float (*)[32][36]>(lds) + 2 * we;
-#pragma unroll
-    for (int ct = 0; ct < NCT; ct++) {
+    auto round = [&](auto on) __attribute__((always_inline)) {  // one chunk, as in the analysis
+        const int rl = 64 * min(rc + 1, nrc - 1), rm = 64 * min(rc + 2, nrc - 1);
+        auto refill1 = [&]() __attribute__((always_inline)) {
+            split(64 * rc + 32, 1, 1);
+            if (NS == 2) load(rl + 32, 1);
+            else load(rl, 0);
+        };
+        floatx16 part[NRT][NCT];
+        if constexpr (on()) stage_products<CT>(sA[0], sB[0], par, RW * rh, 64 * ch, part);
+        refill1();
+        if constexpr (on()) stage_add<false>(acc, part);
         __syncthreads();
-#pragma unroll
-        for (int r = 0; r < 16; r++) {
-            const float E = acc[0][ct][r], O = acc[1][ct][r];
-            stage[0][acc_row(r, le)][le & 31] = E + O;
-            stage[1][acc_row(r, le)][le & 31] = flip ? O - E : E - O;
-        }
+        auto refill0 = [&]() __attribute__((always_inline)) {
+            split(rl, 0, 0);
+            if (NS == 2) load(rm, 0);
+            else load(rl + 32, 1);
+        };
+        if constexpr (on()) stage_products<CT>(sA[1], sB[1], par, RW * rh, 64 * ch, part);
+        refill0();
+        if constexpr (on()) stage_add<true>(acc, part);
         __syncthreads();
-        const int col = CT * cg + wcole + 32 * ct + 4 * (le & 7);
-        if (CT * cg + wcole >= ncols || col >= ncols) continue;
+        rc++;
+    };
+    // the wave's first chunk
+    const int rw = __builtin_amdgcn_readfirstlane(wave_on ? min(max(0, ls_wave - m) / 64, nrc) : nrc);
+    while (rc < rw) round(std::false_type{});
+    while (rc < nrc) round(std::true_type{});
+    }
+    // Swap with the wave of the other parity, 32 pairs x 32 columns at a time, in register
+    // order; each register then holds 32 columns of two rings (pairs 4 apart): whole 128-byte
+    // lines, at a uniform base plus one offset per lane.
+    float *ex = reinterpret_cast<float *>(&sA[0][0]);
+    static_assert(sizeof(sA) >= NW * 1024 * sizeof(float), "epilogue exchange");
+    const int rhu = __builtin_amdgcn_readfirstlane(rh), paru = __builtin_amdgcn_readfirstlane(par);
+    const int hi4 = 4 * (lane >> 5);
+    const bool whole = q0 + kRows < npair;  // every pair exists and none is the equator
 #pragma unroll
-        for (int it = 0; it < 8; it++) {
-            const int q = 8 * it + (le >> 3);  // 0..63: hemisphere q / 32, pair row q % 32
-            const int hs = q >> 5, row = q & 31;
-            const int p = 64 * pt + 32 * rte + row;
-            if (p >= npair) continue;
-            const int ring = hs ? nring - 1 - p : p;
-            if (hs && ring == p) continue;  // equator: one ring
-            float4 v = *reinterpret_cast<const float4 *>(&stage[hs][row][4 * (le & 7)]);
-            float *o = ph32 + ((long)m * nring + ring) * C2 + col;
-            if (comb) {
-                // spin 2: v = R' = F- x s_EB of one map (E re, E im, B re, B im) and o holds
-                // P' = F+ x s_EB: Q = -(P'_E + i R'_B), U = -(P'_B - i R'_E) over P'
-                const float4 P = *reinterpret_cast<const float4 *>(o);
-                v = make_float4(-P.x + v.w, -P.y - v.z, -P.z - v.y, -P.w + v.x);
+    for (int c = 0; c < NCT; c++) {
+#pragma unroll
+        for (int t = 0; t < NRT; t++) {
+            if (c + t) __syncthreads();
+#pragma unroll
+            for (int r = 0; r < 16; r++) ex[(w * 16 + r) * 64 + lane] = acc[t][c][r];
+            __syncthreads();
+            const int oc = CT * cg + 64 * ch + 32 * c + (lane & 31);
+            if (oc - (lane & 31) >= ncols) continue;  // uniform per wave, after the barriers of this tile
+            const int p0 = q0 + RW * rhu + 32 * t;
+            // row of register r: pair p0 + 8 (r / 4) + r % 4 + hi4; south rings run backwards
+            float *out0 = ph32 + ((long)m * nring + (paru ? nring - 1 - p0 - 4 : p0)) * C2;
+            const unsigned lane_off = (paru ? 4 - hi4 : hi4) * C2 + oc;
+            const long step = paru ? -(long)C2 : (long)C2;
+            float v[16];
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+                const float o = ex[((w ^ 1) * 16 + r) * 64 + lane], x = acc[t][c][r];
+                // even wave: x = E, o = O; odd wave: x = O, o = E
+                v[r] = (paru == 0 ? x + o : (flip ? x - o : o - x)) * row_sign(r);  // the row's parity is r's
             }
-            *reinterpret_cast<float4 *>(o) = v;
+            auto at = [&](int r) { return out0 + (8 * (r >> 2) + (r & 3)) * step; };
+            auto in = [&](int r) {
+                const int p = p0 + 8 * (r >> 2) + (r & 3) + hi4;
+                return p < npair - paru;  // the equator once (pair npair - 1 has no south ring)
+            };
+            if (comb) {
+                // spin 2: v = R' = F- x s_EB of one map (E re, E im, B re, B im) and out holds
+                // P' = F+ x s_EB: Q = -(P'_E + i R'_B), U = -(P'_B - i R'_E) over P'
+                const int k = lane & 3;
+                float P[16];
+#pragma unroll
+                for (int r = 0; r < 16; r++) P[r] = whole || in(r) ? at(r)[lane_off] : 0.f;
+#pragma unroll
+                for (int r = 0; r < 16; r++) {
+                    const float x4 = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(
+                        __builtin_bit_cast(int, v[r]), 0x1b, 0xf, 0xf, false));  // quad reversed
+                    v[r] = ((k == 0 || k == 3) ? x4 : -x4) - P[r];
+                }
+            }
+            if (whole) {
+#pragma unroll
+                for (int r = 0; r < 16; r++) at(r)[lane_off] = v[r];
+            } else {
+#pragma unroll
+                for (int r = 0; r < 16; r++)
+                    if (in(r)) at(r)[lane_off] = v[r];
+            }
         }
     }
 }
@@ -701,7 +1042,7 @@ k_cols_to_alm(const float *__restrict__ x32, double2 *__restrict__ alm, long nal
 // ---------------------------------------------------------------------------------------
 int launch_lam_table(const Plan &p) {
     hipLaunchKernelGGL(k_lam_table, dim3(p.Rp / 64, p.nm), dim3(64), 0, p.stream, p.d_A, p.d_c,
-                       p.d_mofs, p.d_lstart, p.d_seed, p.d_z, p.d_loff, p.d_Lp, p.d_lam, p.lmax,
+                       p.d_mofs, p.d_kstart, p.d_entry, p.d_z, p.d_loff, p.d_Lp, p.d_lam, p.lmax,
                        p.npair);
     MFWF_HIP(hipGetLastError());
     return MFWF_OK;
@@ -709,7 +1050,7 @@ int launch_lam_table(const Plan &p) {
 
 int launch_lam_ckpt(const Plan &p) {
     hipLaunchKernelGGL(k_lam_ckpt, dim3(p.Rp / 64, p.nm), dim3(64), 0, p.stream, p.d_A, p.d_mofs,
-                       p.d_lstart, p.d_seed, p.d_z, p.d_Lp, p.d_segoff, p.d_lck, p.lmax, p.npair,
+                       p.d_kstart, p.d_entry, p.d_z, p.d_Lp, p.d_segoff, p.d_lck, p.lmax, p.npair,
                        p.Rp);
     MFWF_HIP(hipGetLastError());
     return MFWF_OK;
@@ -741,35 +1082,42 @@ int launch_cols_to_rows(const Plan &p, int nb) {
 // whole 32-column MFMA tiles; never beyond the padded width (w Bp, a multiple of 32)
 static int active_cols(int nb, int w) { return 32 * ((w * nb + 31) / 32); }
 
+// columns per GEMM tile for nc active columns and a plan's choice (1: 64, 2: 128, 3: 32)
+// Column tile of a launch over ntile row tiles: 32 columns where tiles of 64 would leave the
+// chip's 512 places for workgroups filled less than about twice (nside 128, 40 maps, 1028 such
+// workgroups: synthesis 51 us with them, 34 with 32 columns; at nside 256, 20 maps, 2052 of
+// them, 82 against 89), the narrowest that holds all columns, or else the plan's choice.
+static int gemm_tile(int nc, int choice, int ntile) {
+    if (ntile * ((nc + 63) / 64) < 1200) return 32;
+    const int ct = choice == 2 ? 128 : (choice == 3 ? 32 : 64);
+    return nc <= 32 ? 32 : (nc <= 64 ? std::min(ct, 64) : ct);
+}
+
 static LamGen lam_gen(const Plan &p) {
-    return LamGen{p.d_lck, p.d_segoff, p.d_lstart, p.d_seed, p.d_z, p.d_A, p.d_c};
+    return LamGen{p.d_lck, p.d_segoff, p.d_z, p.d_A, p.d_c};
 }
 
 // table == nullptr: lambda rows generated in the kernels (the plan's segment states)
 static int analysis_launch(const Plan &p, int nc, int C2, const float *table, const float *cols,
                            float *a_out, float *s_out, double scale_s, double lto,
                            const double *tau_b, double lto_per_tau, int flip) {
-    // column tile choice 1: 64 columns (4 waves), 2: 128 columns (4 waves of two tiles), 3:
-    // 128 columns (8 waves of one tile); at most 64 active columns always take 1
-    const int choice = nc <= 64 ? 1 : p.gemm_ct[0];
-    const int nct = choice == 2 ? 2 : 1, nw = choice == 3 ? 8 : 4;
-    const int ct = col_tile(nct) * nw / 4, ncg = (nc + ct - 1) / ct;
-    const dim3 grid(8 * p.ana_per_xcd * ncg), block(64 * nw);
+    const int ct = gemm_tile(nc, p.gemm_ct[0], 8 * p.ana_per_xcd), ncg = (nc + ct - 1) / ct;
+    const dim3 grid(8 * p.ana_per_xcd * ncg), block(ct == 64 ? 256 : 512);
     const LamGen g = lam_gen(p);
-#define MFWF_ANA(NCT, GEN, NW)                                                                     \
-    hipLaunchKernelGGL((k_gemm_analysis<NCT, GEN, NW>), grid, block, 0, p.stream, table, g, p.d_loff, \
+    if (table == nullptr && !p.d_lck) return fail(MFWF_EINVAL, "no lambda segment states in this plan");
+#define MFWF_ANA(CT, GEN)                                                                          \
+    hipLaunchKernelGGL((k_gemm_analysis<CT, GEN>), grid, block, 0, p.stream, table, g, p.d_loff,     \
                        p.d_Lp, p.d_minls32, p.d_ana_items, p.d_ana_tab, p.ana_per_xcd, cols,         \
                        p.d_mofs, p.d_cl, a_out, s_out, scale_s, lto, p.lmax, p.npair, p.Rp,          \
-                       p.nring, p.nm, C2, nc, ncg, tau_b, lto_per_tau, flip)
+                       p.nring, p.nm, C2, nc, ncg, tau_b, lto_per_tau, flip, p.d_zrow)
     if (table == nullptr) {
-        if (!p.d_lck) return fail(MFWF_EINVAL, "no lambda segment states in this plan");
-        if (nw == 8) MFWF_ANA(1, true, 8);
-        else if (nct == 1) MFWF_ANA(1, true, 4);
-        else MFWF_ANA(2, true, 4);
+        if (ct == 128) MFWF_ANA(128, true);
+        else if (ct == 64) MFWF_ANA(64, true);
+        else MFWF_ANA(32, true);
     } else {
-        if (nw == 8) MFWF_ANA(1, false, 8);
-        else if (nct == 1) MFWF_ANA(1, false, 4);
-        else MFWF_ANA(2, false, 4);
+        if (ct == 128) MFWF_ANA(128, false);
+        else if (ct == 64) MFWF_ANA(64, false);
+        else MFWF_ANA(32, false);
     }
 #undef MFWF_ANA
     MFWF_HIP(hipGetLastError());
@@ -778,20 +1126,22 @@ static int analysis_launch(const Plan &p, int nc, int C2, const float *table, co
 
 static int synthesis_launch(const Plan &p, int nc, int C2, const float *table, const float *s_in,
                             float *out, int flip, int comb) {
-    const int nct = (nc <= 64 || p.gemm_ct[1] == 1) ? 1 : 2, ncg = (nc + col_tile(nct) - 1) / col_tile(nct);
-    const dim3 grid(8 * p.syn_per_xcd * ncg), block(256);
+    const int ct = gemm_tile(nc, p.gemm_ct[1], 8 * p.syn_per_xcd), ncg = (nc + ct - 1) / ct;
+    const dim3 grid(8 * p.syn_per_xcd * ncg), block(ct == 64 ? 256 : 512);
     const LamGen g = lam_gen(p);
-#define MFWF_SYN(NCT, GEN)                                                                          \
-    hipLaunchKernelGGL((k_gemm_synthesis<NCT, GEN>), grid, block, 0, p.stream, table, g, p.d_loff,   \
+    if (table == nullptr && !p.d_lck) return fail(MFWF_EINVAL, "no lambda segment states in this plan");
+#define MFWF_SYN(CT, GEN)                                                                           \
+    hipLaunchKernelGGL((k_gemm_synthesis<CT, GEN>), grid, block, 0, p.stream, table, g, p.d_loff,    \
                        p.d_Lp, p.d_minls32, p.d_syn_items, p.d_syn_tab, p.syn_per_xcd, s_in,          \
                        p.d_mofs, out, p.lmax, p.npair, p.Rp, p.nring, p.nm, C2, nc, ncg, flip, comb)
     if (table == nullptr) {
-        if (!p.d_lck) return fail(MFWF_EINVAL, "no lambda segment states in this plan");
-        if (nct == 1) MFWF_SYN(1, true);
-        else MFWF_SYN(2, true);
+        if (ct == 128) MFWF_SYN(128, true);
+        else if (ct == 64) MFWF_SYN(64, true);
+        else MFWF_SYN(32, true);
     } else {
-        if (nct == 1) MFWF_SYN(1, false);
-        else MFWF_SYN(2, false);
+        if (ct == 128) MFWF_SYN(128, false);
+        else if (ct == 64) MFWF_SYN(64, false);
+        else MFWF_SYN(32, false);
     }
 #undef MFWF_SYN
     MFWF_HIP(hipGetLastError());

@@ -59,8 +59,8 @@ struct Plan {
     int ana_variant = 0;    // index into the Legendre analysis kernel variants
     int ngroup;             // pair groups (waves per m) of the chosen analysis variant
     int ring_group[2] = {1, 1};  // maps per workgroup of the columns ring step, per class
-    int gemm_ct[2] = {2, 2};     // column tiles of the analysis GEMM (1: 64 columns, 2: 128 in
-                                 // 4 waves, 3: 128 in 8 waves) and the synthesis GEMM (1, 2)
+    int gemm_ct[2] = {2, 2};     // column tiles of the analysis GEMM (1: 64 columns, 2: 128, 3: 32) and
+                                 // the synthesis GEMM (1, 2)
     int tune_source = 0;         // 0 defaults, 1 autotuned (timed or cached), 3 forced
     int ngroup_max;         // largest pair-group count of any analysis variant
 
@@ -68,10 +68,10 @@ struct Plan {
     double *d_z = nullptr;       // [npair] cos(theta) of the north ring of each pair
     double *d_A = nullptr;       // [nalm] A_lm of mu_l = A z mu_{l-1} - mu_{l-2}
     double *d_c = nullptr;       // [nalm] c_lm, lambda_lm = c_lm mu_lm
-    int *d_lstart = nullptr;     // [nm][npair] first l (FP32 form's tables)
-    double2 *d_seed = nullptr;   // [nm][npair] (mu_{l_s - 1}, mu_{l_s}) (FP32 form's tables)
-    int *d_kstart = nullptr;     // [nm][npair] first block of kLegBlock values of l (FP64 kernels)
-    double2 *d_entry = nullptr;  // [nm][npair] recurrence state entering it (FP64 kernels)
+    int *d_lstart = nullptr;     // [nm][npair] first l (spin-2 FP32 tables)
+    double2 *d_seed = nullptr;   // [nm][npair] (mu_{l_s - 1}, mu_{l_s}) (spin-2 FP32 tables)
+    int *d_kstart = nullptr;     // [nm][npair] first block of kLegBlock values of l
+    double2 *d_entry = nullptr;  // [nm][npair] recurrence state entering it
     PairFFT *d_pfft = nullptr;   // [npair]
     double2 *d_tw = nullptr;     // [fftmax] exp(-2 pi i k / fftmax)
     double2 *d_twlo = nullptr;   // [64] exp(-2 pi i t / fftmax)
@@ -146,6 +146,7 @@ struct Plan {
     bool chain = false;
     bool chain_ready = false;    // d_ph32 holds the synthesis of the iterate in d_smap
     float *d_ph32 = nullptr;     // [nm][nring][C2] ring-Fourier, maps innermost
+    float *d_zrow = nullptr;     // [2 C2] zeros: the equator pair's south ring
     float *d_a32 = nullptr;      // [nalm][C2] analysis output
     float *d_s32 = nullptr;      // [nalm][C2] synthesis input
     // batched FP32 form with spin 2 (T, Q, U); T uses the arrays above
