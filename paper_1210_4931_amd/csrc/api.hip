@@ -798,14 +798,21 @@ static int create(int nside, int lmax, int spin, int dtype, int max_batch, void 
         twhi[h] = make_double2(std::cos(a), std::sin(a));
     }
     // FFT classes: pairs whose transform fits half of the largest length, the rest, and the
-    // split rings (whose combined spectrum of n <= fftmax points passes through LDS)
+    // split rings (whose combined spectrum of n <= fftmax points passes through LDS).  Up to
+    // 2048 points (nside 256) both halves run 256 threads a workgroup, and one launch for all
+    // rings takes less than two, one after the other or on two streams, although the short
+    // rings then get the long ones' LDS: forward FP64 transforms at nside 256 24 -> 14 us (1
+    // map), 67 -> 59 (8), 133 -> 130 (16); FP32 ring step 51 -> 31 us (1 map), 723 -> 714 (64);
+    // nside 32, FP64, an iteration 47 -> 35 us.  Above, the long rings' workgroups of 512 or
+    // 1024 threads and 74 KB or more would leave the short ones a fraction of the CU.
+    const int short_max = fftmax <= 2048 ? fftmax : fftmax / 2;
     std::vector<int> plist;
     p.fft_class_len[0] = 1;
     int nsplit_max = 0;
     for (int c = 0; c < 3; c++) {
         p.fft_class_off[c] = (int)plist.size();
         for (int q = 0; q < p.npair; q++) {
-            const int cls = pf[q].bluestein == 2 ? 2 : (2 * pf[q].fftlen <= fftmax ? 0 : 1);
+            const int cls = pf[q].bluestein == 2 ? 2 : (pf[q].fftlen <= short_max ? 0 : 1);
             if (cls != c) continue;
             plist.push_back(q);
             if (c == 0) p.fft_class_len[0] = std::max(p.fft_class_len[0], pf[q].fftlen);
