@@ -13,9 +13,15 @@
 //     mu_l = A_lm z mu_{l-1} - mu_{l-2},   A_lm = alpha_lm c_{l-1} / c_l,
 // two FP64 operations per (l, ring pair) instead of three.  The synthesis reads the
 // c-scaled coefficients c_lm s_lm and the analysis returns sum mu_l X, which the harmonic
-// kernel multiplies by c_lm.  Each (m, pair) starts at the first l where |lambda_lm| >= 2^-100,
-// from two host-computed values (mu_{l_s - 1}, mu_{l_s}); earlier terms are below 2^-100 and
-// are dropped, and a pair carries mu = 0 (no contribution) before its start.
+// kernel multiplies by c_lm.  Each (m, pair) contributes from the block of kLegBlock values of l
+// that holds the first |lambda_lm| >= 2^-100, from a host-computed recurrence state entering
+// the block; earlier blocks are below 2^-100 and are dropped, and a pair carries mu = 0 (no
+// contribution) before its start.
+//
+// What bounds both kernels is FP64 issue (about 5 cycles per wave instruction): four to six
+// instructions per (l, pair), in the analysis plus the lane reduction.  With starts tested
+// once a block and equal work per XCD, synthesis / analysis of one map went from 123 / 188 to
+// 100 / 138 us at nside 512, lmax 1024, and from 711 / 1114 to 515 / 829 us at nside 1024.
 //
 // Work split: one 64-lane wave per (pair group g, m) or (pair group g, m and lmax - m);
 // lane L handles ring pairs g*64*P + k*64 + L, k < P (adjacent lanes = adjacent latitudes, so

@@ -23,6 +23,7 @@
 // FP32 contractions; the transforms themselves always run in FP64).  The forward transform
 // can apply the messenger pixel update (Eq. 3) to its input as it reads it.
 // Grid (map, pair): the workgroups of one ring pair run back to back, so the pair's chirp
+// tables and noise precision are fetched into L2 once for all maps.
 // Pairs are launched in classes by transform length: up to 2048 points one launch takes all;
 // above, most pairs need at most half the largest length (less LDS and fewer registers per
 // thread, more workgroups per CU); the long Bluestein transforms of the largest polar rings
