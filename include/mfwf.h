@@ -64,7 +64,8 @@ typedef enum {
                      from an FP32 table of lambda_lm; maps, the pixel update, the ring
                      transforms, the harmonic filter's arithmetic and all norms stay
                      FP64.  ~1e-7 relative error per transform, 8e-6 after 300
-                     iterations at nside 512 / lmax 1024                          */
+                     iterations at nside 512 / lmax 1024, of maps whose values and
+                     ring sums lie in FP32's normal range                         */
 } mfwf_dtype;
 
 /*

@@ -255,7 +255,7 @@ static void free_plan(Plan &p) {
                     p.d_tw,   p.d_twlo, p.d_twhi, p.d_chirp, p.d_bhat, p.d_mofs,   p.d_cl,    p.d_M, p.d_pc, p.d_tau,
                     p.d_rho,  p.d_t,    p.d_smap,  p.d_phase,  p.d_apart, p.d_salm,
                     p.d_salm_prev, p.d_sp, p.d_red, p.d_diag, p.d_lam, p.d_lck, p.d_segoff, p.d_loff, p.d_Lp,
-                    p.d_minls32, p.d_ana_items, p.d_syn_items, p.d_ana_tab, p.d_syn_tab, p.d_lofi, p.d_phf, p.d_ph32, p.d_zrow, p.d_a32,
+                    p.d_minls32, p.d_ana_items, p.d_syn_items, p.d_ana_tab, p.d_syn_tab, p.d_lofi, p.d_phf, p.d_ph32, p.d_cscale, p.d_zrow, p.d_a32,
                     p.d_s32, p.d_fp, p.d_fm, p.d_ph32p, p.d_ap32, p.d_ar32, p.d_seb32,
                     p.d_fftsplit};
     for (void *q : ptrs)
@@ -473,7 +473,7 @@ static int autotune(Plan &p, const std::string &devname) {
                 for (int g = 1; g <= fft_cols_group_max(p, c, B); g *= 2) gv.push_back(g);
                 if (gv.size() > 1)
                     MFWF_TRY(tune_knob(p, c == 0 ? kKnobG0 : kKnobG1, gv, [&] {
-                        return launch_fft_inv_fwd_cols(p, p.d_rho, 1.0, nullptr, B);
+                        return launch_fft_inv_fwd_cols(p, p.d_rho, 1.0, B);
                     }));
             }
         }
@@ -618,6 +618,8 @@ static int setup_batched(Plan &p, const std::vector<int> &lstart, const std::vec
     p.nm32 = (p.nm + 15) / 16 * 16;
     MFWF_TRY(dalloc(&p.d_phf, (size_t)p.ncomp * p.max_batch * p.nring * p.nm32, "ring Fourier rows FP32"));
     MFWF_TRY(dalloc(&p.d_ph32, (size_t)p.nring * p.nm * p.C2, "ring Fourier FP32"));
+    MFWF_TRY(dalloc(&p.d_cscale, (size_t)(p.spin == 2 ? 2 : 1) * p.Bp, "column scales"));
+    MFWF_TRY(launch_fill(reinterpret_cast<double *>(p.d_cscale), (p.spin == 2 ? 4L : 2L) * p.Bp, 1.0, p.stream));
     MFWF_TRY(dalloc(&p.d_zrow, (size_t)2 * p.C2, "zero row"));
     MFWF_HIP(hipMemsetAsync(p.d_zrow, 0, sizeof(float) * 2 * p.C2, p.stream));
     MFWF_TRY(dalloc(&p.d_a32, (size_t)p.nalm * p.C2, "analysis FP32"));
@@ -959,7 +961,7 @@ static int iteration_b(Plan &p, const double *rho, int nb, double lam, bool keep
     if (p.chain && p.chain_ready) {
         // the previous synthesis (zero at the start) back to pixels, the pixel update (Eq. 3)
         // and the forward ring transforms, in one kernel on the matrix-core columns
-        MFWF_TRY(launch_fft_inv_fwd_cols(p, rho, lam, nullptr, nb));
+        MFWF_TRY(launch_fft_inv_fwd_cols(p, rho, lam, nb));
     } else {
         // pixel update (Eq. 3) applied inside the forward ring transforms
         MFWF_TRY(launch_fft_fwd_f32(p, p.d_smap, rho, lam, p.d_phf, nb));
@@ -1137,6 +1139,7 @@ static int solve_chunk(Plan &p, const double *input, int nb, double *s_alm_out,
         rho = p.d_rho;
     }
     MFWF_TRY(check_source_finite(p, rho, nb));
+    if (p.dtype == MFWF_F32) MFWF_TRY(launch_col_scale_rho(p, rho, p.tau, 0, nb));
     MFWF_TRY(launch_fill(p.d_smap, nc * p.npix * nb, 0.0, p.stream));
     MFWF_TRY(launch_fill(reinterpret_cast<double *>(p.d_salm), 2 * nc * p.nalm * nb, 0.0, p.stream));
     // batched FP32 form (T; T, Q, U where the chained ring step fits): iterations chained
@@ -1464,6 +1467,7 @@ int mfwf_sht_inv(mfwf_plan plan, const double *alm, double *map, int nmaps) {
     for (int b0 = 0; b0 < nmaps; b0 += p.max_batch) {
         const int nb = std::min(p.max_batch, nmaps - b0);
         if (p.spin == 2 && p.dtype == MFWF_F32) {
+            MFWF_TRY(launch_col_scale(p, alm + 6L * b0 * p.nalm, 2 * p.nalm, kHarmCopy, nb));
             MFWF_TRY(launch_alm_to_cols_pol(p, reinterpret_cast<const double2 *>(alm) + 3L * b0 * p.nalm, nb));
             MFWF_TRY(pol_synthesis_b(p, nb));
             MFWF_TRY(launch_fft_inv_f32(p, p.d_phf, map + 3L * b0 * p.npix, 3 * nb));
@@ -1477,6 +1481,7 @@ int mfwf_sht_inv(mfwf_plan plan, const double *alm, double *map, int nmaps) {
             continue;
         }
         if (p.dtype == MFWF_F32) {
+            MFWF_TRY(launch_col_scale(p, alm + 2L * b0 * p.nalm, 2 * p.nalm, kHarmCopy, nb));
             MFWF_TRY(launch_alm_to_cols(p, reinterpret_cast<const double2 *>(alm) + (long)b0 * p.nalm,
                                         p.d_s32, nb, kHarmCopy));
             MFWF_TRY(launch_gemm_synthesis(p, nb));
@@ -1500,6 +1505,7 @@ int mfwf_sht_fwd(mfwf_plan plan, const double *map, double *alm, int nmaps) {
     for (int b0 = 0; b0 < nmaps; b0 += p.max_batch) {
         const int nb = std::min(p.max_batch, nmaps - b0);
         if (p.spin == 2 && p.dtype == MFWF_F32) {
+            MFWF_TRY(launch_col_scale(p, map + 3L * b0 * p.npix, p.npix, kHarmCopy, nb));
             MFWF_TRY(launch_fft_fwd_f32(p, map + 3L * b0 * p.npix, nullptr, 1.0, p.d_phf, 3 * nb));
             MFWF_TRY(launch_rows_to_cols_pol(p, nb));
             MFWF_TRY(pol_analysis_b(p, nb, 0.0, kPolRaw));
@@ -1515,6 +1521,7 @@ int mfwf_sht_fwd(mfwf_plan plan, const double *map, double *alm, int nmaps) {
             continue;
         }
         if (p.dtype == MFWF_F32) {
+            MFWF_TRY(launch_col_scale(p, map + (long)b0 * p.npix, p.npix, kHarmCopy, nb));
             MFWF_TRY(launch_fft_fwd_f32(p, map + (long)b0 * p.npix, nullptr, 1.0, p.d_phf, nb));
             MFWF_TRY(launch_rows_to_cols(p, nb));
             MFWF_TRY(launch_gemm_analysis(p, nb, p.d_a32, nullptr, 0.0, 0.0));
@@ -1546,6 +1553,7 @@ int mfwf_fluctuation_rhs(mfwf_plan plan, const double *g1, const double *h, int 
                 // K h in FP64 (the FP32 tables carry c, so the T component is not c-scaled)
                 MFWF_TRY(launch_harmonic_pol(p, reinterpret_cast<const double2 *>(h) + 3L * b0 * p.nalm,
                                              1, 1.0, 0.0, kHarmInvSqrtC, p.d_sp, nullptr, nullptr, nb));
+                MFWF_TRY(launch_col_scale(p, reinterpret_cast<const double *>(p.d_sp), 2 * p.nalm, kHarmCopy, nb));
                 MFWF_TRY(launch_alm_to_cols_pol(p, p.d_sp, nb));
                 MFWF_TRY(pol_synthesis_b(p, nb));
                 MFWF_TRY(launch_fft_inv_f32(p, p.d_phf, p.d_t, 3 * nb));
@@ -1560,6 +1568,7 @@ int mfwf_fluctuation_rhs(mfwf_plan plan, const double *g1, const double *h, int 
             continue;
         }
         if (p.dtype == MFWF_F32) {
+            MFWF_TRY(launch_col_scale(p, h + 2L * b0 * p.nalm, 2 * p.nalm, kHarmInvSqrtC, nb));
             MFWF_TRY(launch_alm_to_cols(p, reinterpret_cast<const double2 *>(h) + (long)b0 * p.nalm,
                                         p.d_s32, nb, kHarmInvSqrtC));
             MFWF_TRY(launch_gemm_synthesis(p, nb));
@@ -1729,6 +1738,7 @@ static int cooled_chunk(mfwf_plan plan, const double *data, int nb, double *s_al
                 MFWF_TRY(launch_fill(q->d_smap, nc * p.npix * nb, 0.0, q->stream));
             MFWF_TRY(launch_fill(reinterpret_cast<double *>(q->d_salm), 2 * nc * q->nalm * nb, 0.0, q->stream));
             if (q->dtype == MFWF_F32) {  // harmonic iterate of the FP32 form (outside any capture)
+                MFWF_TRY(launch_col_scale_rho(*q, rho, q->tau, 0, nb));
                 MFWF_HIP(hipMemsetAsync(q->d_s32, 0, sizeof(float) * (size_t)q->nalm * q->C2, q->stream));
                 if (q->spin == 2)
                     MFWF_HIP(hipMemsetAsync(q->d_seb32, 0, sizeof(float) * (size_t)q->nalm * 2 * q->C2, q->stream));
@@ -1926,6 +1936,7 @@ static int bounded_chunk(Plan &p, const double *data, int nb, double *s_alm_out,
         MFWF_TRY(launch_rho_from_data(data, p.d_M, p.d_rho, p.npix, nb, p.stream));
     const double *rho = p.d_rho;
     MFWF_TRY(check_source_finite(p, rho, nb));
+    if (p.dtype == MFWF_F32) MFWF_TRY(launch_col_scale_rho(p, rho, p.tau, 0, nb));
     MFWF_TRY(launch_fill(p.d_smap, nc * p.npix * nb, 0.0, p.stream));
     MFWF_TRY(launch_fill(reinterpret_cast<double *>(p.d_salm), 2 * nc * p.nalm * nb, 0.0, p.stream));
     if (p.dtype == MFWF_F32) {
@@ -2163,7 +2174,7 @@ int mfwf_time_kernels(mfwf_plan plan, int nmaps, int reps, double *ms_out) {
                 // 1: the ring step of a chained iteration: the previous synthesis back to
                 // pixels, pixel update and forward transforms in one kernel on the columns
                 // (the inverse transforms run there, so 5 is empty)
-                case 1: f = [&] { return launch_fft_inv_fwd_cols(p, p.d_rho, 1.0, nullptr, nb); }; break;
+                case 1: f = [&] { return launch_fft_inv_fwd_cols(p, p.d_rho, 1.0, nb); }; break;
                 case 2: f = [&] { return launch_gemm_analysis(p, nb, nullptr, p.d_s32, p.omega, p.omega * p.tau, p.omega); }; break;
                 case 3: ms_out[k] = 0.0; continue;  // harmonic update runs inside the analysis
                 case 4: f = [&] { return launch_gemm_synthesis(p, nb); }; break;

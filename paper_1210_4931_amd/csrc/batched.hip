@@ -139,6 +139,52 @@ struct LamGen {
 };
 
 // ---------------------------------------------------------------------------------------
+// The scale of a map's columns.  The contractions split FP32 values into bf16 pieces; the last
+// piece of a value below 2^-110 lies below bf16's smallest number, so small maps would lose
+// bits that FP32 keeps down to 2^-126 (1.3e-7 relative error, but 2.6e-4 at 1e-37).  The
+// columns of a map therefore carry the map times a power of two, which changes no rounding:
+// 2^40 if no value of the map reaches 2^-70, else 1.  The regrouping and conversion kernels and the
+// ring step apply it and take it off; everything else is linear in it.
+//
+// One workgroup per (map, group of components) looks for a value that reaches 2^-70: first at one
+// value per thread, spread over the whole map, which ends the search on any map that is not
+// small or nearly empty (a transform's call then takes 5 us longer: the launch and two memory
+// latencies), then through the map in order.
+// scale[b] = (S, 1/S); grid.y = 2: a group of n0 and one of n1 values per map (T; Q and U, or
+// E and B), the second to scale[Bp + b]; both: one group, to both.  cl: the values are
+// C^-1/2 x (mode 2 of k_alm_to_cols).
+// ---------------------------------------------------------------------------------------
+static constexpr double kSmallMap = 0x1p-70, kSmallScale = 0x1p40;
+
+__global__ void __launch_bounds__(1024)
+k_col_scale(const double *__restrict__ x, long stride, long n0, long n1, double factor,
+            const double *__restrict__ cl, const int *__restrict__ lofi, int both, int Bp,
+            double2 *__restrict__ scale) {
+    const int b = blockIdx.x, g = blockIdx.y;
+    const double *v = x + b * stride + (g ? n0 : 0);
+    const long n = g ? n1 : n0;
+    auto reaches = [&](long i) {  // written so that a NaN counts as large
+        double f = factor;
+        if (cl) {
+            const double C = cl[lofi[i >> 1]];
+            f = C > 0.0 ? 1.0 / sqrt(C) : 0.0;
+        }
+        return !(fabs(f * v[i]) < kSmallMap);
+    };
+    bool big = __syncthreads_or(reaches(threadIdx.x * (n - 1) / 1023));
+    for (long k = 0; k < n && !big; k += 8 * 1024) {  // big is the same for every thread
+        bool any = false;
+#pragma unroll
+        for (int u = 0; u < 8; u++) any |= reaches(min(k + 1024 * u + threadIdx.x, n - 1));
+        big = __syncthreads_or(any);
+    }
+    if (threadIdx.x != 0) return;
+    const double2 s = big ? make_double2(1.0, 1.0) : make_double2(kSmallScale, 1.0 / kSmallScale);
+    scale[g * Bp + b] = s;
+    if (both) scale[Bp + b] = s;
+}
+
+// ---------------------------------------------------------------------------------------
 // Layout changes between the per-map ring-Fourier rows of the ring transforms,
 // [map][ring][m] (FP32 complex), and the contraction layout [m][ring][C2] with columns 2b
 // (re) and 2b + 1 (im) of map b.  One workgroup moves a tile of 64 values of m x 64 maps
@@ -148,7 +194,7 @@ struct LamGen {
 // ---------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256)
 k_rows_to_cols(const float2 *__restrict__ phf, float *__restrict__ ph32, int nring, int nm,
-               int rs, int nb, int Bp, int C2) {
+               int rs, int nb, int Bp, int C2, const double2 *__restrict__ scale) {
     __shared__ float2 tile[64][64 + 1];  // [map][m]
     const int ring = blockIdx.x, m0 = 64 * blockIdx.y, b0 = 64 * blockIdx.z;
     float2 v[16];
@@ -163,12 +209,15 @@ k_rows_to_cols(const float2 *__restrict__ phf, float *__restrict__ ph32, int nri
         const int e = threadIdx.x + 256 * u;
         tile[e >> 6][e & 63] = v[u];
     }
+    const float sc = (float)scale[min(b0 + ((int)threadIdx.x & 63), nb - 1)].x;
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < 16; u++) {
         const int e = threadIdx.x + 256 * u, mm = e >> 6, bb = e & 63, b = b0 + bb, m = m0 + mm;
+        const float2 x = tile[bb][mm];
         if (b < Bp && m < nm)
-            *reinterpret_cast<float2 *>(ph32 + ((long)m * nring + ring) * C2 + 2 * b) = tile[bb][mm];
+            *reinterpret_cast<float2 *>(ph32 + ((long)m * nring + ring) * C2 + 2 * b) =
+                make_float2(sc * x.x, sc * x.y);
     }
 }
 
@@ -182,16 +231,17 @@ k_zero_map_cols(float *__restrict__ ph32, long nrows, int C2, int b) {
 
 __global__ void __launch_bounds__(256)
 k_cols_to_rows(const float *__restrict__ ph32, float2 *__restrict__ phf, int nring, int nm,
-               int rs, int nb, int C2) {
+               int rs, int nb, int C2, const double2 *__restrict__ scale) {
     __shared__ float2 tile[64][64 + 1];  // [m][map]
     const int ring = blockIdx.x, m0 = 64 * blockIdx.y, b0 = 64 * blockIdx.z;
+    const float sc = (float)scale[min(b0 + ((int)threadIdx.x & 63), nb - 1)].y;
     float2 v[16];
 #pragma unroll
     for (int u = 0; u < 16; u++) {
         const int e = threadIdx.x + 256 * u, mm = e >> 6, bb = e & 63, b = b0 + bb, m = m0 + mm;
         const float2 x = *reinterpret_cast<const float2 *>(
             ph32 + ((long)min(m, nm - 1) * nring + ring) * C2 + 2 * min(b, nb - 1));
-        v[u] = (b < nb && m < nm) ? x : make_float2(0.f, 0.f);
+        v[u] = (b < nb && m < nm) ? make_float2(sc * x.x, sc * x.y) : make_float2(0.f, 0.f);
     }
 #pragma unroll
     for (int u = 0; u < 16; u++) {
@@ -987,25 +1037,31 @@ k_gemm_synthesis(const float *__restrict__ lam, LamGen gen, const long *__restri
 __global__ void __launch_bounds__(256)
 k_alm_to_cols(const double2 *__restrict__ alm, float *__restrict__ x32,
               const double *__restrict__ cl, const int *__restrict__ lofi, long nalm, int nb,
-              int C2, int mode) {
+              int C2, int mode, const double2 *__restrict__ scale) {
     __shared__ float tile[64][65];  // [alm within tile][col within tile]
     const long i0 = (long)blockIdx.x * 64;
     const int c0 = blockIdx.y * 64;  // columns c0 .. c0+63 = maps c0/2 .. c0/2+31
-    for (int e = threadIdx.x; e < 64 * 32; e += 256) {
-        const int ii = e & 63, bb = e >> 6;
-        const long i = i0 + ii;
-        const int b = c0 / 2 + bb;
-        double2 v = make_double2(0.0, 0.0);
-        if (i < nalm && b < nb) {
-            v = alm[(long)b * nalm + i];
-            if (mode == 2) {
-                const double C = cl[lofi[i]];
-                const double f = C > 0.0 ? 1.0 / sqrt(C) : 0.0;
-                v = make_double2(f * v.x, f * v.y);
-            }
-        }
-        tile[ii][2 * bb] = (float)v.x;
-        tile[ii][2 * bb + 1] = (float)v.y;
+    const int ii = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long ic = min(i0 + ii, nalm - 1);
+    double f = 1.0;
+    if (mode == 2) {
+        const double C = cl[lofi[ic]];
+        f = C > 0.0 ? 1.0 / sqrt(C) : 0.0;
+    }
+    double2 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; u++) {  // clamped, so that all loads are in flight together
+        const int b = min(c0 / 2 + w + 4 * u, nb - 1);
+        const double fs = f * scale[b].x;
+        const double2 x = alm[(long)b * nalm + ic];
+        v[u] = make_double2(fs * x.x, fs * x.y);
+    }
+#pragma unroll
+    for (int u = 0; u < 8; u++) {
+        const int bb = w + 4 * u;
+        const bool on = i0 + ii < nalm && c0 / 2 + bb < nb;
+        tile[ii][2 * bb] = on ? (float)v[u].x : 0.f;
+        tile[ii][2 * bb + 1] = on ? (float)v[u].y : 0.f;
     }
     __syncthreads();
     for (int e = threadIdx.x; e < 64 * 64; e += 256) {
@@ -1018,7 +1074,7 @@ k_alm_to_cols(const double2 *__restrict__ alm, float *__restrict__ x32,
 // x32 [nalm][C2] FP32 -> alm FP64 [nb][nalm], times f (mode 1: Omega; mode 3: 1)
 __global__ void __launch_bounds__(256)
 k_cols_to_alm(const float *__restrict__ x32, double2 *__restrict__ alm, long nalm, int nb, int C2,
-              double scale) {
+              double scale, const double2 *__restrict__ cscale) {
     __shared__ float tile[64][65];
     const long i0 = (long)blockIdx.x * 64;
     const int c0 = blockIdx.y * 64;
@@ -1027,13 +1083,16 @@ k_cols_to_alm(const float *__restrict__ x32, double2 *__restrict__ alm, long nal
         const long i = i0 + ii;
         tile[ii][cc] = (i < nalm && c0 + cc < C2) ? x32[i * C2 + c0 + cc] : 0.f;
     }
+    const int ii = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double f[8];
+#pragma unroll
+    for (int u = 0; u < 8; u++) f[u] = scale * cscale[min(c0 / 2 + w + 4 * u, nb - 1)].y;
     __syncthreads();
-    for (int e = threadIdx.x; e < 64 * 32; e += 256) {
-        const int ii = e & 63, bb = e >> 6;
-        const long i = i0 + ii;
-        const int b = c0 / 2 + bb;
-        if (i < nalm && b < nb)
-            alm[(long)b * nalm + i] = make_double2(scale * tile[ii][2 * bb], scale * tile[ii][2 * bb + 1]);
+#pragma unroll
+    for (int u = 0; u < 8; u++) {
+        const int bb = w + 4 * u, b = c0 / 2 + bb;
+        if (i0 + ii < nalm && b < nb)
+            alm[(long)b * nalm + i0 + ii] = make_double2(f[u] * tile[ii][2 * bb], f[u] * tile[ii][2 * bb + 1]);
     }
 }
 
@@ -1056,9 +1115,31 @@ int launch_lam_ckpt(const Plan &p) {
     return MFWF_OK;
 }
 
+static int col_scale(const Plan &p, const double *x, long stride, long n0, long n1, double factor,
+                     const double *cl, int both, int nb, double2 *scale) {
+    hipLaunchKernelGGL(k_col_scale, dim3(nb, n1 > 0 ? 2 : 1), dim3(1024), 0, p.stream, x, stride, n0,
+                       n1, factor, cl, p.d_lofi, both, p.Bp, scale);
+    MFWF_HIP(hipGetLastError());
+    return MFWF_OK;
+}
+
+// of the maps (n = npix) or coefficients (n = 2 nalm) a transform reads, per map T and, spin 2,
+// the other two components
+int launch_col_scale(const Plan &p, const double *x, long n, int mode, int nb) {
+    return col_scale(p, x, p.ncomp * n, n, (p.ncomp - 1) * n, 1.0, mode == kHarmInvSqrtC ? p.d_cl : nullptr,
+                     0, nb, p.d_cscale);
+}
+
+// of the source rho of a solve's maps b0 .. b0 + nb - 1: the iterates are of the size of tau rho and
+// above (tau M <= 1).  The components of T, Q, U mix in the update and share a scale.
+int launch_col_scale_rho(const Plan &p, const double *rho, double tau, int b0, int nb) {
+    return col_scale(p, rho, p.ncomp * p.npix, p.ncomp * p.npix, 0, tau, nullptr, p.spin == 2, nb,
+                     p.d_cscale + b0);
+}
+
 int launch_rows_to_cols(const Plan &p, int nb) {
     hipLaunchKernelGGL(k_rows_to_cols, dim3(p.nring, (p.nm + 63) / 64, (p.Bp + 63) / 64), dim3(256), 0,
-                       p.stream, p.d_phf, p.d_ph32, p.nring, p.nm, p.nm32, nb, p.Bp, p.C2);
+                       p.stream, p.d_phf, p.d_ph32, p.nring, p.nm, p.nm32, nb, p.Bp, p.C2, p.d_cscale);
     MFWF_HIP(hipGetLastError());
     return MFWF_OK;
 }
@@ -1073,7 +1154,7 @@ int launch_zero_map_cols(const Plan &p, int b) {
 
 int launch_cols_to_rows(const Plan &p, int nb) {
     hipLaunchKernelGGL(k_cols_to_rows, dim3(p.nring, (p.nm + 63) / 64, (nb + 63) / 64), dim3(256), 0,
-                       p.stream, p.d_ph32, p.d_phf, p.nring, p.nm, p.nm32, nb, p.C2);
+                       p.stream, p.d_ph32, p.d_phf, p.nring, p.nm, p.nm32, nb, p.C2, p.d_cscale);
     MFWF_HIP(hipGetLastError());
     return MFWF_OK;
 }
@@ -1177,14 +1258,14 @@ int launch_gemm_synthesis_on(const Plan &p, int nb, int w, const float *table, c
 
 int launch_alm_to_cols(const Plan &p, const double2 *alm, float *x32, int nb, int mode) {
     hipLaunchKernelGGL(k_alm_to_cols, dim3((p.nalm + 63) / 64, (p.C2 + 63) / 64), dim3(256), 0,
-                       p.stream, alm, x32, p.d_cl, p.d_lofi, p.nalm, nb, p.C2, mode);
+                       p.stream, alm, x32, p.d_cl, p.d_lofi, p.nalm, nb, p.C2, mode, p.d_cscale);
     MFWF_HIP(hipGetLastError());
     return MFWF_OK;
 }
 
 int launch_cols_to_alm(const Plan &p, const float *x32, double2 *alm, int nb, double scale) {
     hipLaunchKernelGGL(k_cols_to_alm, dim3((p.nalm + 63) / 64, (p.C2 + 63) / 64), dim3(256), 0,
-                       p.stream, x32, alm, p.nalm, nb, p.C2, scale);
+                       p.stream, x32, alm, p.nalm, nb, p.C2, scale, p.d_cscale);
     MFWF_HIP(hipGetLastError());
     return MFWF_OK;
 }

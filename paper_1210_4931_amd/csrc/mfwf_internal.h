@@ -146,6 +146,8 @@ struct Plan {
     bool chain = false;
     bool chain_ready = false;    // d_ph32 holds the synthesis of the iterate in d_smap
     float *d_ph32 = nullptr;     // [nm][nring][C2] ring-Fourier, maps innermost
+    double2 *d_cscale = nullptr; // [Bp], spin 2 [2][Bp] (T; Q, U and E, B): the power of two S that a
+                                 // map's columns carry, and 1/S
     float *d_zrow = nullptr;     // [2 C2] zeros: the equator pair's south ring
     float *d_a32 = nullptr;      // [nalm][C2] analysis output
     float *d_s32 = nullptr;      // [nalm][C2] synthesis input
@@ -202,13 +204,13 @@ int launch_fft_inv(const Plan &p, const double2 *phase, double *maps, int nb);
 int launch_fft_fwd_f32(const Plan &p, const double *maps, const double *rho, double lam,
                        float2 *phase, int nb);
 int launch_fft_inv_f32(const Plan &p, const float2 *phase, double *maps, int nb);
-// synthesis columns d_ph32 -> maps s (to smap if not null) -> t of Eq. (3) -> the columns of
-// its forward transform, in place (one iteration's ring steps without the map in memory)
 // Fork the plan's side stream from its stream before the two in-LDS ring classes of the
 // chained FP32 ring step, and join it back after them (no-ops without a side stream).
 int ring_fork(const Plan &p);
 int ring_join(const Plan &p);
-int launch_fft_inv_fwd_cols(const Plan &p, const double *rho, double lam, double *smap, int nb);
+// synthesis columns d_ph32 -> maps s -> t of Eq. (3) -> the columns of its forward transform, in
+// place (one iteration's ring steps without the map in memory)
+int launch_fft_inv_fwd_cols(const Plan &p, const double *rho, double lam, int nb);
 // T, Q, U batched form: one iteration's ring steps on the columns d_ph32 / d_ph32p from the
 // synthesis columns d_ph32 / d_ph32p (chained iterations), where fft_pol_chain_ok
 bool fft_pol_chain_ok(const Plan &p);
@@ -231,6 +233,10 @@ int leg_analysis_pairs_per_lane(int v);
 // batched.hip (FP32 form)
 int launch_lam_table(const Plan &p);
 int launch_lam_ckpt(const Plan &p);  // d_lck from the recurrence
+// d_cscale for the maps or coefficients x that a transform reads (n doubles per component; mode
+// kHarmInvSqrtC: C^-1/2 x), or for the sources rho of maps b0 .. b0 + nb - 1 of a solve
+int launch_col_scale(const Plan &p, const double *x, long n, int mode, int nb);
+int launch_col_scale_rho(const Plan &p, const double *rho, double tau, int b0, int nb);
 int launch_rows_to_cols(const Plan &p, int nb);  // d_phf -> d_ph32
 int launch_cols_to_rows(const Plan &p, int nb);  // d_ph32 -> d_phf
 int launch_zero_map_cols(const Plan &p, int b);  // map b's columns of d_ph32 = 0

@@ -82,7 +82,8 @@ k_pol_tables(const double *__restrict__ Atab, const double *__restrict__ ctab,
 // ---------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256)
 k_rows_to_cols_pol(const float2 *__restrict__ phf, float *__restrict__ colT,
-                   float *__restrict__ colP, int nring, int nm, int rs, int nb, int Bp) {
+                   float *__restrict__ colP, int nring, int nm, int rs, int nb, int Bp,
+                   const double2 *__restrict__ scale) {
     __shared__ float2 tile[3][32][64 + 1];  // [component][map][m]
     const int ring = blockIdx.x, m0 = 64 * blockIdx.y, b0 = 32 * blockIdx.z;
     float2 v[24];
@@ -98,6 +99,8 @@ k_rows_to_cols_pol(const float2 *__restrict__ phf, float *__restrict__ colT,
         const int e = threadIdx.x + 256 * u;
         tile[e >> 11][(e >> 6) & 31][e & 63] = v[u];
     }
+    const int bs = min(b0 + ((int)threadIdx.x & 31), nb - 1);
+    const float scT = (float)scale[bs].x, scP = (float)scale[Bp + bs].x;  // column scales (k_col_scale)
     __syncthreads();
     const long C2 = 2L * Bp;
 #pragma unroll
@@ -106,8 +109,9 @@ k_rows_to_cols_pol(const float2 *__restrict__ phf, float *__restrict__ colT,
         if (b >= Bp || m >= nm) continue;
         const long row = (long)m * nring + ring;
         const float2 t = tile[0][bb][mm], q = tile[1][bb][mm], u2 = tile[2][bb][mm];
-        *reinterpret_cast<float2 *>(colT + row * C2 + 2 * b) = t;
-        *reinterpret_cast<float4 *>(colP + row * 2 * C2 + 4 * b) = make_float4(q.x, q.y, u2.x, u2.y);
+        *reinterpret_cast<float2 *>(colT + row * C2 + 2 * b) = make_float2(scT * t.x, scT * t.y);
+        *reinterpret_cast<float4 *>(colP + row * 2 * C2 + 4 * b) =
+            make_float4(scP * q.x, scP * q.y, scP * u2.x, scP * u2.y);
     }
 }
 
@@ -115,9 +119,12 @@ k_rows_to_cols_pol(const float2 *__restrict__ phf, float *__restrict__ colT,
 // epilogue from P' and R').
 __global__ void __launch_bounds__(256)
 k_cols_to_rows_pol(const float *__restrict__ colT, const float *__restrict__ colQU,
-                   float2 *__restrict__ phf, int nring, int nm, int rs, int nb, int Bp) {
+                   float2 *__restrict__ phf, int nring, int nm, int rs, int nb, int Bp,
+                   const double2 *__restrict__ scale) {
     __shared__ float2 tile[3][64][32 + 1];  // [component][m][map]
     const int ring = blockIdx.x, m0 = 64 * blockIdx.y, b0 = 32 * blockIdx.z;
+    const int bs = min(b0 + ((int)threadIdx.x & 31), nb - 1);
+    const float scT = (float)scale[bs].y, scP = (float)scale[Bp + bs].y;
     const long C2 = 2L * Bp;
     float2 vt[8];
     float4 vq[8];
@@ -134,9 +141,9 @@ k_cols_to_rows_pol(const float *__restrict__ colT, const float *__restrict__ col
         const int e = threadIdx.x + 256 * u, mm = e >> 5, bb = e & 31;
         const bool on = b0 + bb < nb && m0 + mm < nm;
         const float2 z = make_float2(0.f, 0.f);
-        tile[0][mm][bb] = on ? vt[u] : z;
-        tile[1][mm][bb] = on ? make_float2(vq[u].x, vq[u].y) : z;  // Q
-        tile[2][mm][bb] = on ? make_float2(vq[u].z, vq[u].w) : z;  // U
+        tile[0][mm][bb] = on ? make_float2(scT * vt[u].x, scT * vt[u].y) : z;
+        tile[1][mm][bb] = on ? make_float2(scP * vq[u].x, scP * vq[u].y) : z;  // Q
+        tile[2][mm][bb] = on ? make_float2(scP * vq[u].z, scP * vq[u].w) : z;  // U
     }
     __syncthreads();
 #pragma unroll
@@ -197,17 +204,28 @@ k_pol_combine(const float *__restrict__ aT, const float *__restrict__ aP,
 // ---------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256)
 k_alm_to_cols_pol(const double2 *__restrict__ alm, float *__restrict__ colT,
-                  float *__restrict__ colEB, long nalm, int nb, int Bp) {
+                  float *__restrict__ colEB, long nalm, int nb, int Bp,
+                  const double2 *__restrict__ scale) {
     __shared__ float2 tile[3][64][32 + 1];  // [component][coefficient][map]
     const long i0 = (long)blockIdx.x * 64;
     const int b0 = 32 * blockIdx.y;
-    for (int e = threadIdx.x; e < 3 * 32 * 64; e += 256) {
-        const int c = e >> 11, bb = (e >> 6) & 31, ii = e & 63;
-        const long i = i0 + ii;
-        const int b = b0 + bb;
-        double2 v = make_double2(0.0, 0.0);
-        if (i < nalm && b < nb) v = alm[(3L * b + c) * nalm + i];
-        tile[c][ii][bb] = make_float2((float)v.x, (float)v.y);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ci = threadIdx.x & 63;
+    const long ic = min(i0 + ci, nalm - 1);
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        double2 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) {  // clamped, so that all loads are in flight together
+            const int b = min(b0 + w + 4 * u, nb - 1);
+            const double f = scale[c ? Bp + b : b].x;
+            const double2 x = alm[(3L * b + c) * nalm + ic];
+            v[u] = make_double2(f * x.x, f * x.y);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+            const bool on = i0 + ci < nalm && b0 + w + 4 * u < nb;
+            tile[c][ci][w + 4 * u] = on ? make_float2((float)v[u].x, (float)v[u].y) : make_float2(0.f, 0.f);
+        }
     }
     __syncthreads();
     const long C2 = 2L * Bp;
@@ -224,7 +242,8 @@ k_alm_to_cols_pol(const double2 *__restrict__ alm, float *__restrict__ colT,
 
 __global__ void __launch_bounds__(256)
 k_cols_to_alm_pol(const float *__restrict__ colT, const float *__restrict__ colEB,
-                  double2 *__restrict__ alm, long nalm, int nb, int Bp) {
+                  double2 *__restrict__ alm, long nalm, int nb, int Bp,
+                  const double2 *__restrict__ scale) {
     __shared__ float2 tile[3][64][32 + 1];
     const long i0 = (long)blockIdx.x * 64;
     const int b0 = 32 * blockIdx.y;
@@ -244,16 +263,24 @@ k_cols_to_alm_pol(const float *__restrict__ colT, const float *__restrict__ colE
         tile[1][ii][bb] = x;
         tile[2][ii][bb] = y;
     }
-    __syncthreads();
-    for (int e = threadIdx.x; e < 3 * 32 * 64; e += 256) {
-        const int c = e >> 11, bb = (e >> 6) & 31, ii = e & 63;
-        const long i = i0 + ii;
-        const int b = b0 + bb;
-        if (i < nalm && b < nb) {
-            const float2 v = tile[c][ii][bb];
-            alm[(3L * b + c) * nalm + i] = make_double2(v.x, v.y);
-        }
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ci = threadIdx.x & 63;
+    double f[2][8];
+#pragma unroll
+    for (int u = 0; u < 8; u++) {
+        const int b = min(b0 + w + 4 * u, nb - 1);
+        f[0][u] = scale[b].y;
+        f[1][u] = scale[Bp + b].y;
     }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 3; c++)
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+            const int b = b0 + w + 4 * u;
+            const float2 v = tile[c][ci][w + 4 * u];
+            if (i0 + ci < nalm && b < nb)
+                alm[(3L * b + c) * nalm + i0 + ci] = make_double2(f[c > 0][u] * v.x, f[c > 0][u] * v.y);
+        }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -270,7 +297,7 @@ int launch_pol_tables(const Plan &p) {
 int launch_rows_to_cols_pol(const Plan &p, int nb) {
     hipLaunchKernelGGL(k_rows_to_cols_pol, dim3(p.nring, (p.nm + 63) / 64, (p.Bp + 31) / 32),
                        dim3(256), 0, p.stream, p.d_phf, p.d_ph32, p.d_ph32p, p.nring, p.nm, p.nm32,
-                       nb, p.Bp);
+                       nb, p.Bp, p.d_cscale);
     MFWF_HIP(hipGetLastError());
     return MFWF_OK;
 }
@@ -278,7 +305,7 @@ int launch_rows_to_cols_pol(const Plan &p, int nb) {
 int launch_cols_to_rows_pol(const Plan &p, int nb) {
     hipLaunchKernelGGL(k_cols_to_rows_pol, dim3(p.nring, (p.nm + 63) / 64, (nb + 31) / 32),
                        dim3(256), 0, p.stream, p.d_ph32, p.d_ph32p, p.d_phf, p.nring,
-                       p.nm, p.nm32, nb, p.Bp);
+                       p.nm, p.nm32, nb, p.Bp, p.d_cscale);
     MFWF_HIP(hipGetLastError());
     return MFWF_OK;
 }
@@ -294,14 +321,14 @@ int launch_pol_combine(const Plan &p, double lto, int mode) {
 
 int launch_alm_to_cols_pol(const Plan &p, const double2 *alm, int nb) {
     hipLaunchKernelGGL(k_alm_to_cols_pol, dim3((unsigned)((p.nalm + 63) / 64), (p.Bp + 31) / 32),
-                       dim3(256), 0, p.stream, alm, p.d_s32, p.d_seb32, p.nalm, nb, p.Bp);
+                       dim3(256), 0, p.stream, alm, p.d_s32, p.d_seb32, p.nalm, nb, p.Bp, p.d_cscale);
     MFWF_HIP(hipGetLastError());
     return MFWF_OK;
 }
 
 int launch_cols_to_alm_pol(const Plan &p, double2 *alm, int nb) {
     hipLaunchKernelGGL(k_cols_to_alm_pol, dim3((unsigned)((p.nalm + 63) / 64), (nb + 31) / 32),
-                       dim3(256), 0, p.stream, p.d_s32, p.d_seb32, alm, p.nalm, nb, p.Bp);
+                       dim3(256), 0, p.stream, p.d_s32, p.d_seb32, alm, p.nalm, nb, p.Bp, p.d_cscale);
     MFWF_HIP(hipGetLastError());
     return MFWF_OK;
 }

@@ -400,7 +400,8 @@ k_fft_split_sub(const double *__restrict__ maps, double2 *__restrict__ scratch, 
                 int fftmax, const double2 *__restrict__ chirp, const double2 *__restrict__ bhat,
                 long npix, const double *__restrict__ rho = nullptr,
                 const double *__restrict__ M = nullptr, double lam = 1.0, double tau = 0.0,
-                long mstride = 0, const double *__restrict__ tau_b = nullptr) {
+                long mstride = 0, const double *__restrict__ tau_b = nullptr,
+                const double2 *__restrict__ cscale = nullptr) {
     extern __shared__ double2 buf[];
     const int p = plist[blockIdx.y], b = blockIdx.x, r = blockIdx.z;
     const PairFFT pf = pfft[p];
@@ -414,7 +415,8 @@ k_fft_split_sub(const double *__restrict__ maps, double2 *__restrict__ scratch, 
     double2 *Z = G + sstride / 2 + (long)r * i;
     const double *sp = maps + (long)b * npix;
     if (PIX && tau_b) tau = tau_b[b];
-    const double lt = lam * tau, l1t = (lam - 1.0) * tau;
+    // cscale: maps hold s times its column scale (chained iterations), so t is formed scaled
+    const double lt = PIX && cscale ? lam * tau * cscale[b].x : lam * tau, l1t = (lam - 1.0) * tau;
     const double *rp = rho + (long)b * npix;
     const double *mp = M + (long)b * mstride;
     auto pix = [&](long q) {
@@ -537,10 +539,12 @@ k_fft_inv_split_combine(double *__restrict__ maps, const double2 *__restrict__ s
 
 // One iteration's ring steps in one pass over a pair (batched FP32 form), on the
 // matrix-core columns [m][ring][C2] (map b at column 2b) in place: the synthesis F is folded
-// and transformed back to the pair's pixels s (optionally stored to smap), the messenger
+// and transformed back to the pair's pixels s, the messenger
 // field t of Eq. (3) is formed from s, rho and M on the spot, and its transform overwrites
 // the columns with G = the analysis input.  The map s never travels through memory; the
-// arithmetic is that of k_fft_inv followed by k_fft_fwd<PIX>, value for value.
+// arithmetic is that of k_fft_inv followed by k_fft_fwd<PIX>, value for value.  The columns
+// hold s times the map's column scale; t is linear in s and rho, so it comes out with the
+// same scale if the factor of rho carries it.
 //
 // A workgroup takes G maps b0 .. b0 + G - 1 of one pair (G groups of TPB threads, one
 // transform each in its own LDS area): the column entries of those maps for one (m, ring)
@@ -706,9 +710,10 @@ __device__ __forceinline__ void store_cols_group(const double2 *buf, int area, c
 
 template <int TPB, int EPT, int G>
 __global__ void __launch_bounds__(TPB * G)
-k_fft_inv_fwd(float2 *__restrict__ data, int C2, int nmap, int ngrp, int npl, double *__restrict__ smap,
+k_fft_inv_fwd(float2 *__restrict__ data, int C2, int nmap, int ngrp, int npl,
               const double *__restrict__ rho, const double *__restrict__ M, double lam,
               double tau, long mstride, const double *__restrict__ tau_b,
+              const double2 *__restrict__ cscale,
               const PairFFT *__restrict__ pfft, const int *__restrict__ plist,
               const double2 *__restrict__ twlo, const double2 *__restrict__ twhi, int ntwhi,
               int fftmax, const double2 *__restrict__ chirp, const double2 *__restrict__ bhat,
@@ -740,7 +745,7 @@ k_fft_inv_fwd(float2 *__restrict__ data, int C2, int nmap, int ngrp, int npl, do
     __syncthreads();
     ring_dft_c<TPB, EPT>(buf, pf, tw, fftmax, chirp, bhat);
     if (tau_b && live) tau = tau_b[b];
-    const double lt = lam * tau, l1t = (lam - 1.0) * tau;
+    const double lt = lam * tau * (live ? cscale[b].x : 1.0), l1t = (lam - 1.0) * tau;
     const double *rp = rho + (long)b * npix;
     const double *mp = M + (long)b * mstride;
     double mN[EPT], mS[EPT], rN[EPT], rS[EPT];
@@ -762,10 +767,6 @@ k_fft_inv_fwd(float2 *__restrict__ data, int C2, int nmap, int ngrp, int npl, do
         if (u * TPB >= n) break;
         const int jj = tid + u * TPB;
         const double2 xs = cconj(dft_bin(buf, pf, chirp, min(jj, n - 1)));  // (s_N, s_S) at jj
-        if (smap && live && jj < n) {
-            smap[(long)b * npix + pf.startN + jj] = xs.x;
-            if (!equator) smap[(long)b * npix + pf.startS + jj] = xs.y;
-        }
         v[u] = make_double2(pix(xs.x, mN[u], rN[u]), equator ? 0.0 : pix(xs.y, mS[u], rS[u]));
     }
     __syncthreads();  // every read of the inverse transform is done
@@ -791,7 +792,7 @@ template <int TPB, int EPT>
 __global__ void __launch_bounds__(TPB)
 k_fft_inv_fwd_pol(float *__restrict__ colT, float *__restrict__ colP, int C2, int nmap, int npl, const double *__restrict__ rho,
                   const double *__restrict__ M6, double lam, double tau,
-                  const PairFFT *__restrict__ pfft, const int *__restrict__ plist,
+                  const double2 *__restrict__ cscale, const PairFFT *__restrict__ pfft, const int *__restrict__ plist,
                   const double2 *__restrict__ twlo, const double2 *__restrict__ twhi, int ntwhi,
                   int fftmax, const double2 *__restrict__ chirp, const double2 *__restrict__ bhat,
                   long npix, int nring, int nm, int lmax, int fftlen_class) {
@@ -825,7 +826,7 @@ k_fft_inv_fwd_pol(float *__restrict__ colT, float *__restrict__ colP, int C2, in
     inverse(RingSeq<const float2, true>{TN, csT}, RingSeq<const float2, true>{TS, csT}, sT);
     inverse(RingSeq<const float2, true>{QN, csP}, RingSeq<const float2, true>{QS, csP}, sQ);
     inverse(RingSeq<const float2, true>{QN + 1, csP}, RingSeq<const float2, true>{QS + 1, csP}, sU);
-    const double lt = lam * tau, l1t = (lam - 1.0) * tau;
+    const double lt = lam * tau * cscale[b].x, l1t = (lam - 1.0) * tau;  // as in k_fft_inv_fwd
     const double *rp = rho + 3L * b * npix;
 #pragma unroll
     for (int u = 0; u < EPT; u++) {
@@ -937,24 +938,25 @@ static size_t split_sub_lds(const Plan &p) {
 
 template <bool FROM_MAP, bool PIX = false>
 static int split_sub(const Plan &p, const double *maps, int nb, const double *rho = nullptr,
-                     double lam = 1.0) {
+                     double lam = 1.0, const double2 *cscale = nullptr) {
     const int cnt = p.fft_class_count[2];
     hipLaunchKernelGGL((k_fft_split_sub<kSplitSubTPB, 8, FROM_MAP, PIX>), dim3(nb, cnt, 4),
                        dim3(kSplitSubTPB), split_sub_lds(p), p.stream, maps, p.d_fftsplit,
                        p.fftsplit_stride, fft_area(p.fftsplit_sublen, kSplitSubTPB), p.d_pfft,
                        p.d_plist + p.fft_class_off[2], p.d_twlo, p.d_twhi, p.fft_ntwhi, p.fftmax,
-                       p.d_chirp, p.d_bhat, p.npix, rho, p.d_M, lam, p.tau, p.mstride, p.d_tau);
+                       p.d_chirp, p.d_bhat, p.npix, rho, p.d_M, lam, p.tau, p.mstride, p.d_tau, cscale);
     MFWF_HIP(hipGetLastError());
     return MFWF_OK;
 }
 
 // forward split transforms of nb maps (PIX: of the messenger field formed from maps, rho and
-// M) into rows of OutT (row stride rs) or, COLS, into the matrix-core columns
+// M) into rows of OutT (row stride rs) or, COLS, into the matrix-core columns, with maps and
+// columns times the column scales
 template <typename OutT, bool PIX, bool COLS>
 static int fwd_split(const Plan &p, const double *maps, const double *rho, double lam, OutT *out,
                      int rs, int nb) {
     MFWF_TRY(split_check(p, nb));
-    MFWF_TRY((split_sub<true, PIX>(p, maps, nb, rho, lam)));
+    MFWF_TRY((split_sub<true, PIX>(p, maps, nb, rho, lam, COLS ? p.d_cscale : nullptr)));
     hipLaunchKernelGGL((k_fft_fwd_split_combine<kSplitTPB, 8, OutT, COLS>),
                        dim3(nb, p.fft_class_count[2]), dim3(kSplitTPB), fft_class_lds(p, 2),
                        p.stream, out, p.d_fftsplit, p.fftsplit_stride, MFWF_FFT_ARGS(2, rs), p.C2);
@@ -1062,15 +1064,14 @@ int ring_join(const Plan &p) {
     return MFWF_OK;
 }
 
-int launch_fft_inv_fwd_cols(const Plan &p, const double *rho, double lam, double *smap, int nb) {
+int launch_fft_inv_fwd_cols(const Plan &p, const double *rho, double lam, int nb) {
     if (p.fft_class_count[2] > 0) {
         // split rings (nside 2048): the synthesis columns folded and transformed back to the
-        // pixels of those rings (into smap, or the plan's map workspace t), then the
-        // messenger field's split transforms into the columns
+        // pixels of those rings (into the plan's map workspace t), then the messenger
+        // field's split transforms into the columns
         float2 *data = reinterpret_cast<float2 *>(p.d_ph32);
-        double *maps = smap ? smap : p.d_t;
-        MFWF_TRY((inv_split<float2, true>(p, data, p.nm32, maps, nb)));
-        MFWF_TRY((fwd_split<float2, true, true>(p, maps, rho, lam, data, p.nm32, nb)));
+        MFWF_TRY((inv_split<float2, true>(p, data, p.nm32, p.d_t, nb)));
+        MFWF_TRY((fwd_split<float2, true, true>(p, p.d_t, rho, lam, data, p.nm32, nb)));
     }
     MFWF_TRY(ring_fork(p));  // class 1 on the side stream, class 0 on the plan's stream
     for (int c = 1; c >= 0; c--) {
@@ -1087,7 +1088,7 @@ int launch_fft_inv_fwd_cols(const Plan &p, const double *rho, double lam, double
         float2 *data = reinterpret_cast<float2 *>(p.d_ph32);
 #define MFWF_INVFWD(T, G)                                                                           \
     hipLaunchKernelGGL((k_fft_inv_fwd<T, 8, G>), grid, dim3(T * G), lds, st, data, p.C2, nb,        \
-                       ngrp, cnt, smap, rho, p.d_M, lam, p.tau, p.mstride, p.d_tau, MFWF_FFT_ARGS(c, rs))
+                       ngrp, cnt, rho, p.d_M, lam, p.tau, p.mstride, p.d_tau, p.d_cscale, MFWF_FFT_ARGS(c, rs))
         if (tpb == 256 && g == 4) MFWF_INVFWD(256, 4);
         else if (tpb == 256 && g == 2) MFWF_INVFWD(256, 2);
         else if (tpb == 256) MFWF_INVFWD(256, 1);
@@ -1126,7 +1127,7 @@ int launch_fft_inv_fwd_pol_cols(const Plan &p, const double *rho, double lam, in
         const size_t lds = fft_cols_lds(p, c, 1);
 #define MFWF_INVFWD_POL(T)                                                                          \
     hipLaunchKernelGGL((k_fft_inv_fwd_pol<T, 8>), grid, dim3(T), lds, st, p.d_ph32, p.d_ph32p,       \
-                       p.C2, nb, cnt, rho, p.d_M, lam, p.tau, MFWF_FFT_ARGS(c, p.nm32))
+                       p.C2, nb, cnt, rho, p.d_M, lam, p.tau, p.d_cscale, MFWF_FFT_ARGS(c, p.nm32))
         if (tpb == 256) MFWF_INVFWD_POL(256);
         else MFWF_INVFWD_POL(512);
 #undef MFWF_INVFWD_POL

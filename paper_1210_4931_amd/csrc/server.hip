@@ -166,6 +166,7 @@ struct HipBackend {
         MFWF_TRY(launch_fill(p.d_tau + b, 1, q.tau, p.stream));
         MFWF_TRY(launch_rho_from_data(q.r.data, p.d_M + off, p.d_rho + off, p.npix, 1, p.stream));
         MFWF_TRY(launch_fill(p.d_smap + off, p.npix, 0.0, p.stream));
+        if (p.dtype == MFWF_F32) MFWF_TRY(launch_col_scale_rho(p, p.d_rho + off, q.tau, b, 1));
         if (p.chain) MFWF_TRY(launch_zero_map_cols(p, b));  // the slot's synthesis columns: s = 0
         return MFWF_OK;
     }
