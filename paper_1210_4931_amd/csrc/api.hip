@@ -285,7 +285,8 @@ static int device_name(std::string &name) {
 //   synth, ana  FP64 Legendre kernels: ring pairs per lane 1/2/4, rows of m per wave 1/2,
 //               coefficients per scalar load block 4/8 (9 synthesis, 6 analysis variants)
 //   g0, g1      maps per workgroup of the batched form's ring step, short-transform class
-//               and longest-transform class (1, 2 or 4; as LDS and 1024 threads allow)
+//               and longest-transform class, or both where one launch takes them (1, 2 or
+//               4; as LDS and 1024 threads allow)
 //   cta, cts    column tile of the analysis / synthesis GEMMs: 1: 64 columns, 2: 128, 3
 //               (analysis only): 32
 //   lamgen      temperature GEMMs: lambda read from the FP32 table (0) or generated from the
@@ -469,6 +470,8 @@ static int autotune(Plan &p, const std::string &devname) {
         // on zeroed work arrays: the batched kernels' work does not depend on the values
         if (p.spin == 0) {
             for (int c = 1; c >= 0; c--) {
+                // one launch for both classes takes class 1's shape
+                if (p.fft_class_count[c] == 0 || (c == 0 && ring_merged(p, kRingCols, B))) continue;
                 std::vector<int> gv;
                 for (int g = 1; g <= fft_cols_group_max(p, c, B); g *= 2) gv.push_back(g);
                 if (gv.size() > 1)
@@ -799,22 +802,16 @@ static int create(int nside, int lmax, int spin, int dtype, int max_batch, void 
         const double a = -2.0 * M_PI * (double)(64L * h) / fftmax;
         twhi[h] = make_double2(std::cos(a), std::sin(a));
     }
-    // FFT classes: pairs whose transform fits half of the largest length, the rest, and the
-    // split rings (whose combined spectrum of n <= fftmax points passes through LDS).  Up to
-    // 2048 points (nside 256) both halves run 256 threads a workgroup, and one launch for all
-    // rings takes less than two, one after the other or on two streams, although the short
-    // rings then get the long ones' LDS: forward FP64 transforms at nside 256 24 -> 14 us (1
-    // map), 67 -> 59 (8), 133 -> 130 (16); FP32 ring step 51 -> 31 us (1 map), 723 -> 714 (64);
-    // nside 32, FP64, an iteration 47 -> 35 us.  Above, the long rings' workgroups of 512 or
-    // 1024 threads and 74 KB or more would leave the short ones a fraction of the CU.
-    const int short_max = fftmax <= 2048 ? fftmax : fftmax / 2;
+    // FFT classes: pairs whose transform fits half of the largest length (0), the rest (1), and the
+    // split rings (2; their combined spectrum of n <= fftmax points passes through LDS).  Class 1
+    // comes first in the list and class 0 follows it, so that one launch can take both.
     std::vector<int> plist;
     p.fft_class_len[0] = 1;
     int nsplit_max = 0;
-    for (int c = 0; c < 3; c++) {
+    for (int c : {1, 0, 2}) {
         p.fft_class_off[c] = (int)plist.size();
         for (int q = 0; q < p.npair; q++) {
-            const int cls = pf[q].bluestein == 2 ? 2 : (pf[q].fftlen <= short_max ? 0 : 1);
+            const int cls = pf[q].bluestein == 2 ? 2 : (2 * pf[q].fftlen <= fftmax ? 0 : 1);
             if (cls != c) continue;
             plist.push_back(q);
             if (c == 0) p.fft_class_len[0] = std::max(p.fft_class_len[0], pf[q].fftlen);
@@ -873,7 +870,8 @@ static int create(int nside, int lmax, int spin, int dtype, int max_batch, void 
     MFWF_TRY(dalloc(&p.d_twhi, twhi.size(), "twiddles hi"));
     MFWF_TRY(dalloc(&p.d_chirp, std::max<size_t>(1, chirp.size()), "chirp"));
     MFWF_TRY(dalloc(&p.d_bhat, std::max<size_t>(1, bhat.size()), "chirp kernel"));
-    if (f32 && p.fft_class_count[0] > 0 && p.fft_class_count[1] > 0) {
+    if (f32 && p.fft_class_count[0] > 0 && p.fft_class_count[1] > 0 &&
+        !ring_merged(p, spin == 2 ? kRingPolCols : kRingCols, max_batch)) {
         // the two in-LDS ring classes of the chained ring step run side by side (default
         // priority, non-blocking: it orders only against the fork and join events)
         MFWF_HIP(hipStreamCreateWithFlags(&p.side, hipStreamNonBlocking));

@@ -81,7 +81,7 @@ struct Plan {
     double2 *d_bhat = nullptr;   // Bluestein kernels FFT_M(conj chirp) / M, natural order
     int fftmax;                  // largest power-of-two transform length
     int *d_plist = nullptr;      // [npair] pair indices grouped by FFT class
-    // classes: 0 short transforms (up to 2048 points: all), 1 the longest in-LDS ones, 2 split rings
+    // classes: 0 short transforms, 1 the longest in-LDS ones (first in the list), 2 split rings
     int fft_class_off[3] = {0, 0, 0}, fft_class_count[3] = {0, 0, 0}, fft_class_len[3] = {1, 1, 1};
     // FP32 ring step: the longest ring class runs on a side stream forked from `stream` (and
     // joined back) while the short class runs on `stream`; the classes touch disjoint rings
@@ -204,10 +204,11 @@ int launch_fft_inv(const Plan &p, const double2 *phase, double *maps, int nb);
 int launch_fft_fwd_f32(const Plan &p, const double *maps, const double *rho, double lam,
                        float2 *phase, int nb);
 int launch_fft_inv_f32(const Plan &p, const float2 *phase, double *maps, int nb);
-// Fork the plan's side stream from its stream before the two in-LDS ring classes of the
-// chained FP32 ring step, and join it back after them (no-ops without a side stream).
-int ring_fork(const Plan &p);
-int ring_join(const Plan &p);
+// Ring transforms whose two in-LDS classes (up to half the largest length, and above) go in one
+// launch rather than two
+// (forward of maps, with the pixel update, inverse, chained step of T, of T, Q, U)
+enum RingStep { kRingFwd, kRingFwdPix, kRingInv, kRingCols, kRingPolCols };
+bool ring_merged(const Plan &p, RingStep step, int rows);
 // synthesis columns d_ph32 -> maps s -> t of Eq. (3) -> the columns of its forward transform, in
 // place (one iteration's ring steps without the map in memory)
 int launch_fft_inv_fwd_cols(const Plan &p, const double *rho, double lam, int nb);

@@ -24,10 +24,10 @@
 // can apply the messenger pixel update (Eq. 3) to its input as it reads it.
 // Grid (map, pair): the workgroups of one ring pair run back to back, so the pair's chirp
 // tables and noise precision are fetched into L2 once for all maps.
-// Pairs are launched in classes by transform length: up to 2048 points one launch takes all;
-// above, most pairs need at most half the largest length (less LDS and fewer registers per
-// thread, more workgroups per CU); the long Bluestein transforms of the largest polar rings
-// form the second class; polar rings whose chirp-z transform would outgrow LDS (nside 2048)
+// Pairs are launched in classes by transform length: most pairs need at most half the
+// largest length (less LDS and fewer registers per thread, more workgroups per CU); the long
+// Bluestein transforms of the largest polar rings form the second class (the two go in one
+// launch where that is faster, ring_merged); polar rings whose chirp-z transform would outgrow LDS (nside 2048)
 // form a third, split into four shorter transforms (below).
 #include <mutex>
 #include <type_traits>
@@ -979,15 +979,47 @@ static int inv_split(const Plan &p, const InT *in, int rs, double *maps, int nb)
     return MFWF_OK;
 }
 
+// The launches of the two in-LDS classes, long transforms first; merged, one launch walks the
+// lists of both with class 1's shape.
+struct RingLaunch {
+    int c, cnt;
+};
+static int ring_launches(const Plan &p, bool merged, RingLaunch (&out)[2]) {
+    int n = 0;
+    if (merged && p.fft_class_count[0] > 0 && p.fft_class_count[1] > 0) {
+        out[n++] = RingLaunch{1, p.fft_class_count[0] + p.fft_class_count[1]};
+    } else {
+        for (int c = 1; c >= 0; c--)
+            if (p.fft_class_count[c] > 0) out[n++] = RingLaunch{c, p.fft_class_count[c]};
+    }
+    return n;
+}
+
+// Up to 2048 points (nside 256) both classes run 256 threads a workgroup, and one launch saves
+// the latency of a second one (7-9 us), but gives the short rings the long ones' LDS.  Where
+// that costs more, measured apart / merged, us: forward transforms of 2048 points over 24 rows
+// 360.7 / 359.0, 32 407.2 / 408.0, 64 708.6 / 718.5, 192 2464 / 2507 (calls of sht_fwd, nside 256);
+// the chained T, Q, U step, whose registers allow two waves a SIMD, an iteration with 8 maps
+// 962.6 / 959.9, 16 1522 / 1543, 32 2787 / 2854, 64 5356 / 5452.  Everything else gains at every
+// size measured: inverse transforms of 1 row 18.9 / 10.8, 32 177.7 / 167.9; with the pixel update
+// 23.4 / 13.1, 243.4 / 232.2; the chained T step of 1 map 49.7 / 29.7, 64 702 / 677; 1024 points,
+// 192 rows forward 716 / 706.  Above 2048 points the long rings' workgroups of 512 or 1024 threads and
+// 74 KB or more would leave the short ones a fraction of the CU.
+bool ring_merged(const Plan &p, RingStep step, int rows) {
+    if (p.fft_class_len[1] > 2048) return false;
+    if (p.fft_class_len[1] <= 1024) return true;
+    return step == kRingFwd ? rows <= 24 : (step == kRingPolCols ? rows <= 8 : true);
+}
+
 template <typename OutT, bool PIX>
 static int fwd_classes(const Plan &p, const double *maps, const double *rho, double lam,
                        OutT *out, int nb) {
     if (p.fft_class_count[2] > 0)
         MFWF_TRY((fwd_split<OutT, PIX, false>(p, maps, rho, lam, out,
                                               sizeof(OutT) == sizeof(float2) ? p.nm32 : p.nm, nb)));
-    for (int c = 1; c >= 0; c--) {  // long transforms first
-        const int cnt = p.fft_class_count[c];
-        if (cnt == 0) continue;
+    RingLaunch L[2];
+    for (int k = 0, nl = ring_launches(p, ring_merged(p, PIX ? kRingFwdPix : kRingFwd, nb), L); k < nl; k++) {
+        const int c = L[k].c, cnt = L[k].cnt;
         int ept;
         const int tpb = fft_class_shape(p, c, ept);
         const dim3 grid(nb, cnt);  // maps of one pair adjacent: its tables and M stay in L2
@@ -1008,9 +1040,9 @@ template <typename InT>
 static int inv_classes(const Plan &p, const InT *in, double *maps, int nb) {
     if (p.fft_class_count[2] > 0)
         MFWF_TRY((inv_split<InT, false>(p, in, sizeof(InT) == sizeof(float2) ? p.nm32 : p.nm, maps, nb)));
-    for (int c = 1; c >= 0; c--) {
-        const int cnt = p.fft_class_count[c];
-        if (cnt == 0) continue;
+    RingLaunch L[2];
+    for (int k = 0, nl = ring_launches(p, ring_merged(p, kRingInv, nb), L); k < nl; k++) {
+        const int c = L[k].c, cnt = L[k].cnt;
         int ept;
         const int tpb = fft_class_shape(p, c, ept);
         const dim3 grid(nb, cnt);  // maps of one pair adjacent: its tables and M stay in L2
@@ -1050,15 +1082,13 @@ int launch_fft_inv_f32(const Plan &p, const float2 *phase, double *maps, int nb)
     return inv_classes<float2>(p, phase, maps, nb);
 }
 
-int ring_fork(const Plan &p) {
-    if (!p.side) return MFWF_OK;
+static int ring_fork(const Plan &p) {
     MFWF_HIP(hipEventRecord(p.side_fork, p.stream));
     MFWF_HIP(hipStreamWaitEvent(p.side, p.side_fork, 0));
     return MFWF_OK;
 }
 
-int ring_join(const Plan &p) {
-    if (!p.side) return MFWF_OK;
+static int ring_join(const Plan &p) {
     MFWF_HIP(hipEventRecord(p.side_join, p.side));
     MFWF_HIP(hipStreamWaitEvent(p.stream, p.side_join, 0));
     return MFWF_OK;
@@ -1073,11 +1103,12 @@ int launch_fft_inv_fwd_cols(const Plan &p, const double *rho, double lam, int nb
         MFWF_TRY((inv_split<float2, true>(p, data, p.nm32, p.d_t, nb)));
         MFWF_TRY((fwd_split<float2, true, true>(p, p.d_t, rho, lam, data, p.nm32, nb)));
     }
-    MFWF_TRY(ring_fork(p));  // class 1 on the side stream, class 0 on the plan's stream
-    for (int c = 1; c >= 0; c--) {
-        const int cnt = p.fft_class_count[c];
-        if (cnt == 0) continue;
-        const hipStream_t st = (c == 1 && p.side) ? p.side : p.stream;
+    RingLaunch L[2];
+    const int nl = ring_launches(p, ring_merged(p, kRingCols, nb), L);
+    if (nl == 2) MFWF_TRY(ring_fork(p));  // class 1 on the side stream, class 0 on the plan's stream
+    for (int k = 0; k < nl; k++) {
+        const int c = L[k].c, cnt = L[k].cnt;
+        const hipStream_t st = (nl == 2 && c == 1) ? p.side : p.stream;
         int ept;
         const int tpb = fft_class_shape(p, c, ept);
         const int g = fft_cols_group(p, c, nb);
@@ -1098,7 +1129,7 @@ int launch_fft_inv_fwd_cols(const Plan &p, const double *rho, double lam, int nb
 #undef MFWF_INVFWD
         MFWF_HIP(hipGetLastError());
     }
-    return ring_join(p);
+    return nl == 2 ? ring_join(p) : MFWF_OK;
 }
 
 
@@ -1116,11 +1147,12 @@ bool fft_pol_chain_ok(const Plan &p) {
 
 int launch_fft_inv_fwd_pol_cols(const Plan &p, const double *rho, double lam, int nb) {
     if (!fft_pol_chain_ok(p)) return fail(MFWF_EINVAL, "chained T, Q, U ring step: ring class too long");
-    MFWF_TRY(ring_fork(p));  // class 1 on the side stream, class 0 on the plan's stream
-    for (int c = 1; c >= 0; c--) {
-        const int cnt = p.fft_class_count[c];
-        if (cnt == 0) continue;
-        const hipStream_t st = (c == 1 && p.side) ? p.side : p.stream;
+    RingLaunch L[2];
+    const int nl = ring_launches(p, ring_merged(p, kRingPolCols, nb), L);
+    if (nl == 2) MFWF_TRY(ring_fork(p));  // class 1 on the side stream, class 0 on the plan's stream
+    for (int k = 0; k < nl; k++) {
+        const int c = L[k].c, cnt = L[k].cnt;
+        const hipStream_t st = (nl == 2 && c == 1) ? p.side : p.stream;
         int ept;
         const int tpb = fft_class_shape(p, c, ept);
         const dim3 grid(8 * nb * ((cnt + 7) / 8));  // whole pairs per XCD
@@ -1133,7 +1165,7 @@ int launch_fft_inv_fwd_pol_cols(const Plan &p, const double *rho, double lam, in
 #undef MFWF_INVFWD_POL
         MFWF_HIP(hipGetLastError());
     }
-    return ring_join(p);
+    return nl == 2 ? ring_join(p) : MFWF_OK;
 }
 
 int fft_max_length() { return 8 * 1024; }
