@@ -622,7 +622,7 @@ static int setup_batched(Plan &p, const std::vector<int> &lstart, const std::vec
     MFWF_TRY(dalloc(&p.d_phf, (size_t)p.ncomp * p.max_batch * p.nring * p.nm32, "ring Fourier rows FP32"));
     MFWF_TRY(dalloc(&p.d_ph32, (size_t)p.nring * p.nm * p.C2, "ring Fourier FP32"));
     MFWF_TRY(dalloc(&p.d_cscale, (size_t)(p.spin == 2 ? 2 : 1) * p.Bp, "column scales"));
-    MFWF_TRY(launch_fill(reinterpret_cast<double *>(p.d_cscale), (p.spin == 2 ? 4L : 2L) * p.Bp, 1.0, p.stream));
+    MFWF_TRY(launch_unit_scale(p));
     MFWF_TRY(dalloc(&p.d_zrow, (size_t)2 * p.C2, "zero row"));
     MFWF_HIP(hipMemsetAsync(p.d_zrow, 0, sizeof(float) * 2 * p.C2, p.stream));
     MFWF_TRY(dalloc(&p.d_a32, (size_t)p.nalm * p.C2, "analysis FP32"));

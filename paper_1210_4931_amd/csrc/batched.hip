@@ -150,16 +150,21 @@ struct LamGen {
 // value per thread, spread over the whole map, which ends the search on any map that is not
 // small or nearly empty (a transform's call then takes 5 us longer: the launch and two memory
 // latencies), then through the map in order.
-// scale[b] = (S, 1/S); grid.y = 2: a group of n0 and one of n1 values per map (T; Q and U, or
+// grid.y = 2: a group of n0 and one of n1 values per map (T; Q and U, or
 // E and B), the second to scale[Bp + b]; both: one group, to both.  cl: the values are
 // C^-1/2 x (mode 2 of k_alm_to_cols).
 // ---------------------------------------------------------------------------------------
 static constexpr double kSmallMap = 0x1p-70, kSmallScale = 0x1p40;
+static constexpr ColScale kUnitScale{1.0, 1.0, 1.f, 1.f};
 
-__global__ void __launch_bounds__(1024)
+__global__ void __launch_bounds__(256) k_unit_scale(ColScale *__restrict__ scale, int n) {
+    for (int i = threadIdx.x; i < n; i += 256) scale[i] = kUnitScale;
+}
+
+__global__ void __launch_bounds__(256)
 k_col_scale(const double *__restrict__ x, long stride, long n0, long n1, double factor,
             const double *__restrict__ cl, const int *__restrict__ lofi, int both, int Bp,
-            double2 *__restrict__ scale) {
+            ColScale *__restrict__ scale) {
     const int b = blockIdx.x, g = blockIdx.y;
     const double *v = x + b * stride + (g ? n0 : 0);
     const long n = g ? n1 : n0;
@@ -171,15 +176,15 @@ k_col_scale(const double *__restrict__ x, long stride, long n0, long n1, double 
         }
         return !(fabs(f * v[i]) < kSmallMap);
     };
-    bool big = __syncthreads_or(reaches(threadIdx.x * (n - 1) / 1023));
-    for (long k = 0; k < n && !big; k += 8 * 1024) {  // big is the same for every thread
+    bool big = __syncthreads_or(reaches(min(threadIdx.x * max(n >> 8, 1L), n - 1)));
+    for (long k = 0; k < n && !big; k += 32 * 256) {  // big is the same for every thread
         bool any = false;
 #pragma unroll
-        for (int u = 0; u < 8; u++) any |= reaches(min(k + 1024 * u + threadIdx.x, n - 1));
+        for (int u = 0; u < 32; u++) any |= reaches(min(k + 256 * u + threadIdx.x, n - 1));
         big = __syncthreads_or(any);
     }
     if (threadIdx.x != 0) return;
-    const double2 s = big ? make_double2(1.0, 1.0) : make_double2(kSmallScale, 1.0 / kSmallScale);
+    const ColScale s = big ? kUnitScale : ColScale{kSmallScale, 1.0 / kSmallScale, (float)kSmallScale, (float)(1.0 / kSmallScale)};
     scale[g * Bp + b] = s;
     if (both) scale[Bp + b] = s;
 }
@@ -194,9 +199,13 @@ k_col_scale(const double *__restrict__ x, long stride, long n0, long n1, double 
 // ---------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256)
 k_rows_to_cols(const float2 *__restrict__ phf, float *__restrict__ ph32, int nring, int nm,
-               int rs, int nb, int Bp, int C2, const double2 *__restrict__ scale) {
+               int rs, int nb, int Bp, int C2, const ColScale *__restrict__ scale) {
     __shared__ float2 tile[64][64 + 1];  // [map][m]
     const int ring = blockIdx.x, m0 = 64 * blockIdx.y, b0 = 64 * blockIdx.z;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // maps b0 + w + 4 u
+    float sc[16];
+#pragma unroll
+    for (int u = 0; u < 16; u++) sc[u] = scale[min(b0 + w + 4 * u, nb - 1)].s32;
     float2 v[16];
 #pragma unroll
     for (int u = 0; u < 16; u++) {
@@ -207,17 +216,14 @@ k_rows_to_cols(const float2 *__restrict__ phf, float *__restrict__ ph32, int nri
 #pragma unroll
     for (int u = 0; u < 16; u++) {
         const int e = threadIdx.x + 256 * u;
-        tile[e >> 6][e & 63] = v[u];
+        tile[e >> 6][e & 63] = make_float2(sc[u] * v[u].x, sc[u] * v[u].y);
     }
-    const float sc = (float)scale[min(b0 + ((int)threadIdx.x & 63), nb - 1)].x;
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < 16; u++) {
         const int e = threadIdx.x + 256 * u, mm = e >> 6, bb = e & 63, b = b0 + bb, m = m0 + mm;
-        const float2 x = tile[bb][mm];
         if (b < Bp && m < nm)
-            *reinterpret_cast<float2 *>(ph32 + ((long)m * nring + ring) * C2 + 2 * b) =
-                make_float2(sc * x.x, sc * x.y);
+            *reinterpret_cast<float2 *>(ph32 + ((long)m * nring + ring) * C2 + 2 * b) = tile[bb][mm];
     }
 }
 
@@ -231,17 +237,20 @@ k_zero_map_cols(float *__restrict__ ph32, long nrows, int C2, int b) {
 
 __global__ void __launch_bounds__(256)
 k_cols_to_rows(const float *__restrict__ ph32, float2 *__restrict__ phf, int nring, int nm,
-               int rs, int nb, int C2, const double2 *__restrict__ scale) {
+               int rs, int nb, int C2, const ColScale *__restrict__ scale) {
     __shared__ float2 tile[64][64 + 1];  // [m][map]
     const int ring = blockIdx.x, m0 = 64 * blockIdx.y, b0 = 64 * blockIdx.z;
-    const float sc = (float)scale[min(b0 + ((int)threadIdx.x & 63), nb - 1)].y;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // maps b0 + w + 4 u
+    float sc[16];
+#pragma unroll
+    for (int u = 0; u < 16; u++) sc[u] = scale[min(b0 + w + 4 * u, nb - 1)].inv32;
     float2 v[16];
 #pragma unroll
     for (int u = 0; u < 16; u++) {
         const int e = threadIdx.x + 256 * u, mm = e >> 6, bb = e & 63, b = b0 + bb, m = m0 + mm;
         const float2 x = *reinterpret_cast<const float2 *>(
             ph32 + ((long)min(m, nm - 1) * nring + ring) * C2 + 2 * min(b, nb - 1));
-        v[u] = (b < nb && m < nm) ? make_float2(sc * x.x, sc * x.y) : make_float2(0.f, 0.f);
+        v[u] = (b < nb && m < nm) ? x : make_float2(0.f, 0.f);
     }
 #pragma unroll
     for (int u = 0; u < 16; u++) {
@@ -252,7 +261,9 @@ k_cols_to_rows(const float *__restrict__ ph32, float2 *__restrict__ phf, int nri
 #pragma unroll
     for (int u = 0; u < 16; u++) {
         const int e = threadIdx.x + 256 * u, bb = e >> 6, mm = e & 63, b = b0 + bb, m = m0 + mm;
-        if (b < nb && m < nm) phf[((long)b * nring + ring) * rs + m] = tile[mm][bb];
+        const float2 x = tile[mm][bb];
+        if (b < nb && m < nm)
+            phf[((long)b * nring + ring) * rs + m] = make_float2(sc[u] * x.x, sc[u] * x.y);
     }
 }
 
@@ -1037,7 +1048,7 @@ k_gemm_synthesis(const float *__restrict__ lam, LamGen gen, const long *__restri
 __global__ void __launch_bounds__(256)
 k_alm_to_cols(const double2 *__restrict__ alm, float *__restrict__ x32,
               const double *__restrict__ cl, const int *__restrict__ lofi, long nalm, int nb,
-              int C2, int mode, const double2 *__restrict__ scale) {
+              int C2, int mode, const ColScale *__restrict__ scale) {
     __shared__ float tile[64][65];  // [alm within tile][col within tile]
     const long i0 = (long)blockIdx.x * 64;
     const int c0 = blockIdx.y * 64;  // columns c0 .. c0+63 = maps c0/2 .. c0/2+31
@@ -1052,7 +1063,7 @@ k_alm_to_cols(const double2 *__restrict__ alm, float *__restrict__ x32,
 #pragma unroll
     for (int u = 0; u < 8; u++) {  // clamped, so that all loads are in flight together
         const int b = min(c0 / 2 + w + 4 * u, nb - 1);
-        const double fs = f * scale[b].x;
+        const double fs = f * scale[b].s;
         const double2 x = alm[(long)b * nalm + ic];
         v[u] = make_double2(fs * x.x, fs * x.y);
     }
@@ -1074,7 +1085,7 @@ k_alm_to_cols(const double2 *__restrict__ alm, float *__restrict__ x32,
 // x32 [nalm][C2] FP32 -> alm FP64 [nb][nalm], times f (mode 1: Omega; mode 3: 1)
 __global__ void __launch_bounds__(256)
 k_cols_to_alm(const float *__restrict__ x32, double2 *__restrict__ alm, long nalm, int nb, int C2,
-              double scale, const double2 *__restrict__ cscale) {
+              double scale, const ColScale *__restrict__ cscale) {
     __shared__ float tile[64][65];
     const long i0 = (long)blockIdx.x * 64;
     const int c0 = blockIdx.y * 64;
@@ -1086,7 +1097,7 @@ k_cols_to_alm(const float *__restrict__ x32, double2 *__restrict__ alm, long nal
     const int ii = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     double f[8];
 #pragma unroll
-    for (int u = 0; u < 8; u++) f[u] = scale * cscale[min(c0 / 2 + w + 4 * u, nb - 1)].y;
+    for (int u = 0; u < 8; u++) f[u] = scale * cscale[min(c0 / 2 + w + 4 * u, nb - 1)].inv;
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < 8; u++) {
@@ -1116,9 +1127,15 @@ int launch_lam_ckpt(const Plan &p) {
 }
 
 static int col_scale(const Plan &p, const double *x, long stride, long n0, long n1, double factor,
-                     const double *cl, int both, int nb, double2 *scale) {
-    hipLaunchKernelGGL(k_col_scale, dim3(nb, n1 > 0 ? 2 : 1), dim3(1024), 0, p.stream, x, stride, n0,
+                     const double *cl, int both, int nb, ColScale *scale) {
+    hipLaunchKernelGGL(k_col_scale, dim3(nb, n1 > 0 ? 2 : 1), dim3(256), 0, p.stream, x, stride, n0,
                        n1, factor, cl, p.d_lofi, both, p.Bp, scale);
+    MFWF_HIP(hipGetLastError());
+    return MFWF_OK;
+}
+
+int launch_unit_scale(const Plan &p) {
+    hipLaunchKernelGGL(k_unit_scale, dim3(1), dim3(256), 0, p.stream, p.d_cscale, p.spin == 2 ? 2 * p.Bp : p.Bp);
     MFWF_HIP(hipGetLastError());
     return MFWF_OK;
 }

@@ -46,6 +46,12 @@ struct PairFFT {
 // Legendre work split: the wave of lanes handling ring pairs [g * 64 * P, (g+1) * 64 * P)
 // for one m.  Seeds: for every (m, pair) the first l with |lambda_lm| >= 2^-100 and the
 // two values (lambda_{l_s - 1, m}, lambda_{l_s, m}); l_s = lmax + 1 if never reached.
+// the power of two that a map's FP32 columns carry, and its inverse (batched.hip, k_col_scale)
+struct ColScale {
+    double s, inv;
+    float s32, inv32;
+};
+
 struct Plan {
     int nside, lmax, spin, dtype, max_batch;
     int device = 0;  // HIP device current when the plan was created
@@ -146,8 +152,7 @@ struct Plan {
     bool chain = false;
     bool chain_ready = false;    // d_ph32 holds the synthesis of the iterate in d_smap
     float *d_ph32 = nullptr;     // [nm][nring][C2] ring-Fourier, maps innermost
-    double2 *d_cscale = nullptr; // [Bp], spin 2 [2][Bp] (T; Q, U and E, B): the power of two S that a
-                                 // map's columns carry, and 1/S
+    ColScale *d_cscale = nullptr; // [Bp], spin 2 [2][Bp] (T; Q, U and E, B)
     float *d_zrow = nullptr;     // [2 C2] zeros: the equator pair's south ring
     float *d_a32 = nullptr;      // [nalm][C2] analysis output
     float *d_s32 = nullptr;      // [nalm][C2] synthesis input
@@ -236,6 +241,7 @@ int launch_lam_table(const Plan &p);
 int launch_lam_ckpt(const Plan &p);  // d_lck from the recurrence
 // d_cscale for the maps or coefficients x that a transform reads (n doubles per component; mode
 // kHarmInvSqrtC: C^-1/2 x), or for the sources rho of maps b0 .. b0 + nb - 1 of a solve
+int launch_unit_scale(const Plan &p);  // d_cscale = 1
 int launch_col_scale(const Plan &p, const double *x, long n, int mode, int nb);
 int launch_col_scale_rho(const Plan &p, const double *rho, double tau, int b0, int nb);
 int launch_rows_to_cols(const Plan &p, int nb);  // d_phf -> d_ph32

@@ -83,9 +83,17 @@ k_pol_tables(const double *__restrict__ Atab, const double *__restrict__ ctab,
 __global__ void __launch_bounds__(256)
 k_rows_to_cols_pol(const float2 *__restrict__ phf, float *__restrict__ colT,
                    float *__restrict__ colP, int nring, int nm, int rs, int nb, int Bp,
-                   const double2 *__restrict__ scale) {
+                   const ColScale *__restrict__ scale) {
     __shared__ float2 tile[3][32][64 + 1];  // [component][map][m]
     const int ring = blockIdx.x, m0 = 64 * blockIdx.y, b0 = 32 * blockIdx.z;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // maps b0 + w + 4 (u mod 8)
+    float sc[2][8];  // column scales (k_col_scale) of T; of Q, U
+#pragma unroll
+    for (int u = 0; u < 8; u++) {
+        const int b = min(b0 + w + 4 * u, nb - 1);
+        sc[0][u] = scale[b].s32;
+        sc[1][u] = scale[Bp + b].s32;
+    }
     float2 v[24];
 #pragma unroll
     for (int u = 0; u < 24; u++) {
@@ -97,10 +105,9 @@ k_rows_to_cols_pol(const float2 *__restrict__ phf, float *__restrict__ colT,
 #pragma unroll
     for (int u = 0; u < 24; u++) {
         const int e = threadIdx.x + 256 * u;
-        tile[e >> 11][(e >> 6) & 31][e & 63] = v[u];
+        const float f = sc[u >= 8][u & 7];
+        tile[e >> 11][(e >> 6) & 31][e & 63] = make_float2(f * v[u].x, f * v[u].y);
     }
-    const int bs = min(b0 + ((int)threadIdx.x & 31), nb - 1);
-    const float scT = (float)scale[bs].x, scP = (float)scale[Bp + bs].x;  // column scales (k_col_scale)
     __syncthreads();
     const long C2 = 2L * Bp;
 #pragma unroll
@@ -109,9 +116,8 @@ k_rows_to_cols_pol(const float2 *__restrict__ phf, float *__restrict__ colT,
         if (b >= Bp || m >= nm) continue;
         const long row = (long)m * nring + ring;
         const float2 t = tile[0][bb][mm], q = tile[1][bb][mm], u2 = tile[2][bb][mm];
-        *reinterpret_cast<float2 *>(colT + row * C2 + 2 * b) = make_float2(scT * t.x, scT * t.y);
-        *reinterpret_cast<float4 *>(colP + row * 2 * C2 + 4 * b) =
-            make_float4(scP * q.x, scP * q.y, scP * u2.x, scP * u2.y);
+        *reinterpret_cast<float2 *>(colT + row * C2 + 2 * b) = t;
+        *reinterpret_cast<float4 *>(colP + row * 2 * C2 + 4 * b) = make_float4(q.x, q.y, u2.x, u2.y);
     }
 }
 
@@ -120,12 +126,18 @@ k_rows_to_cols_pol(const float2 *__restrict__ phf, float *__restrict__ colT,
 __global__ void __launch_bounds__(256)
 k_cols_to_rows_pol(const float *__restrict__ colT, const float *__restrict__ colQU,
                    float2 *__restrict__ phf, int nring, int nm, int rs, int nb, int Bp,
-                   const double2 *__restrict__ scale) {
+                   const ColScale *__restrict__ scale) {
     __shared__ float2 tile[3][64][32 + 1];  // [component][m][map]
     const int ring = blockIdx.x, m0 = 64 * blockIdx.y, b0 = 32 * blockIdx.z;
-    const int bs = min(b0 + ((int)threadIdx.x & 31), nb - 1);
-    const float scT = (float)scale[bs].y, scP = (float)scale[Bp + bs].y;
     const long C2 = 2L * Bp;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // maps b0 + w + 4 (u mod 8)
+    float sc[2][8];  // column scales (k_col_scale) of T; of Q, U
+#pragma unroll
+    for (int u = 0; u < 8; u++) {
+        const int b = min(b0 + w + 4 * u, nb - 1);
+        sc[0][u] = scale[b].inv32;
+        sc[1][u] = scale[Bp + b].inv32;
+    }
     float2 vt[8];
     float4 vq[8];
 #pragma unroll
@@ -141,16 +153,18 @@ k_cols_to_rows_pol(const float *__restrict__ colT, const float *__restrict__ col
         const int e = threadIdx.x + 256 * u, mm = e >> 5, bb = e & 31;
         const bool on = b0 + bb < nb && m0 + mm < nm;
         const float2 z = make_float2(0.f, 0.f);
-        tile[0][mm][bb] = on ? make_float2(scT * vt[u].x, scT * vt[u].y) : z;
-        tile[1][mm][bb] = on ? make_float2(scP * vq[u].x, scP * vq[u].y) : z;  // Q
-        tile[2][mm][bb] = on ? make_float2(scP * vq[u].z, scP * vq[u].w) : z;  // U
+        tile[0][mm][bb] = on ? vt[u] : z;
+        tile[1][mm][bb] = on ? make_float2(vq[u].x, vq[u].y) : z;  // Q
+        tile[2][mm][bb] = on ? make_float2(vq[u].z, vq[u].w) : z;  // U
     }
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < 24; u++) {
         const int e = threadIdx.x + 256 * u;
         const int c = e >> 11, bb = (e >> 6) & 31, mm = e & 63, b = b0 + bb, m = m0 + mm;
-        if (b < nb && m < nm) phf[((3L * b + c) * nring + ring) * rs + m] = tile[c][mm][bb];
+        const float f = sc[u >= 8][u & 7];
+        const float2 x = tile[c][mm][bb];
+        if (b < nb && m < nm) phf[((3L * b + c) * nring + ring) * rs + m] = make_float2(f * x.x, f * x.y);
     }
 }
 
@@ -205,7 +219,7 @@ k_pol_combine(const float *__restrict__ aT, const float *__restrict__ aP,
 __global__ void __launch_bounds__(256)
 k_alm_to_cols_pol(const double2 *__restrict__ alm, float *__restrict__ colT,
                   float *__restrict__ colEB, long nalm, int nb, int Bp,
-                  const double2 *__restrict__ scale) {
+                  const ColScale *__restrict__ scale) {
     __shared__ float2 tile[3][64][32 + 1];  // [component][coefficient][map]
     const long i0 = (long)blockIdx.x * 64;
     const int b0 = 32 * blockIdx.y;
@@ -217,7 +231,7 @@ k_alm_to_cols_pol(const double2 *__restrict__ alm, float *__restrict__ colT,
 #pragma unroll
         for (int u = 0; u < 8; u++) {  // clamped, so that all loads are in flight together
             const int b = min(b0 + w + 4 * u, nb - 1);
-            const double f = scale[c ? Bp + b : b].x;
+            const double f = scale[c ? Bp + b : b].s;
             const double2 x = alm[(3L * b + c) * nalm + ic];
             v[u] = make_double2(f * x.x, f * x.y);
         }
@@ -243,7 +257,7 @@ k_alm_to_cols_pol(const double2 *__restrict__ alm, float *__restrict__ colT,
 __global__ void __launch_bounds__(256)
 k_cols_to_alm_pol(const float *__restrict__ colT, const float *__restrict__ colEB,
                   double2 *__restrict__ alm, long nalm, int nb, int Bp,
-                  const double2 *__restrict__ scale) {
+                  const ColScale *__restrict__ scale) {
     __shared__ float2 tile[3][64][32 + 1];
     const long i0 = (long)blockIdx.x * 64;
     const int b0 = 32 * blockIdx.y;
@@ -268,8 +282,8 @@ k_cols_to_alm_pol(const float *__restrict__ colT, const float *__restrict__ colE
 #pragma unroll
     for (int u = 0; u < 8; u++) {
         const int b = min(b0 + w + 4 * u, nb - 1);
-        f[0][u] = scale[b].y;
-        f[1][u] = scale[Bp + b].y;
+        f[0][u] = scale[b].inv;
+        f[1][u] = scale[Bp + b].inv;
     }
     __syncthreads();
 #pragma unroll

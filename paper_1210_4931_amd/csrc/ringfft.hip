@@ -401,7 +401,7 @@ k_fft_split_sub(const double *__restrict__ maps, double2 *__restrict__ scratch, 
                 long npix, const double *__restrict__ rho = nullptr,
                 const double *__restrict__ M = nullptr, double lam = 1.0, double tau = 0.0,
                 long mstride = 0, const double *__restrict__ tau_b = nullptr,
-                const double2 *__restrict__ cscale = nullptr) {
+                const ColScale *__restrict__ cscale = nullptr) {
     extern __shared__ double2 buf[];
     const int p = plist[blockIdx.y], b = blockIdx.x, r = blockIdx.z;
     const PairFFT pf = pfft[p];
@@ -416,7 +416,7 @@ k_fft_split_sub(const double *__restrict__ maps, double2 *__restrict__ scratch, 
     const double *sp = maps + (long)b * npix;
     if (PIX && tau_b) tau = tau_b[b];
     // cscale: maps hold s times its column scale (chained iterations), so t is formed scaled
-    const double lt = PIX && cscale ? lam * tau * cscale[b].x : lam * tau, l1t = (lam - 1.0) * tau;
+    const double lt = PIX && cscale ? lam * tau * cscale[b].s : lam * tau, l1t = (lam - 1.0) * tau;
     const double *rp = rho + (long)b * npix;
     const double *mp = M + (long)b * mstride;
     auto pix = [&](long q) {
@@ -713,7 +713,7 @@ __global__ void __launch_bounds__(TPB * G)
 k_fft_inv_fwd(float2 *__restrict__ data, int C2, int nmap, int ngrp, int npl,
               const double *__restrict__ rho, const double *__restrict__ M, double lam,
               double tau, long mstride, const double *__restrict__ tau_b,
-              const double2 *__restrict__ cscale,
+              const ColScale *__restrict__ cscale,
               const PairFFT *__restrict__ pfft, const int *__restrict__ plist,
               const double2 *__restrict__ twlo, const double2 *__restrict__ twhi, int ntwhi,
               int fftmax, const double2 *__restrict__ chirp, const double2 *__restrict__ bhat,
@@ -745,7 +745,7 @@ k_fft_inv_fwd(float2 *__restrict__ data, int C2, int nmap, int ngrp, int npl,
     __syncthreads();
     ring_dft_c<TPB, EPT>(buf, pf, tw, fftmax, chirp, bhat);
     if (tau_b && live) tau = tau_b[b];
-    const double lt = lam * tau * (live ? cscale[b].x : 1.0), l1t = (lam - 1.0) * tau;
+    const double lt = lam * tau * (live ? cscale[b].s : 1.0), l1t = (lam - 1.0) * tau;
     const double *rp = rho + (long)b * npix;
     const double *mp = M + (long)b * mstride;
     double mN[EPT], mS[EPT], rN[EPT], rS[EPT];
@@ -792,7 +792,7 @@ template <int TPB, int EPT>
 __global__ void __launch_bounds__(TPB)
 k_fft_inv_fwd_pol(float *__restrict__ colT, float *__restrict__ colP, int C2, int nmap, int npl, const double *__restrict__ rho,
                   const double *__restrict__ M6, double lam, double tau,
-                  const double2 *__restrict__ cscale, const PairFFT *__restrict__ pfft, const int *__restrict__ plist,
+                  const ColScale *__restrict__ cscale, const PairFFT *__restrict__ pfft, const int *__restrict__ plist,
                   const double2 *__restrict__ twlo, const double2 *__restrict__ twhi, int ntwhi,
                   int fftmax, const double2 *__restrict__ chirp, const double2 *__restrict__ bhat,
                   long npix, int nring, int nm, int lmax, int fftlen_class) {
@@ -826,7 +826,7 @@ k_fft_inv_fwd_pol(float *__restrict__ colT, float *__restrict__ colP, int C2, in
     inverse(RingSeq<const float2, true>{TN, csT}, RingSeq<const float2, true>{TS, csT}, sT);
     inverse(RingSeq<const float2, true>{QN, csP}, RingSeq<const float2, true>{QS, csP}, sQ);
     inverse(RingSeq<const float2, true>{QN + 1, csP}, RingSeq<const float2, true>{QS + 1, csP}, sU);
-    const double lt = lam * tau * cscale[b].x, l1t = (lam - 1.0) * tau;  // as in k_fft_inv_fwd
+    const double lt = lam * tau * cscale[b].s, l1t = (lam - 1.0) * tau;  // as in k_fft_inv_fwd
     const double *rp = rho + 3L * b * npix;
 #pragma unroll
     for (int u = 0; u < EPT; u++) {
@@ -938,7 +938,7 @@ static size_t split_sub_lds(const Plan &p) {
 
 template <bool FROM_MAP, bool PIX = false>
 static int split_sub(const Plan &p, const double *maps, int nb, const double *rho = nullptr,
-                     double lam = 1.0, const double2 *cscale = nullptr) {
+                     double lam = 1.0, const ColScale *cscale = nullptr) {
     const int cnt = p.fft_class_count[2];
     hipLaunchKernelGGL((k_fft_split_sub<kSplitSubTPB, 8, FROM_MAP, PIX>), dim3(nb, cnt, 4),
                        dim3(kSplitSubTPB), split_sub_lds(p), p.stream, maps, p.d_fftsplit,
