@@ -609,6 +609,7 @@ static int setup_batched(Plan &p, const std::vector<int> &lstart, const std::vec
         MFWF_TRY(dalloc(&p.d_segoff, segoff.size(), "lambda segment offsets"));
         MFWF_TRY(upload(p.d_segoff, segoff, p.stream));
     }
+    p.table_bytes = 4 * tot;
     if (table) MFWF_TRY(dalloc(&p.d_lam, tot, "lambda table"));
     MFWF_TRY(dalloc(&p.d_loff, loff.size(), "lambda offsets"));
     MFWF_TRY(dalloc(&p.d_Lp, Lp.size(), "lambda row lengths"));

@@ -798,7 +798,8 @@ k_gemm_analysis(const float *__restrict__ lam, LamGen gen, const long *__restric
 // The waves of the two parities swap their sums through LDS: the even one stores the north
 // rings E + O, the odd one the south rings E - O (lambda's mirror symmetry), or O - E with
 // flip (the spin-2 F-).
-template <int CT, bool GEN>
+// ONCE: the table's loads are streaming loads (launch rule: synthesis_once).
+template <int CT, bool GEN, bool ONCE>
 __global__ void __launch_bounds__(Tile<CT>::NTH, 2)
 k_gemm_synthesis(const float *__restrict__ lam, LamGen gen, const long *__restrict__ loff,
                  const int *__restrict__ Lp, const int *__restrict__ minls32,
@@ -850,7 +851,9 @@ k_gemm_synthesis(const float *__restrict__ lam, LamGen gen, const long *__restri
 #pragma unroll
             for (int u = 0; u < 2 * NA; u++) {
                 const char *x = reinterpret_cast<const char *>(lrow + (long)(u * (NTH / 8)) * L + r0);
-                ra[set][u] = *reinterpret_cast<const floatx4 *>(x + aoff);
+                const floatx4 *q = reinterpret_cast<const floatx4 *>(x + aoff);
+                if constexpr (ONCE) ra[set][u] = __builtin_nontemporal_load(q);
+                else ra[set][u] = *q;
             }
         }
         if constexpr (T::B1) {  // past lmax: valid data, times lambda = 0
@@ -1222,24 +1225,36 @@ static int analysis_launch(const Plan &p, int nc, int C2, const float *table, co
     return MFWF_OK;
 }
 
+// Streaming loads of the table, which leave the caches to coefficients and rings, where one
+// column group reads it (with two, the second finds the first one's rows in L2: nside 256, 64 maps,
+// us a call of sht_inv 795 cached, 803 streaming) and it is at most twice the 256 MB last-level
+// cache.  nside 256 (336 MB), an iteration, cached / streaming: 1 map 191 / 185, 16 maps 341 / 318, 24 maps
+// 511 / 484, 32 maps 595 / 566; nside 512 (2.1 GB): 1 map 1050 / 1070, 16 maps 1574 / 1602, and the
+// regrouping after it, 32 maps, 206 / 221.
+static bool synthesis_once(const Plan &p, int ncg) { return ncg == 1 && p.table_bytes <= (512L << 20); }
+
 static int synthesis_launch(const Plan &p, int nc, int C2, const float *table, const float *s_in,
                             float *out, int flip, int comb) {
     const int ct = gemm_tile(nc, p.gemm_ct[1], 8 * p.syn_per_xcd), ncg = (nc + ct - 1) / ct;
     const dim3 grid(8 * p.syn_per_xcd * ncg), block(ct == 64 ? 256 : 512);
     const LamGen g = lam_gen(p);
     if (table == nullptr && !p.d_lck) return fail(MFWF_EINVAL, "no lambda segment states in this plan");
-#define MFWF_SYN(CT, GEN)                                                                           \
-    hipLaunchKernelGGL((k_gemm_synthesis<CT, GEN>), grid, block, 0, p.stream, table, g, p.d_loff,    \
+#define MFWF_SYN(CT, GEN, ONCE)                                                                     \
+    hipLaunchKernelGGL((k_gemm_synthesis<CT, GEN, ONCE>), grid, block, 0, p.stream, table, g, p.d_loff,\
                        p.d_Lp, p.d_minls32, p.d_syn_items, p.d_syn_tab, p.syn_per_xcd, s_in,          \
                        p.d_mofs, out, p.lmax, p.npair, p.Rp, p.nring, p.nm, C2, nc, ncg, flip, comb)
     if (table == nullptr) {
-        if (ct == 128) MFWF_SYN(128, true);
-        else if (ct == 64) MFWF_SYN(64, true);
-        else MFWF_SYN(32, true);
+        if (ct == 128) MFWF_SYN(128, true, false);
+        else if (ct == 64) MFWF_SYN(64, true, false);
+        else MFWF_SYN(32, true, false);
+    } else if (synthesis_once(p, ncg)) {
+        if (ct == 128) MFWF_SYN(128, false, true);
+        else if (ct == 64) MFWF_SYN(64, false, true);
+        else MFWF_SYN(32, false, true);
     } else {
-        if (ct == 128) MFWF_SYN(128, false);
-        else if (ct == 64) MFWF_SYN(64, false);
-        else MFWF_SYN(32, false);
+        if (ct == 128) MFWF_SYN(128, false, false);
+        else if (ct == 64) MFWF_SYN(64, false, false);
+        else MFWF_SYN(32, false, false);
     }
 #undef MFWF_SYN
     MFWF_HIP(hipGetLastError());

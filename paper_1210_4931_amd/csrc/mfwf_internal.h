@@ -131,6 +131,7 @@ struct Plan {
     int C2 = 0;                  // columns = 2 Bp (re, im of each map)
     float *d_lam = nullptr;      // lambda_lm(z_p) FP32, rows [m][pair][l - m] padded to 128
                                  // (null when the temperature GEMMs generate their rows)
+    long table_bytes = 0;        // of d_lam (and of d_fp, d_fm)
     bool lam_gen = false;        // temperature GEMMs generate lambda from d_lck instead of d_lam
     double2 *d_lck = nullptr;    // recurrence state entering every 16-row segment of the rows,
                                  // [(segoff[m] + seg) Rp + pair] (temperature FP32 plans)
