@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "leg_core.h"
+#include "stage_graphs.h"
 
 struct mfwf_plan_s {
     mfwf::Plan p;
@@ -1079,15 +1080,41 @@ int plan_set_cl(Plan &p, const double *cl) {
 }
 
 // One captured iteration of a stage, replayed as often as needed.  Its launches read the
-// executable graph while they run, so it waits for them before it goes.
+// executable graph while they run, so it waits for them before it goes: for those before its
+// mark, or for the whole stream.
 struct StageGraph {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     hipStream_t stream = nullptr;
+    hipEvent_t last = nullptr;  // after the last launch
     ~StageGraph() {
-        if (exec) (void)hipStreamSynchronize(stream);
+        if (exec && last) (void)hipEventSynchronize(last);
+        else if (exec) (void)hipStreamSynchronize(stream);
+        if (last) (void)hipEventDestroy(last);
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
+    }
+    int mark() {
+        hipEvent_t e = nullptr;
+        MFWF_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        const hipError_t rc = hipEventRecord(e, stream);
+        if (rc != hipSuccess) {
+            (void)hipEventDestroy(e);
+            return fail(MFWF_EDEVICE, std::string("stage end: ") + hipGetErrorString(rc));
+        }
+        last = e;
+        return MFWF_OK;
+    }
+    int passed(bool &yes) {
+        const hipError_t e = hipEventQuery(last);
+        yes = e == hipSuccess;
+        if (e != hipSuccess && e != hipErrorNotReady)
+            return fail(MFWF_EDEVICE, std::string("stage end: ") + hipGetErrorString(e));
+        return MFWF_OK;
+    }
+    int wait() {
+        MFWF_HIP(hipEventSynchronize(last));
+        return MFWF_OK;
     }
     int capture(Plan &p, const double *rho, int nb, double lam) {
         stream = p.stream;
@@ -1191,9 +1218,7 @@ static int solve_chunk(Plan &p, const double *input, int nb, double *s_alm_out,
     // in diag[b][6..7] on the device (no host wait)
     long chk_last = -1, chk_prev = -1;
     bool stopped = false;
-    // every stage's graph until the results are in: destroyed between two stages, a graph
-    // would go while its launches still run
-    std::vector<std::unique_ptr<StageGraph>> graphs;
+    StageGraphs<StageGraph> graphs;
     for (size_t s = 0; s < lam.size() && !stopped; s++) {
         long remaining = its[s];
         if (remaining <= 0) continue;
@@ -1209,8 +1234,7 @@ static int solve_chunk(Plan &p, const double *input, int nb, double *s_alm_out,
             const long plain = check ? run - 1 : run;
             if (graph && plain >= 2) {
                 if (!sg) {
-                    graphs.push_back(std::make_unique<StageGraph>());
-                    sg = graphs.back().get();
+                    MFWF_TRY(graphs.next(sg));
                     MFWF_TRY(sg->capture(p, rho, nb, lam[s]));
                 }
                 MFWF_TRY(sg->launch(p, (int)plain));
