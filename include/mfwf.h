@@ -361,9 +361,10 @@ int mfwf_plan_work(mfwf_plan plan, double *out4);
 /*
  * Kernel shapes the plan uses (host, 8 ints): [0] FP64 Legendre synthesis variant (0..8),
  * [1] analysis variant (0..5), [2] maps per workgroup of the batched form's ring step for
- * the shorter transforms and [3] for the longest (1, 2, 4), [4] column tile of the analysis
- * GEMM (1: 64 columns in 4 waves, 2: 128 columns in 4 waves, 3: 128 columns in 8 waves) and
- * [5] largest column tile of the synthesis GEMM, in units of 64 columns (1, 2), [6] 1 if the
+ * the shorter transforms and [3] for the longest (1, 2, 4; the same where one launch takes
+ * both), [4], [5] column tile of the analysis and of the synthesis GEMM's widest launches
+ * over max_batch maps (1: 64 columns, 2: 128, 3: 32, which launches too small to fill the chip
+ * with wider ones take whatever the choice, unless it is forced), [6] 1 if the
  * temperature GEMMs generate lambda_lm from the FP64 recurrence (its state every 16 values
  * of l, tabulated per plan) instead of reading the FP32 table (0; no table above nside 1024),
  * [7] how they were set: 0 defaults, 1 by the autotuner at plan creation (timed, or read
@@ -373,8 +374,8 @@ int mfwf_plan_work(mfwf_plan plan, double *out4);
  * more) times every applicable value of each at plan creation and caches the choice per
  * (device, library build, nside, lmax, max_batch, dtype, spin) in $MFWF_TUNE_CACHE (default
  * $XDG_CACHE_HOME/mfwf/tune.txt or ~/.cache/mfwf/tune.txt).  MFWF_TUNE_FORCE =
- * "synth=3,ana=1,g0=2,g1=1,cta=1,cts=2,lamgen=1" (any subset) sets them at plan creation for any
- * plan size; a malformed value makes mfwf_plan_create fail with MFWF_EINVAL.
+ * "synth=3,ana=1,g0=2,g1=1,cta=1,cts=2,lamgen=1" (any subset; cta 1, 2, 3, cts 1, 2) sets them at
+ * plan creation for any plan size; a malformed value makes mfwf_plan_create fail with MFWF_EINVAL.
  */
 int mfwf_plan_tuning(mfwf_plan plan, int *out8);
 

@@ -289,7 +289,7 @@ static int device_name(std::string &name) {
 //               and longest-transform class, or both where one launch takes them (1, 2 or
 //               4; as LDS and 1024 threads allow)
 //   cta, cts    column tile of the analysis / synthesis GEMMs: 1: 64 columns, 2: 128, 3
-//               (analysis only): 32
+//               (analysis only): 32; launches too small for it take 32 columns, unless forced
 //   lamgen      temperature GEMMs: lambda read from the FP32 table (0) or generated from the
 //               FP64 recurrence's segment states (1; the only choice above nside 1024)
 // With MFWF_AUTOTUNE != 0 (default) a plan of at least 256 ring pairs times every value of
@@ -403,6 +403,7 @@ static bool tune_force(const char *env, Plan &p) {
         if (q == kNumKnobs || !end || *end != '\0' || !knob_valid(q, (int)v))
             return fail(MFWF_EINVAL, "MFWF_TUNE_FORCE: bad entry '" + tok + "'"), false;
         k[q] = (int)v;
+        if (q == kKnobCtA || q == kKnobCtS) p.gemm_forced[q - kKnobCtA] = true;
     }
     set_knobs(p, k);
     return true;
@@ -490,16 +491,29 @@ static int autotune(Plan &p, const std::string &devname) {
         }
         // the widest GEMM launches: 2 columns a map (temperature), 4 (the spin-2 F+- tables)
         const int w = p.spin == 2 ? 4 : 2;
-        if (w * B > 64) {  // more than 64 active columns: every column tile applies
-            const std::vector<int> cv = {1, 2}, cva = {1, 2, 3};
-            MFWF_TRY(tune_knob(p, kKnobCtA, cva, [&] {
-                return p.spin == 2 ? launch_gemm_analysis_raw(p, B, 4, p.d_fp, p.d_ph32p, p.d_ap32, 0)
-                                   : launch_gemm_analysis(p, B, p.d_a32, nullptr, 1.0, 1.0);
-            }));
-            MFWF_TRY(tune_knob(p, kKnobCtS, cv, [&] {
-                return p.spin == 2 ? launch_gemm_synthesis_on(p, B, 4, p.d_fp, p.d_seb32, p.d_ph32p, 0, 0)
-                                   : launch_gemm_synthesis(p, B);
-            }));
+        if (w * B > 64) {  // more than 64 active columns
+            // the choices that launch different tiles (small launches leave one)
+            auto tiles = [&](int which, std::vector<int> v) {
+                std::vector<int> out, seen;
+                for (int c : v) {
+                    const int t = gemm_effective(p, which, c);
+                    if (std::find(seen.begin(), seen.end(), t) != seen.end()) continue;
+                    seen.push_back(t);
+                    out.push_back(c);
+                }
+                return out;
+            };
+            const std::vector<int> cva = tiles(0, {1, 2, 3}), cvs = tiles(1, {1, 2});
+            if (cva.size() > 1)
+                MFWF_TRY(tune_knob(p, kKnobCtA, cva, [&] {
+                    return p.spin == 2 ? launch_gemm_analysis_raw(p, B, 4, p.d_fp, p.d_ph32p, p.d_ap32, 0)
+                                       : launch_gemm_analysis(p, B, p.d_a32, nullptr, 1.0, 1.0);
+                }));
+            if (cvs.size() > 1)
+                MFWF_TRY(tune_knob(p, kKnobCtS, cvs, [&] {
+                    return p.spin == 2 ? launch_gemm_synthesis_on(p, B, 4, p.d_fp, p.d_seb32, p.d_ph32p, 0, 0)
+                                       : launch_gemm_synthesis(p, B);
+                }));
         }
     }
     get_knobs(p, k);
@@ -2155,6 +2169,10 @@ int mfwf_plan_tuning(mfwf_plan plan, int *out8) {
     const Plan &p = plan->p;
     int k[kNumKnobs];
     get_knobs(p, k);
+    if (p.dtype == MFWF_F32) {  // what is launched
+        if (ring_merged(p, kRingCols, p.max_batch)) k[kKnobG0] = k[kKnobG1];
+        for (int which = 0; which < 2; which++) k[kKnobCtA + which] = gemm_effective(p, which, p.gemm_ct[which]);
+    }
     for (int q = 0; q < kNumKnobs; q++) out8[q] = k[q];
     out8[7] = p.tune_source;
     return MFWF_OK;

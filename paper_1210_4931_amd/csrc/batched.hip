@@ -1183,15 +1183,22 @@ int launch_cols_to_rows(const Plan &p, int nb) {
 // whole 32-column MFMA tiles; never beyond the padded width (w Bp, a multiple of 32)
 static int active_cols(int nb, int w) { return 32 * ((w * nb + 31) / 32); }
 
-// columns per GEMM tile for nc active columns and a plan's choice (1: 64, 2: 128, 3: 32)
-// Column tile of a launch over ntile row tiles: 32 columns where tiles of 64 would leave the
-// chip's 512 places for workgroups filled less than about twice (nside 128, 40 maps, 1028 such
-// workgroups: synthesis 51 us with them, 34 with 32 columns; at nside 256, 20 maps, 2052 of
-// them, 82 against 89), the narrowest that holds all columns, or else the plan's choice.
-static int gemm_tile(int nc, int choice, int ntile) {
-    if (ntile * ((nc + 63) / 64) < 1200) return 32;
+// Column tile of a launch of the analysis (which = 0) or synthesis (1) over nc active columns for
+// a choice 1: 64 columns, 2: 128, 3: 32: 32 columns where tiles of 64 would leave the chip's 512
+// places for workgroups filled less than about twice (nside 128, 40 maps, 1028 such workgroups:
+// synthesis 51 us with them, 34 with 32 columns; at nside 256, 20 maps, 2052 of them, 82 against
+// 89), the narrowest that holds all columns, or else the choice; a forced choice as it is.
+static int gemm_tile(const Plan &p, int which, int choice, int nc) {
     const int ct = choice == 2 ? 128 : (choice == 3 ? 32 : 64);
+    if (p.gemm_forced[which]) return ct;
+    const int ntile = 8 * (which ? p.syn_per_xcd : p.ana_per_xcd);
+    if (ntile * ((nc + 63) / 64) < 1200) return 32;
     return nc <= 32 ? 32 : (nc <= 64 ? std::min(ct, 64) : ct);
+}
+
+int gemm_effective(const Plan &p, int which, int choice) {
+    const int ct = gemm_tile(p, which, choice, active_cols(p.max_batch, p.spin == 2 ? 4 : 2));
+    return ct == 128 ? 2 : (ct == 32 ? 3 : 1);
 }
 
 static LamGen lam_gen(const Plan &p) {
@@ -1202,7 +1209,7 @@ static LamGen lam_gen(const Plan &p) {
 static int analysis_launch(const Plan &p, int nc, int C2, const float *table, const float *cols,
                            float *a_out, float *s_out, double scale_s, double lto,
                            const double *tau_b, double lto_per_tau, int flip) {
-    const int ct = gemm_tile(nc, p.gemm_ct[0], 8 * p.ana_per_xcd), ncg = (nc + ct - 1) / ct;
+    const int ct = gemm_tile(p, 0, p.gemm_ct[0], nc), ncg = (nc + ct - 1) / ct;
     const dim3 grid(8 * p.ana_per_xcd * ncg), block(ct == 64 ? 256 : 512);
     const LamGen g = lam_gen(p);
     if (table == nullptr && !p.d_lck) return fail(MFWF_EINVAL, "no lambda segment states in this plan");
@@ -1235,7 +1242,7 @@ static bool synthesis_once(const Plan &p, int ncg) { return ncg == 1 && p.table_
 
 static int synthesis_launch(const Plan &p, int nc, int C2, const float *table, const float *s_in,
                             float *out, int flip, int comb) {
-    const int ct = gemm_tile(nc, p.gemm_ct[1], 8 * p.syn_per_xcd), ncg = (nc + ct - 1) / ct;
+    const int ct = gemm_tile(p, 1, p.gemm_ct[1], nc), ncg = (nc + ct - 1) / ct;
     const dim3 grid(8 * p.syn_per_xcd * ncg), block(ct == 64 ? 256 : 512);
     const LamGen g = lam_gen(p);
     if (table == nullptr && !p.d_lck) return fail(MFWF_EINVAL, "no lambda segment states in this plan");

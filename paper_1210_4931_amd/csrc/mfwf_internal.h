@@ -66,7 +66,9 @@ struct Plan {
     int ngroup;             // pair groups (waves per m) of the chosen analysis variant
     int ring_group[2] = {1, 1};  // maps per workgroup of the columns ring step, per class
     int gemm_ct[2] = {2, 2};     // column tiles of the analysis GEMM (1: 64 columns, 2: 128, 3: 32) and
-                                 // the synthesis GEMM (1, 2)
+                                 // the synthesis GEMM (1, 2), where the launch's size leaves them a
+                                 // choice or they are forced (gemm_tile)
+    bool gemm_forced[2] = {false, false};
     int tune_source = 0;         // 0 defaults, 1 autotuned (timed or cached), 3 forced
     int ngroup_max;         // largest pair-group count of any analysis variant
 
@@ -126,7 +128,7 @@ struct Plan {
     double work_tuples = 0.0;  // (l, m, pair) triples with l >= start index
 
     // batched FP32 form (dtype MFWF_F32): lambda table and column-major work arrays
-    int Rp = 0;                  // ring pairs padded to 64
+    int Rp = 0;                  // ring pairs padded to 128
     int Bp = 0;                  // maps padded to 16
     int C2 = 0;                  // columns = 2 Bp (re, im of each map)
     float *d_lam = nullptr;      // lambda_lm(z_p) FP32, rows [m][pair][l - m] padded to 128
@@ -139,8 +141,8 @@ struct Plan {
     long *d_loff = nullptr;      // [nm] offset of m's rows
     int *d_Lp = nullptr;         // [nm] padded row length
     int *d_minls32 = nullptr;    // [nm][Rp/32] smallest start index in each 32-pair chunk
-    int2 *d_ana_items = nullptr; // (m, 128-row l tile) work items of the analysis GEMM
-    int2 *d_syn_items = nullptr; // (m, 64-pair tile) work items of the synthesis GEMM
+    int2 *d_ana_items = nullptr; // (m, tile of 256 values of l) work items of the analysis GEMM
+    int2 *d_syn_items = nullptr; // (m, tile of 128 pairs) work items of the synthesis GEMM
     int *d_ana_tab = nullptr;    // [8][ana_per_xcd] item list of each XCD (-1 = none)
     int *d_syn_tab = nullptr;    // [8][syn_per_xcd]
     int ana_per_xcd = 0, syn_per_xcd = 0;
@@ -251,6 +253,9 @@ int launch_zero_map_cols(const Plan &p, int b);  // map b's columns of d_ph32 = 
 int launch_gemm_analysis(const Plan &p, int nb, float *a_out, float *s_out, double scale_s,
                          double lto, double lto_per_tau = 0.0);
 int launch_gemm_synthesis(const Plan &p, int nb);
+// the tile (1: 64 columns, 2: 128, 3: 32) that a choice gives the widest launches over max_batch
+// maps of the analysis (which = 0) or synthesis (1) GEMM
+int gemm_effective(const Plan &p, int which, int choice);
 int launch_alm_to_cols(const Plan &p, const double2 *alm, float *x32, int nb, int mode);
 int launch_cols_to_alm(const Plan &p, const float *x32, double2 *alm, int nb, double scale);
 // w real columns per map (width w Bp); flip: the table has the opposite mirror symmetry
