@@ -1232,13 +1232,17 @@ static int analysis_launch(const Plan &p, int nc, int C2, const float *table, co
     return MFWF_OK;
 }
 
-// Streaming loads of the table, which leave the caches to coefficients and rings, where one
-// column group reads it (with two, the second finds the first one's rows in L2: nside 256, 64 maps,
-// us a call of sht_inv 795 cached, 803 streaming) and it is at most twice the 256 MB last-level
-// cache.  nside 256 (336 MB), an iteration, cached / streaming: 1 map 191 / 185, 16 maps 341 / 318, 24 maps
-// 511 / 484, 32 maps 595 / 566; nside 512 (2.1 GB): 1 map 1050 / 1070, 16 maps 1574 / 1602, and the
-// regrouping after it, 32 maps, 206 / 221.
-static bool synthesis_once(const Plan &p, int ncg) { return ncg == 1 && p.table_bytes <= (512L << 20); }
+// Streaming loads of the table, which leave the 256 MB last-level cache to coefficients and rings,
+// where one column group reads the table (with two, the second finds the first one's rows in L2:
+// nside 256, 64 maps, us a call of sht_inv 795 cached, 803 streaming) and it is somewhat larger than
+// that cache: a smaller one stays there from one contraction to the next, and of a much larger one
+// nothing is lost.  An iteration, us cached / streaming, with 1, 4, 24 maps: 130 MB (nside 256) 97 / 105,
+// 118 / 124, 345 / 349; 260 MB (nside 512) 202 / 206, 283 / 285; 321 MB (nside 256) 190 / 184, 216 / 204, 501 / 490;
+// 542 MB 292 / 278, 320 / 305, 657 / 653; 642 MB (nside 512) 375 / 366, 457 / 451; 1143 MB 581 / 579, 672 / 676;
+// 2308 MB 1048 / 1065, 1159 / 1175.
+static bool synthesis_once(const Plan &p, int ncg) {
+    return ncg == 1 && p.table_bytes > (288L << 20) && p.table_bytes <= (768L << 20);
+}
 
 static int synthesis_launch(const Plan &p, int nc, int C2, const float *table, const float *s_in,
                             float *out, int flip, int comb) {
