@@ -272,10 +272,12 @@ k_cols_to_rows(const float *__restrict__ ph32, float2 *__restrict__ phf, int nri
 // with A = lambda (analysis: rows = values of l of parity q, k = ring pairs; synthesis: rows
 // = ring pairs, k = values of l of parity q) and B the FP32 columns.
 //
-// FP32 products on the bf16 matrix cores: every FP32 operand is the exact sum of three bf16
-// pieces (8 + 8 + 8 bits, each the rounded remainder of the ones before), and the six piece
-// products above 2^-27 of the product (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi) are
-// accumulated in FP32; what is left out is below FP32's own rounding.  On this card random
+// FP32 products on the bf16 matrix cores: every FP32 operand is the sum of three bf16 pieces, each
+// the nearest to what the ones before leave (exact above 2^-110, where the column scales keep
+// the values that count, and up to the largest finite bf16).  Of the nine piece products the
+// six large ones (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi) are accumulated in FP32; the other
+// three are at most 2^-24 of the product, the rounding of an FP32 product, and 2^-27.5 in the rms
+// (mid is at most 2^-8 of the value, lo 2^-17).  On this card random
 // data runs v_mfma_f32_32x32x16_bf16 at 1.67 PFLOP/s, so six of them take the time of 278
 // TFLOP/s, where v_mfma_f32_32x32x2_f32 reaches 117-142; and one rounding per 16 values of k
 // instead of one per 2 makes the sums more exact, not less.  The sums of 16 values of k start
@@ -333,28 +335,10 @@ __device__ __forceinline__ unsigned pack_bf16(float x, float y) {
     const bf16x2 v = {(__bf16)x, (__bf16)y};  // one v_cvt_pk_bf16_f32, round to nearest even
     return __builtin_bit_cast(unsigned, v);
 }
-// DITHER: hi is not the nearest bf16 but one of the two neighbours, chosen by the value's own
-// lowest byte as the rounding threshold (the remainders stay exact).  The data of successive
-// iterations differ in their last bits only; with the nearest hi the largest piece products,
-// and with them the matrix cores' rounding, would be the same from one iteration to the next,
-// and an error that repeats grows linearly where one that varies averages out.
-template <bool DITHER>
 __device__ __forceinline__ Split4 split4(float v0, float v1, float v2, float v3) {
     Split4 s;
-    if constexpr (DITHER) {
-        auto thr = [](float v) {
-            const unsigned u = __float_as_uint(v);
-            return u + ((u & 0xffu) << 8);
-        };
-        const unsigned d0 = thr(v0), d1 = thr(v1), d2 = thr(v2), d3 = thr(v3);
-        s.p[0] = make_uint2(__builtin_amdgcn_perm(d1, d0, 0x07060302u), __builtin_amdgcn_perm(d3, d2, 0x07060302u));
-        v0 -= __uint_as_float(d0 & 0xffff0000u);
-        v1 -= __uint_as_float(d1 & 0xffff0000u);
-        v2 -= __uint_as_float(d2 & 0xffff0000u);
-        v3 -= __uint_as_float(d3 & 0xffff0000u);
-    }
 #pragma unroll
-    for (int q = DITHER ? 1 : 0; q < 3; q++) {
+    for (int q = 0; q < 3; q++) {
         const unsigned a = pack_bf16(v0, v1), b = pack_bf16(v2, v3);
         s.p[q] = make_uint2(a, b);
         if (q < 2) {  // the remainders, exact
@@ -368,16 +352,15 @@ __device__ __forceinline__ Split4 split4(float v0, float v1, float v2, float v3)
 }
 
 // the same of two floats, each piece in the halves of one register
-__device__ __forceinline__ void split2_dithered(float v0, float v1, unsigned (&p)[3]) {
-    const unsigned u0 = __float_as_uint(v0), u1 = __float_as_uint(v1);
-    const unsigned d0 = u0 + ((u0 & 0xffu) << 8), d1 = u1 + ((u1 & 0xffu) << 8);
-    p[0] = __builtin_amdgcn_perm(d1, d0, 0x07060302u);
-    v0 -= __uint_as_float(d0 & 0xffff0000u);
-    v1 -= __uint_as_float(d1 & 0xffff0000u);
-    p[1] = pack_bf16(v0, v1);
-    v0 -= __uint_as_float(p[1] << 16);
-    v1 -= __uint_as_float(p[1] & 0xffff0000u);
-    p[2] = pack_bf16(v0, v1);
+__device__ __forceinline__ void split2(float v0, float v1, unsigned (&p)[3]) {
+#pragma unroll
+    for (int q = 0; q < 3; q++) {
+        p[q] = pack_bf16(v0, v1);
+        if (q < 2) {
+            v0 -= __uint_as_float(p[q] << 16);
+            v1 -= __uint_as_float(p[q] & 0xffff0000u);
+        }
+    }
 }
 
 static constexpr int kRows = 128;       // rows per parity of a tile
@@ -415,7 +398,7 @@ __device__ __forceinline__ void put_split(unsigned short *buf, int par, int k4, 
 __device__ __forceinline__ void put_split1(unsigned short *buf, int par, int k, int row, int rows,
                                            float v0, float v1) {
     unsigned x[3];
-    split2_dithered(v0, v1, x);
+    split2(v0, v1, x);
 #pragma unroll
     for (int q = 0; q < 3; q++) {
         buf[piece_at(par, q, k >> 2, row, rows) + (k & 3)] = (unsigned short)x[q];
@@ -480,13 +463,15 @@ __device__ __forceinline__ float ld_off(const float *base, unsigned byte) {
 // The matrix cores bring the terms of one v_mfma_f32_32x32x16_bf16 to the largest one's
 // exponent by rounding towards minus infinity one bit below its last (measured: a small C
 // under a product loses 0.25 ulp of the sum on average, whatever the signs; the FP32 form
-// rounds to nearest).  Left alone, that bias is the same in every iteration and grows
-// linearly in the modes that converge slowly (3.4e-6 after 300 iterations at nside 512, where
-// the FP32 products had 2.2e-6).  So its sign alternates: the stages of both
-// contractions alternate between sums and negated sums, and in the synthesis, whose terms
-// fall off with l, so do the rings, whose alternating error has no large-scale part.  With
-// that and the dithered splits the errors after 5 to 300 iterations are those of the FP32
-// products or smaller (nside 512: 1.0e-6 after 100, where they had 1.15e-6).
+// rounds to nearest).  Left alone, every sum comes out low: the mean error of an analysis is -0.24 of
+// its rms at nside 64 and -0.33 at nside 512, the same in every iteration, and it adds up in the
+// modes that converge slowly (nside 512, two maps, 300 iterations: 2.2e-6).  So its sign
+// alternates: the stages of both contractions alternate between sums and negated sums, and in
+// the synthesis, whose terms fall off with l, so do the rings, whose alternating error has no
+// large-scale part.  The mean is then 0.003-0.03 of the rms and the error after 300 iterations 1.6e-6
+// (1.7e-6 with the FP32 instructions; after 100 6.6e-7-7.6e-7 against 7.3e-7).
+// Rounding the leading piece at random, so that the pieces differ from one iteration to the
+// next, changes neither the mean nor the errors, and lets the products left out reach 2^-23.6.
 __device__ __forceinline__ float row_sign(int row) { return row & 1 ? -1.f : 1.f; }
 
 // analysis: tile = (m, 256 values of l, CT columns); K loop over active chunks of 32 ring
@@ -645,8 +630,8 @@ k_gemm_analysis(const float *__restrict__ lam, LamGen gen, const long *__restric
                     v[2 * j + 1] = ra[set][u][2 * j + 1];
                 }
             }
-            put_split(sA[buf], 0, k4, row, kRows, split4<false>(v[0], v[2], v[4], v[6]));
-            put_split(sA[buf], 1, k4, row, kRows, split4<false>(v[1], v[3], v[5], v[7]));
+            put_split(sA[buf], 0, k4, row, kRows, split4(v[0], v[2], v[4], v[6]));
+            put_split(sA[buf], 1, k4, row, kRows, split4(v[1], v[3], v[5], v[7]));
         }
         if constexpr (T::B1) {
             float n = rb[set][0], v = p0 + bk4 < npair - 1 ? rb[set][1] : 0.f;  // the equator counts once
@@ -659,8 +644,8 @@ k_gemm_analysis(const float *__restrict__ lam, LamGen gen, const long *__restric
                 ps[j] = buf ? -rb[set][j] - rb[set][4 + j] : rb[set][j] + rb[set][4 + j];
                 df[j] = buf ? rb[set][4 + j] - rb[set][j] : rb[set][j] - rb[set][4 + j];
             }
-            put_split(sB[buf], flip, bk4, bcol, CT, split4<true>(ps[0], ps[1], ps[2], ps[3]));
-            put_split(sB[buf], flip ^ 1, bk4, bcol, CT, split4<true>(df[0], df[1], df[2], df[3]));
+            put_split(sB[buf], flip, bk4, bcol, CT, split4(ps[0], ps[1], ps[2], ps[3]));
+            put_split(sB[buf], flip ^ 1, bk4, bcol, CT, split4(df[0], df[1], df[2], df[3]));
         }
     };
     float acc[NRT][NCT][16];
@@ -889,14 +874,14 @@ k_gemm_synthesis(const float *__restrict__ lam, LamGen gen, const long *__restri
 #pragma unroll
                     for (int q = 0; q < 2; q++)
                         put_split(sA[buf], q, 2 * gk + h, gp, kRows,
-                                  split4<false>(v[8 * h + q], v[8 * h + 2 + q], v[8 * h + 4 + q], v[8 * h + 6 + q]));
+                                  split4(v[8 * h + q], v[8 * h + 2 + q], v[8 * h + 4 + q], v[8 * h + 6 + q]));
             }
         } else {
 #pragma unroll
             for (int u = 0; u < 2 * NA; u++) {
                 // l = 4 al .. 4 al + 3: k = 2 al, 2 al + 1 of each parity
                 const floatx4 v = (buf ? -rsgn : rsgn) * ra[set][u];
-                const Split4 x = split4<false>(v[0], v[2], v[1], v[3]);  // .x even pair, .y odd pair
+                const Split4 x = split4(v[0], v[2], v[1], v[3]);  // .x even pair, .y odd pair
 #pragma unroll
                 for (int q = 0; q < 3; q++) {
                     unsigned short *o = sA[buf] + piece_at(0, q, al >> 1, arow + u * (NTH / 8), kRows) + 2 * (al & 1);
@@ -909,8 +894,8 @@ k_gemm_synthesis(const float *__restrict__ lam, LamGen gen, const long *__restri
             put_split1(sB[buf], 0, bk4, bcol, CT, rb[set][0], rb[set][1]);
         } else if (b_on) {
             const float *v = rb[set];
-            put_split(sB[buf], 0, bk4, bcol, CT, split4<true>(v[0], v[2], v[4], v[6]));
-            put_split(sB[buf], 1, bk4, bcol, CT, split4<true>(v[1], v[3], v[5], v[7]));
+            put_split(sB[buf], 0, bk4, bcol, CT, split4(v[0], v[2], v[4], v[6]));
+            put_split(sB[buf], 1, bk4, bcol, CT, split4(v[1], v[3], v[5], v[7]));
         }
     };
     float acc[NRT][NCT][16];
