@@ -306,8 +306,6 @@ k_cols_to_rows(const float *__restrict__ ph32, float2 *__restrict__ phf, int nri
 // i + 32 (k / 8), element k % 8, B[k][j] likewise in lane j + 32 (k / 8); accumulator register r
 // of lane L holds D[8 (r/4) + 4 (L/32) + r%4][L%32].
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
-
 // Tile of workgroup bid: XCD x = bid mod 8 works through its own list tab[x][*] of tiles
 // (balanced by work on the host, tiles of one m adjacent); columns groups innermost.
 struct XcdTile {
@@ -321,8 +319,6 @@ __device__ __forceinline__ XcdTile xcd_tile(const int *__restrict__ tab, int per
     r.item = (k < per_xcd) ? tab[x * per_xcd + k] : -1;
     return r;
 }
-
-__device__ __forceinline__ floatx4 ld4(const float *q) { return *reinterpret_cast<const floatx4 *>(q); }
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -691,14 +687,9 @@ k_gemm_analysis(const float *__restrict__ lam, LamGen gen, const long *__restric
             __syncthreads();  // sAc
             load(32 * pc, 0);
             gen_rows(0);
-            float keep[T::NBV];
-#pragma unroll
-            for (int j = 0; j < T::NBV; j++) keep[j] = rb[0][j];
             load(32 * pc + 16, 1);
             gen_rows(1);
             __syncthreads();
-#pragma unroll
-            for (int j = 0; j < T::NBV; j++) rb[0][j] = keep[j];
             split(32 * pc, 0, 0);
         } else {
             load(32 * pc, 0);

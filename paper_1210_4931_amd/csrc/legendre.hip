@@ -41,29 +41,25 @@ namespace mfwf {
 // ---------------------------------------------------------------------------------------
 // Synthesis
 // ---------------------------------------------------------------------------------------
-template <int NB, int P>
+template <int P>
 struct SynthAcc {
-    double Er[P][NB], Ei[P][NB], Or[P][NB], Oi[P][NB];
+    double Er[P], Ei[P], Or[P], Oi[P];
     __device__ __forceinline__ void zero() {
 #pragma unroll
-        for (int k = 0; k < P; k++)
-#pragma unroll
-            for (int j = 0; j < NB; j++) Er[k][j] = Ei[k][j] = Or[k][j] = Oi[k][j] = 0.0;
+        for (int k = 0; k < P; k++) Er[k] = Ei[k] = Or[k] = Oi[k] = 0.0;
     }
     template <bool ODD>
-    __device__ __forceinline__ void add(const double (&cur)[P], const double2 (&a)[NB]) {
+    __device__ __forceinline__ void add(const double (&cur)[P], double2 a) {
 #pragma unroll
-        for (int j = 0; j < NB; j++)
-#pragma unroll
-            for (int k = 0; k < P; k++) {
-                if (ODD) {
-                    Or[k][j] = fma(cur[k], a[j].x, Or[k][j]);
-                    Oi[k][j] = fma(cur[k], a[j].y, Oi[k][j]);
-                } else {
-                    Er[k][j] = fma(cur[k], a[j].x, Er[k][j]);
-                    Ei[k][j] = fma(cur[k], a[j].y, Ei[k][j]);
-                }
+        for (int k = 0; k < P; k++) {
+            if (ODD) {
+                Or[k] = fma(cur[k], a.x, Or[k]);
+                Oi[k] = fma(cur[k], a.y, Oi[k]);
+            } else {
+                Er[k] = fma(cur[k], a.x, Er[k]);
+                Ei[k] = fma(cur[k], a.y, Ei[k]);
             }
+        }
     }
 };
 
@@ -82,7 +78,7 @@ __device__ __forceinline__ void synth_one_m(int m, int g, const double2 *__restr
     const long off = mofs[m];
     const double *Am = Atab + off;
     const double2 *am = alm + off;
-    SynthAcc<1, P> acc;
+    SynthAcc<P> acc;
     acc.zero();
     const int nl = lmax - m + 1;  // values of l, from r = l - m = 0
     int r = st.klo * kLegBlock;
@@ -100,20 +96,18 @@ __device__ __forceinline__ void synth_one_m(int m, int g, const double2 *__restr
 #pragma unroll
             for (int u = 0; u < U; u++) {
                 double cur[P];
-                const double2 au[1] = {a[u]};
                 st.step(A[u], cur);
-                if (u & 1) acc.template add<true>(cur, au);
-                else acc.template add<false>(cur, au);
+                if (u & 1) acc.template add<true>(cur, a[u]);
+                else acc.template add<false>(cur, a[u]);
             }
         }
     }
     if (r < nl) st.enter(r / kLegBlock);
     for (; r < nl; r++) {  // the last, partial block
         double cur[P];
-        const double2 au[1] = {am[r]};
         st.step(Am[r], cur);
-        if (r & 1) acc.template add<true>(cur, au);
-        else acc.template add<false>(cur, au);
+        if (r & 1) acc.template add<true>(cur, am[r]);
+        else acc.template add<false>(cur, am[r]);
     }
 #pragma unroll
     for (int k = 0; k < P; k++) {
@@ -121,9 +115,9 @@ __device__ __forceinline__ void synth_one_m(int m, int g, const double2 *__restr
         if (p >= npair) continue;
         const int rN = p, rS = nring - 1 - p;
         double2 *out = phase + m;  // ring-Fourier layout [map][ring][m]
-        out[(long)rN * nm] = make_double2(acc.Er[k][0] + acc.Or[k][0], acc.Ei[k][0] + acc.Oi[k][0]);
+        out[(long)rN * nm] = make_double2(acc.Er[k] + acc.Or[k], acc.Ei[k] + acc.Oi[k]);
         if (rS != rN)
-            out[(long)rS * nm] = make_double2(acc.Er[k][0] - acc.Or[k][0], acc.Ei[k][0] - acc.Oi[k][0]);
+            out[(long)rS * nm] = make_double2(acc.Er[k] - acc.Or[k], acc.Ei[k] - acc.Oi[k]);
     }
 }
 
