@@ -819,16 +819,16 @@ static int create(int nside, int lmax, int spin, int dtype, int max_batch, void 
         twhi[h] = make_double2(std::cos(a), std::sin(a));
     }
     // FFT classes: pairs whose transform fits half of the largest length (0), the rest (1), and the
-    // split rings (2; their combined spectrum of n <= fftmax points passes through LDS).  Class 1
-    // comes first in the list and class 0 follows it, so that one launch can take both.
+    // split rings (2; their combined spectrum of n <= fftmax points passes through LDS), and the first
+    // two together (3), for launches that take both
     std::vector<int> plist;
     p.fft_class_len[0] = 1;
     int nsplit_max = 0;
-    for (int c : {1, 0, 2}) {
+    for (int c = 0; c < 4; c++) {
         p.fft_class_off[c] = (int)plist.size();
         for (int q = 0; q < p.npair; q++) {
             const int cls = pf[q].bluestein == 2 ? 2 : (2 * pf[q].fftlen <= fftmax ? 0 : 1);
-            if (cls != c) continue;
+            if (c == 3 ? cls == 2 : cls != c) continue;
             plist.push_back(q);
             if (c == 0) p.fft_class_len[0] = std::max(p.fft_class_len[0], pf[q].fftlen);
             if (c == 2) {
@@ -838,8 +838,7 @@ static int create(int nside, int lmax, int spin, int dtype, int max_batch, void 
         }
         p.fft_class_count[c] = (int)plist.size() - p.fft_class_off[c];
     }
-    p.fft_class_len[1] = fftmax;
-    p.fft_class_len[2] = fftmax;
+    for (int c = 1; c < 4; c++) p.fft_class_len[c] = fftmax;
     if (nsplit_max > fftmax)
         return fail(MFWF_EINVAL, "split ring of " + std::to_string(nsplit_max) +
                                      " pixels above the largest transform length");
@@ -849,7 +848,7 @@ static int create(int nside, int lmax, int spin, int dtype, int max_batch, void 
     size_t lds = std::max({fft_class_lds(p, 0), fft_class_lds(p, 1), fft_class_lds(p, 2)});
     if (dtype == MFWF_F32)  // the columns ring step of the batched form, G maps per workgroup
         for (int c = 0; c < 2; c++)
-            lds = std::max(lds, fft_cols_lds(p, c, fft_cols_group_max(p, c, max_batch)));
+            lds = std::max(lds, fft_cols_lds(p, c, fft_cols_group_max(p, c, max_batch)));  // 3: as 1
     {
         int dev = 0, maxlds = 0;
         MFWF_HIP(hipGetDevice(&dev));

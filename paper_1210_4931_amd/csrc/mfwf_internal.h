@@ -89,8 +89,9 @@ struct Plan {
     double2 *d_bhat = nullptr;   // Bluestein kernels FFT_M(conj chirp) / M, natural order
     int fftmax;                  // largest power-of-two transform length
     int *d_plist = nullptr;      // [npair] pair indices grouped by FFT class
-    // classes: 0 short transforms, 1 the longest in-LDS ones (first in the list), 2 split rings
-    int fft_class_off[3] = {0, 0, 0}, fft_class_count[3] = {0, 0, 0}, fft_class_len[3] = {1, 1, 1};
+    // classes: 0 short transforms, 1 the longest in-LDS ones, 2 split rings, 3 those of 0 and 1
+    // together, in ring order
+    int fft_class_off[4] = {}, fft_class_count[4] = {}, fft_class_len[4] = {1, 1, 1, 1};
     // FP32 ring step: the longest ring class runs on a side stream forked from `stream` (and
     // joined back) while the short class runs on `stream`; the classes touch disjoint rings
     hipStream_t side = nullptr;
