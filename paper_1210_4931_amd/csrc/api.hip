@@ -256,7 +256,7 @@ static void free_plan(Plan &p) {
                     p.d_tw,   p.d_twlo, p.d_twhi, p.d_chirp, p.d_bhat, p.d_mofs,   p.d_cl,    p.d_M, p.d_pc, p.d_tau,
                     p.d_rho,  p.d_t,    p.d_smap,  p.d_phase,  p.d_apart, p.d_salm,
                     p.d_salm_prev, p.d_sp, p.d_red, p.d_diag, p.d_lam, p.d_lck, p.d_segoff, p.d_loff, p.d_Lp,
-                    p.d_minls32, p.d_ana_items, p.d_syn_items, p.d_ana_tab, p.d_syn_tab, p.d_lofi, p.d_phf, p.d_ph32, p.d_cscale, p.d_zrow, p.d_a32,
+                    p.d_minls32, p.d_ana_items, p.d_syn_items, p.d_ana_tab, p.d_syn_tab, p.d_lofi, p.d_phf, p.d_ph32, p.d_cscale, p.d_csearch, p.d_zrow, p.d_a32,
                     p.d_s32, p.d_fp, p.d_fm, p.d_ph32p, p.d_ap32, p.d_ar32, p.d_seb32,
                     p.d_fftsplit};
     for (void *q : ptrs)
@@ -638,6 +638,7 @@ static int setup_batched(Plan &p, const std::vector<int> &lstart, const std::vec
     MFWF_TRY(dalloc(&p.d_phf, (size_t)p.ncomp * p.max_batch * p.nring * p.nm32, "ring Fourier rows FP32"));
     MFWF_TRY(dalloc(&p.d_ph32, (size_t)p.nring * p.nm * p.C2, "ring Fourier FP32"));
     MFWF_TRY(dalloc(&p.d_cscale, (size_t)(p.spin == 2 ? 2 : 1) * p.Bp, "column scales"));
+    MFWF_TRY(dalloc(&p.d_csearch, (size_t)(p.spin == 2 ? 2 : 1) * p.Bp, "column scale searches"));
     MFWF_TRY(launch_unit_scale(p));
     MFWF_TRY(dalloc(&p.d_zrow, (size_t)2 * p.C2, "zero row"));
     MFWF_HIP(hipMemsetAsync(p.d_zrow, 0, sizeof(float) * 2 * p.C2, p.stream));
@@ -1541,8 +1542,7 @@ int mfwf_sht_fwd(mfwf_plan plan, const double *map, double *alm, int nmaps) {
     for (int b0 = 0; b0 < nmaps; b0 += p.max_batch) {
         const int nb = std::min(p.max_batch, nmaps - b0);
         if (p.spin == 2 && p.dtype == MFWF_F32) {
-            MFWF_TRY(launch_col_scale(p, map + 3L * b0 * p.npix, p.npix, kHarmCopy, nb));
-            MFWF_TRY(launch_fft_fwd_f32(p, map + 3L * b0 * p.npix, nullptr, 1.0, p.d_phf, 3 * nb));
+            MFWF_TRY(launch_fft_fwd_f32(p, map + 3L * b0 * p.npix, nullptr, 1.0, p.d_phf, 3 * nb, true));
             MFWF_TRY(launch_rows_to_cols_pol(p, nb));
             MFWF_TRY(pol_analysis_b(p, nb, 0.0, kPolRaw));
             MFWF_TRY(launch_cols_to_alm_pol(p, reinterpret_cast<double2 *>(alm) + 3L * b0 * p.nalm, nb));
@@ -1557,8 +1557,7 @@ int mfwf_sht_fwd(mfwf_plan plan, const double *map, double *alm, int nmaps) {
             continue;
         }
         if (p.dtype == MFWF_F32) {
-            MFWF_TRY(launch_col_scale(p, map + (long)b0 * p.npix, p.npix, kHarmCopy, nb));
-            MFWF_TRY(launch_fft_fwd_f32(p, map + (long)b0 * p.npix, nullptr, 1.0, p.d_phf, nb));
+            MFWF_TRY(launch_fft_fwd_f32(p, map + (long)b0 * p.npix, nullptr, 1.0, p.d_phf, nb, true));
             MFWF_TRY(launch_rows_to_cols(p, nb));
             MFWF_TRY(launch_gemm_analysis(p, nb, p.d_a32, nullptr, 0.0, 0.0));
             MFWF_TRY(launch_cols_to_alm(p, p.d_a32, reinterpret_cast<double2 *>(alm) + (long)b0 * p.nalm,

@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "col_scale.h"
 #include "fft_core.h"
 #include "leg_core.h"
 
@@ -138,55 +139,34 @@ struct LamGen {
     const double *A, *c;   // [nalm]
 };
 
-// ---------------------------------------------------------------------------------------
-// The scale of a map's columns.  The contractions split FP32 values into bf16 pieces; the last
-// piece of a value below 2^-110 lies below bf16's smallest number, so small maps would lose
-// bits that FP32 keeps down to 2^-126 (1.3e-7 relative error, but 2.6e-4 at 1e-37).  The
-// columns of a map therefore carry the map times a power of two, which changes no rounding:
-// 2^40 if no value of the map reaches 2^-70, else 1.  The regrouping and conversion kernels and the
-// ring step apply it and take it off; everything else is linear in it.
-//
-// One workgroup per (map, group of components) looks for a value that reaches 2^-70: first at one
-// value per thread, spread over the whole map, which ends the search on any map that is not
-// small or nearly empty (a transform's call then takes 5 us longer: the launch and two memory
-// latencies), then through the map in order.
-// grid.y = 2: a group of n0 and one of n1 values per map (T; Q and U, or
-// E and B), the second to scale[Bp + b]; both: one group, to both.  cl: the values are
-// C^-1/2 x (mode 2 of k_alm_to_cols).
-// ---------------------------------------------------------------------------------------
-static constexpr double kSmallMap = 0x1p-70, kSmallScale = 0x1p40;
-static constexpr ColScale kUnitScale{1.0, 1.0, 1.f, 1.f};
-
-__global__ void __launch_bounds__(256) k_unit_scale(ColScale *__restrict__ scale, int n) {
-    for (int i = threadIdx.x; i < n; i += 256) scale[i] = kUnitScale;
+// The column scales (col_scale.h) of the maps of a solve, or of the coefficients a transform reads:
+// grid (map, group of components, part), 5 us a call.  Two groups: n0 and n1 values per map (T; E
+// and B), the second's scale to [Bp + b]; both: one group, to both.  cl: the values are C^-1/2 x
+// (mode 2 of k_alm_to_cols).
+__global__ void __launch_bounds__(256)
+k_unit_scale(ColScale *__restrict__ scale, ColScaleSearch *__restrict__ search, int n) {
+    for (int i = threadIdx.x; i < n; i += 256) {
+        scale[i] = kUnitScale;
+        search[i] = ColScaleSearch{0, 0};
+    }
 }
 
 __global__ void __launch_bounds__(256)
 k_col_scale(const double *__restrict__ x, long stride, long n0, long n1, double factor,
             const double *__restrict__ cl, const int *__restrict__ lofi, int both, int Bp,
-            ColScale *__restrict__ scale) {
+            ColScale *scale, ColScaleSearch *search) {
+    __shared__ int flag;
     const int b = blockIdx.x, g = blockIdx.y;
     const double *v = x + b * stride + (g ? n0 : 0);
-    const long n = g ? n1 : n0;
-    auto reaches = [&](long i) {  // written so that a NaN counts as large
+    find_col_scale<256>(g ? n1 : n0, blockIdx.z, gridDim.z, &flag, search + g * Bp + b, scale + g * Bp + b,
+                        both ? scale + Bp + b : nullptr, [&](long i) {
         double f = factor;
         if (cl) {
             const double C = cl[lofi[i >> 1]];
             f = C > 0.0 ? 1.0 / sqrt(C) : 0.0;
         }
-        return !(fabs(f * v[i]) < kSmallMap);
-    };
-    bool big = __syncthreads_or(reaches(min(threadIdx.x * max(n >> 8, 1L), n - 1)));
-    for (long k = 0; k < n && !big; k += 32 * 256) {  // big is the same for every thread
-        bool any = false;
-#pragma unroll
-        for (int u = 0; u < 32; u++) any |= reaches(min(k + 256 * u + threadIdx.x, n - 1));
-        big = __syncthreads_or(any);
-    }
-    if (threadIdx.x != 0) return;
-    const ColScale s = big ? kUnitScale : ColScale{kSmallScale, 1.0 / kSmallScale, (float)kSmallScale, (float)(1.0 / kSmallScale)};
-    scale[g * Bp + b] = s;
-    if (both) scale[Bp + b] = s;
+        return f * v[i];
+    });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1106,31 +1086,31 @@ int launch_lam_ckpt(const Plan &p) {
 }
 
 static int col_scale(const Plan &p, const double *x, long stride, long n0, long n1, double factor,
-                     const double *cl, int both, int nb, ColScale *scale) {
-    hipLaunchKernelGGL(k_col_scale, dim3(nb, n1 > 0 ? 2 : 1), dim3(256), 0, p.stream, x, stride, n0,
-                       n1, factor, cl, p.d_lofi, both, p.Bp, scale);
+                     const double *cl, int both, int b0, int nb) {
+    hipLaunchKernelGGL(k_col_scale, dim3(nb, n1 > 0 ? 2 : 1, col_scale_parts(n0)), dim3(256), 0, p.stream, x,
+                       stride, n0, n1, factor, cl, p.d_lofi, both, p.Bp, p.d_cscale + b0, p.d_csearch + b0);
     MFWF_HIP(hipGetLastError());
     return MFWF_OK;
 }
 
 int launch_unit_scale(const Plan &p) {
-    hipLaunchKernelGGL(k_unit_scale, dim3(1), dim3(256), 0, p.stream, p.d_cscale, p.spin == 2 ? 2 * p.Bp : p.Bp);
+    hipLaunchKernelGGL(k_unit_scale, dim3(1), dim3(256), 0, p.stream, p.d_cscale, p.d_csearch,
+                       p.spin == 2 ? 2 * p.Bp : p.Bp);
     MFWF_HIP(hipGetLastError());
     return MFWF_OK;
 }
 
-// of the maps (n = npix) or coefficients (n = 2 nalm) a transform reads, per map T and, spin 2,
-// the other two components
+// of the coefficients a transform reads (n = 2 nalm doubles a component), per map T and, spin 2, E
+// and B
 int launch_col_scale(const Plan &p, const double *x, long n, int mode, int nb) {
     return col_scale(p, x, p.ncomp * n, n, (p.ncomp - 1) * n, 1.0, mode == kHarmInvSqrtC ? p.d_cl : nullptr,
-                     0, nb, p.d_cscale);
+                     0, 0, nb);
 }
 
 // of the source rho of a solve's maps b0 .. b0 + nb - 1: the iterates are of the size of tau rho and
 // above (tau M <= 1).  The components of T, Q, U mix in the update and share a scale.
 int launch_col_scale_rho(const Plan &p, const double *rho, double tau, int b0, int nb) {
-    return col_scale(p, rho, p.ncomp * p.npix, p.ncomp * p.npix, 0, tau, nullptr, p.spin == 2, nb,
-                     p.d_cscale + b0);
+    return col_scale(p, rho, p.ncomp * p.npix, p.ncomp * p.npix, 0, tau, nullptr, p.spin == 2, b0, nb);
 }
 
 int launch_rows_to_cols(const Plan &p, int nb) {

@@ -46,10 +46,14 @@ struct PairFFT {
 // Legendre work split: the wave of lanes handling ring pairs [g * 64 * P, (g+1) * 64 * P)
 // for one m.  Seeds: for every (m, pair) the first l with |lambda_lm| >= 2^-100 and the
 // two values (lambda_{l_s - 1, m}, lambda_{l_s, m}); l_s = lmax + 1 if never reached.
-// the power of two that a map's FP32 columns carry, and its inverse (batched.hip, k_col_scale)
+// the power of two that a map's FP32 columns carry, and its inverse (col_scale.h)
 struct ColScale {
     double s, inv;
     float s32, inv32;
+};
+// state of the search for it, zero between searches
+struct ColScaleSearch {
+    int found, done;
 };
 
 struct Plan {
@@ -157,6 +161,7 @@ struct Plan {
     bool chain_ready = false;    // d_ph32 holds the synthesis of the iterate in d_smap
     float *d_ph32 = nullptr;     // [nm][nring][C2] ring-Fourier, maps innermost
     ColScale *d_cscale = nullptr; // [Bp], spin 2 [2][Bp] (T; Q, U and E, B)
+    ColScaleSearch *d_csearch = nullptr;  // alike
     float *d_zrow = nullptr;     // [2 C2] zeros: the equator pair's south ring
     float *d_a32 = nullptr;      // [nalm][C2] analysis output
     float *d_s32 = nullptr;      // [nalm][C2] synthesis input
@@ -210,8 +215,9 @@ int launch_fft_fwd_pix(const Plan &p, const double *maps, const double *rho, dou
 int launch_fft_inv(const Plan &p, const double2 *phase, double *maps, int nb);
 // FP32 rows [map][ring][m]; with rho the input is the messenger field of Eq. (3) built from
 // rho, M and s = maps on the fly
+// (scales: no rho, and the maps' column scales d_cscale are found in the same launch)
 int launch_fft_fwd_f32(const Plan &p, const double *maps, const double *rho, double lam,
-                       float2 *phase, int nb);
+                       float2 *phase, int nb, bool scales = false);
 int launch_fft_inv_f32(const Plan &p, const float2 *phase, double *maps, int nb);
 // Ring transforms whose two in-LDS classes (up to half the largest length, and above) go in one
 // launch rather than two
@@ -243,7 +249,7 @@ int leg_analysis_pairs_per_lane(int v);
 // batched.hip (FP32 form)
 int launch_lam_table(const Plan &p);
 int launch_lam_ckpt(const Plan &p);  // d_lck from the recurrence
-// d_cscale for the maps or coefficients x that a transform reads (n doubles per component; mode
+// d_cscale for the coefficients x that a transform reads (n doubles per component; mode
 // kHarmInvSqrtC: C^-1/2 x), or for the sources rho of maps b0 .. b0 + nb - 1 of a solve
 int launch_unit_scale(const Plan &p);  // d_cscale = 1
 int launch_col_scale(const Plan &p, const double *x, long n, int mode, int nb);

@@ -32,6 +32,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "col_scale.h"
 #include "fft_core.h"
 #include "sym3.h"
 
@@ -119,13 +120,27 @@ template <int TPB, int EPT, typename OutT, bool PIX>
 __global__ void __launch_bounds__(TPB)
 k_fft_fwd(const double *__restrict__ maps, const double *__restrict__ rho,
           const double *__restrict__ M, double lam, double tau, long mstride,
-          const double *__restrict__ tau_b, OutT *__restrict__ phase,
-          const PairFFT *__restrict__ pfft, const int *__restrict__ plist,
+          const double *__restrict__ tau_b, ColScale *find, ColScaleSearch *search, int parts, int ncomp, int Bp,
+          OutT *__restrict__ phase, const PairFFT *__restrict__ pfft, const int *__restrict__ plist,
           const double2 *__restrict__ twlo, const double2 *__restrict__ twhi, int ntwhi,
           int fftmax, const double2 *__restrict__ chirp, const double2 *__restrict__ bhat,
           long npix, int nring, int nm, int lmax, int fftlen_class) {
     extern __shared__ double2 buf[];
-    const int p = plist[blockIdx.y], b = blockIdx.x;
+    int y = blockIdx.y;
+    if constexpr (!PIX && sizeof(OutT) == sizeof(float2)) {
+        // find: the first rows of workgroups look for the maps' column scales, beside the
+        // transforms (a launch of its own took 5-7 us)
+        if (find && y < parts) {
+            const int row = blockIdx.x, c = row % ncomp, at = c * Bp + row / ncomp;
+            if (c == 2) return;  // U, with Q
+            const double *v = maps + (long)row * npix;
+            find_col_scale<TPB>(c ? 2 * npix : npix, y, parts, reinterpret_cast<int *>(buf), search + at,
+                                find + at, nullptr, [&](long i) { return v[i]; });
+            return;
+        }
+        if (find) y -= parts;
+    }
+    const int p = plist[y], b = blockIdx.x;
     const PairFFT pf = pfft[p];
     const int n = pf.nphi;
     const bool equator = (pf.startS == pf.startN);
@@ -1014,7 +1029,7 @@ bool ring_merged(const Plan &p, RingStep step, int rows) {
 
 template <typename OutT, bool PIX>
 static int fwd_classes(const Plan &p, const double *maps, const double *rho, double lam,
-                       OutT *out, int nb) {
+                       OutT *out, int nb, bool scales = false) {
     if (p.fft_class_count[2] > 0)
         MFWF_TRY((fwd_split<OutT, PIX, false>(p, maps, rho, lam, out,
                                               sizeof(OutT) == sizeof(float2) ? p.nm32 : p.nm, nb)));
@@ -1023,15 +1038,17 @@ static int fwd_classes(const Plan &p, const double *maps, const double *rho, dou
         const int c = L[k].c, cnt = L[k].cnt;
         int ept;
         const int tpb = fft_class_shape(p, c, ept);
-        const dim3 grid(nb, cnt);  // maps of one pair adjacent: its tables and M stay in L2
+        ColScale *find = scales && k == 0 ? p.d_cscale : nullptr;
+        const int parts = find ? col_scale_parts(p.npix) : 0;
+        const dim3 grid(nb, cnt + parts);  // maps of one pair adjacent: its tables and M stay in L2
         const size_t lds = fft_class_lds(p, c);
         const int rs = sizeof(OutT) == sizeof(float2) ? p.nm32 : p.nm;
         if (tpb == 256)
-            hipLaunchKernelGGL((k_fft_fwd<256, 8, OutT, PIX>), grid, dim3(256), lds, p.stream, maps, rho, p.d_M, lam, p.tau, p.mstride, p.d_tau, out, MFWF_FFT_ARGS(c, rs));
+            hipLaunchKernelGGL((k_fft_fwd<256, 8, OutT, PIX>), grid, dim3(256), lds, p.stream, maps, rho, p.d_M, lam, p.tau, p.mstride, p.d_tau, find, p.d_csearch, parts, p.ncomp, p.Bp, out, MFWF_FFT_ARGS(c, rs));
         else if (tpb == 512)
-            hipLaunchKernelGGL((k_fft_fwd<512, 8, OutT, PIX>), grid, dim3(512), lds, p.stream, maps, rho, p.d_M, lam, p.tau, p.mstride, p.d_tau, out, MFWF_FFT_ARGS(c, rs));
+            hipLaunchKernelGGL((k_fft_fwd<512, 8, OutT, PIX>), grid, dim3(512), lds, p.stream, maps, rho, p.d_M, lam, p.tau, p.mstride, p.d_tau, find, p.d_csearch, parts, p.ncomp, p.Bp, out, MFWF_FFT_ARGS(c, rs));
         else
-            hipLaunchKernelGGL((k_fft_fwd<1024, 8, OutT, PIX>), grid, dim3(1024), lds, p.stream, maps, rho, p.d_M, lam, p.tau, p.mstride, p.d_tau, out, MFWF_FFT_ARGS(c, rs));
+            hipLaunchKernelGGL((k_fft_fwd<1024, 8, OutT, PIX>), grid, dim3(1024), lds, p.stream, maps, rho, p.d_M, lam, p.tau, p.mstride, p.d_tau, find, p.d_csearch, parts, p.ncomp, p.Bp, out, MFWF_FFT_ARGS(c, rs));
         MFWF_HIP(hipGetLastError());
     }
     return MFWF_OK;
@@ -1070,9 +1087,9 @@ int launch_fft_fwd_pix(const Plan &p, const double *maps, const double *rho, dou
 }
 
 int launch_fft_fwd_f32(const Plan &p, const double *maps, const double *rho, double lam,
-                       float2 *phase, int nb) {
+                       float2 *phase, int nb, bool scales) {
     if (rho) return fwd_classes<float2, true>(p, maps, rho, lam, phase, nb);
-    return fwd_classes<float2, false>(p, maps, nullptr, 1.0, phase, nb);
+    return fwd_classes<float2, false>(p, maps, nullptr, 1.0, phase, nb, scales);
 }
 
 int launch_fft_inv(const Plan &p, const double2 *phase, double *maps, int nb) {
