@@ -756,7 +756,7 @@ k_gemm_analysis(const float *__restrict__ lam, LamGen gen, const long *__restric
 // flip (the spin-2 F-).
 // ONCE: the table's loads are streaming loads (launch rule: synthesis_once).
 template <int CT, bool GEN, bool ONCE>
-__global__ void __launch_bounds__(Tile<CT>::NTH, 2)
+__global__ void __launch_bounds__(Tile<CT>::NTH, CT == 32 ? 4 : 2)
 k_gemm_synthesis(const float *__restrict__ lam, LamGen gen, const long *__restrict__ loff,
                  const int *__restrict__ Lp, const int *__restrict__ minls32,
                  const int2 *__restrict__ items, const int *__restrict__ tab, int per_xcd,
