@@ -1143,7 +1143,10 @@ static int active_cols(int nb, int w) { return 32 * ((w * nb + 31) / 32); }
 // a choice 1: 64 columns, 2: 128, 3: 32: 32 columns where tiles of 64 would leave the chip's 512
 // places for workgroups filled less than about twice (nside 128, 40 maps, 1028 such workgroups:
 // synthesis 51 us with them, 34 with 32 columns; at nside 256, 20 maps, 2052 of them, 82 against
-// 89), the narrowest that holds all columns, or else the choice; a forced choice as it is.
+// 89), the narrowest that holds all columns, or else the choice; a forced choice as it is.  The
+// analysis that generates lambda takes 128 columns for more than 32: each tile generates anew, and
+// eight waves hide that better than four (nside 2048, lmax 4096, sht_fwd, ms with 64 / 128 columns:
+// 24 maps 67.2 / 59.7, 32 maps 72.2 / 64.9; lmax 2048, 24 maps 26.6 / 24.4).
 static int gemm_tile(const Plan &p, int which, int choice, int nc) {
     const int ct = choice == 2 ? 128 : (choice == 3 ? 32 : 64);
     if (p.gemm_forced[which]) return ct;
