@@ -1152,7 +1152,9 @@ static int gemm_tile(const Plan &p, int which, int choice, int nc) {
     if (p.gemm_forced[which]) return ct;
     const int ntile = 8 * (which ? p.syn_per_xcd : p.ana_per_xcd);
     if (ntile * ((nc + 63) / 64) < 1200) return 32;
-    return nc <= 32 ? 32 : (nc <= 64 ? std::min(ct, 64) : ct);
+    if (nc <= 32) return 32;
+    if (p.lam_gen && which == 0) return 128;
+    return nc <= 64 ? std::min(ct, 64) : ct;
 }
 
 int gemm_effective(const Plan &p, int which, int choice) {
