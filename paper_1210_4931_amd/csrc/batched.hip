@@ -265,11 +265,11 @@ k_cols_to_rows(const float *__restrict__ ph32, float2 *__restrict__ phf, int nri
 // rings would round several times more).
 //
 // Measured against the FP32 matrix instructions (us, analysis / synthesis): nside 512, 64 maps
-// 1359 / 1221 -> 1090 / 1160; nside 256, 64 maps 230 / 203 -> 202 / 216; nside 128, 4 maps
-// 30 / 19 -> 19 / 17; nside 512, T, Q, U, 32 maps 3401 / 3250 -> 2775 / 3105; lambda generated,
-// nside 2048, 4 maps 44500 / 40000 -> 36200 / 30500.  What is left at nside 512: the table is
-// 2.1 GB (0.43 ms at a copy's rate), the six products 0.5 ms, and the splits, which share the
-// issue slots with them, about as much again.
+// 1304 / 1163 -> 985 / 1123; nside 256, 64 maps 230 / 203 -> 191 / 201; nside 128, 4 maps
+// 30 / 19 -> 20 / 18; nside 512, T, Q, U, 32 maps 3324 / 3112 -> 2514 / 2959; transforms with
+// generated lambda, nside 2048, lmax 4096, 4 maps 49500 / 44500 -> 37100 / 30000.  What is left at
+// nside 512: the table is 2.1 GB (0.43 ms at a copy's rate), the six products 0.5 ms, and the
+// splits, which share the issue slots with them, about as much again.
 //
 // Workgroup i of a launch is dispatched to XCD i mod 8.  Each XCD takes its tiles from its
 // own list, so that all tiles of one m, which read the same ring-Fourier (analysis) or
