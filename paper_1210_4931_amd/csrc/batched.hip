@@ -346,14 +346,13 @@ static constexpr int kAnaL = 2 * kRows; // values of l per analysis tile
 // narrower one leaves more workgroups, and the eight small waves hide each other's latency
 // where a CU holds one or two workgroups (nside 128, 4 maps: analysis 26 -> 19 us against four
 // waves of 64 x 32; the 64-column tile cut the same way needs more than 128 registers, loses
-// its second workgroup per CU and goes from 202 to 290 us at nside 256, 64 maps; EIGHT cuts it so
-// where lambda is generated, see the synthesis).  Every output column sees the same operations
-// with any tile.
-template <int CT, bool EIGHT = CT != 64>
+// its second workgroup per CU and goes from 202 to 290 us at nside 256, 64 maps).  Every output
+// column sees the same operations with any tile.
+template <int CT>
 struct Tile {
-    static constexpr int NTH = EIGHT ? 512 : 256;      // threads
+    static constexpr int NTH = CT == 64 ? 256 : 512;   // threads
     static constexpr int NCT = CT == 32 ? 1 : 2;       // 32-column tiles per wave
-    static constexpr int NRT = EIGHT && CT != 128 ? 1 : 2;  // 32-row tiles per wave
+    static constexpr int NRT = CT == 32 ? 1 : 2;       // 32-row tiles per wave
     static constexpr int NA = 4 * kRows / NTH;         // staging tasks per thread, A and B
     static constexpr bool B1 = CT == 32;               // a staging task of B: one k of both parities, else four
     static constexpr int NB = B1 ? NTH : 4 * CT;       // staging tasks of B
@@ -391,9 +390,10 @@ __device__ __forceinline__ bf16x8 get_operand(const unsigned short *buf, int par
 
 // A wave's products of one stage, its 64 rows x 32 NCT columns of parity par, summed from zero,
 // small piece products first
-template <int CT, int NRT, int NCT>
+template <int CT>
 __device__ __forceinline__ void stage_products(const unsigned short *A, const unsigned short *B, int par,
-                                               int row0, int col0, floatx16 (&part)[NRT][NCT]) {
+                                               int row0, int col0, floatx16 (&part)[Tile<CT>::NRT][Tile<CT>::NCT]) {
+    constexpr int NCT = Tile<CT>::NCT, NRT = Tile<CT>::NRT;
     const int lane = threadIdx.x & 63, i = lane & 31, kg = lane >> 5;
     bf16x8 a[NRT][3];
 #pragma unroll
@@ -755,20 +755,15 @@ k_gemm_analysis(const float *__restrict__ lam, LamGen gen, const long *__restric
 // rings E + O, the odd one the south rings E - O (lambda's mirror symmetry), or O - E with
 // flip (the spin-2 F-).
 // ONCE: the table's loads are streaming loads (launch rule: synthesis_once).
-// GEN: lambda is generated from the segment states by four waves, chains of sixteen steps in
-// double precision, which bound the kernel: tiles of 32 and of 64 columns take eight waves of
-// 32 rows and at most 128 registers, so that two workgroups of a CU hide each other's chains
-// (nside 2048, lmax 4096, sht_inv, ms with 8 / 16 waves per CU: 4 maps 49.9 / 30.1, 16 maps
-// 57.9 / 38.2, 24 maps 65.0 / 61.5, 32 maps 71.0 / 67.6; with 64 columns five registers spill).
 template <int CT, bool GEN, bool ONCE>
-__global__ void __launch_bounds__((Tile<CT, CT != 64 || GEN>::NTH), (CT == 32 || (GEN && CT == 64) ? 4 : 2))
+__global__ void __launch_bounds__(Tile<CT>::NTH, CT == 32 ? 4 : 2)
 k_gemm_synthesis(const float *__restrict__ lam, LamGen gen, const long *__restrict__ loff,
                  const int *__restrict__ Lp, const int *__restrict__ minls32,
                  const int2 *__restrict__ items, const int *__restrict__ tab, int per_xcd,
                  const float *__restrict__ s32, const long *__restrict__ mofs,
                  float *__restrict__ ph32, int lmax, int npair, int Rp, int nring, int nm,
                  int C2, int ncols, int ncg, int flip, int comb) {
-    using T = Tile<CT, CT != 64 || GEN>;
+    using T = Tile<CT>;
     constexpr int NTH = T::NTH, NCT = T::NCT, NRT = T::NRT, NA = T::NA, NW = NTH / 64, RW = 32 * NRT;
     __shared__ __align__(16) unsigned short sA[2][T::A_EL], sB[2][T::B_EL];
     const XcdTile xt = xcd_tile(tab, per_xcd, ncg);
@@ -786,10 +781,7 @@ k_gemm_synthesis(const float *__restrict__ lam, LamGen gen, const long *__restri
     // staging tasks of a stage: A: (pair; four values of l), two per thread of 512; B: (column;
     // eight values of l, four of each parity)
     // register sets of loads in flight: two stages ahead, one where two would not fit
-    constexpr int NS = CT == 64 ? 1 : 2;
-    // the stage's sums added before the next one's splitting, not after: the other waves cover the
-    // products' latency, and the partial sums hold no registers while lambda is generated
-    constexpr bool EARLY = CT == 64 && GEN;
+    constexpr int NS = CT == 64 && !GEN ? 1 : 2;
     constexpr bool COMPACT = CT == 32 && !GEN;
     floatx4 ra[GEN ? 1 : NS][GEN ? 1 : 2 * NA];
     float rb[NS][T::NBV];
@@ -927,9 +919,8 @@ k_gemm_synthesis(const float *__restrict__ lam, LamGen gen, const long *__restri
         };
         floatx16 part[NRT][NCT];
         if constexpr (on()) stage_products<CT>(sA[0], sB[0], par, RW * rh, 64 * ch, part);
-        if constexpr (!EARLY) refill1();
+        refill1();
         if constexpr (on()) stage_add<false>(acc, part);
-        if constexpr (EARLY) refill1();
         __syncthreads();
         auto refill0 = [&]() __attribute__((always_inline)) {
             split(rl, 0, 0);
@@ -937,9 +928,8 @@ k_gemm_synthesis(const float *__restrict__ lam, LamGen gen, const long *__restri
             else load(rl + 32, 1);
         };
         if constexpr (on()) stage_products<CT>(sA[1], sB[1], par, RW * rh, 64 * ch, part);
-        if constexpr (!EARLY) refill0();
+        refill0();
         if constexpr (on()) stage_add<true>(acc, part);
-        if constexpr (EARLY) refill0();
         __syncthreads();
         rc++;
     };
@@ -1218,7 +1208,7 @@ static bool synthesis_once(const Plan &p, int ncg) {
 static int synthesis_launch(const Plan &p, int nc, int C2, const float *table, const float *s_in,
                             float *out, int flip, int comb) {
     const int ct = gemm_tile(p, 1, p.gemm_ct[1], nc), ncg = (nc + ct - 1) / ct;
-    const dim3 grid(8 * p.syn_per_xcd * ncg), block(ct == 64 && table ? 256 : 512);
+    const dim3 grid(8 * p.syn_per_xcd * ncg), block(ct == 64 ? 256 : 512);
     const LamGen g = lam_gen(p);
     if (table == nullptr && !p.d_lck) return fail(MFWF_EINVAL, "no lambda segment states in this plan");
 #define MFWF_SYN(CT, GEN, ONCE)                                                                     \
