@@ -755,6 +755,10 @@ k_gemm_analysis(const float *__restrict__ lam, LamGen gen, const long *__restric
 // rings E + O, the odd one the south rings E - O (lambda's mirror symmetry), or O - E with
 // flip (the spin-2 F-).
 // ONCE: the table's loads are streaming loads (launch rule: synthesis_once).
+// GEN: lambda is generated from the segment states by four waves, chains of sixteen steps in
+// double precision, which bound the kernel: 32 columns take at most 128 registers, so that two
+// workgroups of a CU hide each other's chains (nside 2048, lmax 4096, sht_inv, ms with one / two:
+// 4 maps 49.9 / 30.1, 16 maps 57.9 / 38.2).  64 columns cut the same way spill.
 template <int CT, bool GEN, bool ONCE>
 __global__ void __launch_bounds__(Tile<CT>::NTH, CT == 32 ? 4 : 2)
 k_gemm_synthesis(const float *__restrict__ lam, LamGen gen, const long *__restrict__ loff,
