@@ -43,16 +43,16 @@ PEAK_HBM = 8.0e12                              # HBM3E bytes/s
 # more maps per workgroup write larger column pieces), so they are kept per (g0, g1).  Valid only
 # for the kernel source they were taken on, identified by the SHA-256 of the source file.
 TRAFFIC = {
-    "ring_step": {"bytes": {(1, 1): 4.362e+09, (2, 1): 3.9462e+09}, "source": "ringfft.hip",
-                  "sha256": "c9b4266582b594104aa72a0f282339b23db43c2dc5f7bafaa90cdc95b24237aa"},
+    "ring_step": {"bytes": {(2, 1): 3.9226e+09}, "source": "ringfft.hip",
+                  "sha256": "562d7a35a228c24695342370114e9e2478df33a8c3ec199723a7c7f6f7b28e73"},
     # the analysis GEMM's, per (column tile choice "cta", lambda generated "lamgen")
-    "gemm_analysis": {"bytes": {(1, 0): 5.3876e+09}, "source": "batched.hip",
-                      "sha256": "cf741d30ae83034de945d059f9844b1e0fee8f93c8168cea03ce9daf44a0597d"},
+    "gemm_analysis": {"bytes": {(2, 0): 3.2621e+09}, "source": "batched.hip",
+                      "sha256": "b6a1d59a9d5df1b0ffabf9844e6b298179d2db0abb7ea16682904d88473b99f7"},
 }
 # What the shader counters say limits the ring step (VALU issue and LDS bank conflicts, not
 # HBM): profiles/batched_nside512_lmax1024_b64_shader_counters.md, same kernel sources.
 RING_COUNTERS = {"valu_busy": [0.43, 0.53], "lds_bank_conflict_share": [0.25, 0.27],
-                 "mfma_busy": 0.0, "hbm_traffic_over_algorithmic": {"g0=1,g1=1": 1.15, "g0=2,g1=1": 1.04},
+                 "mfma_busy": 0.0, "hbm_traffic_over_algorithmic": {"g0=2,g1=1": 1.04},
                  "profile": "profiles/batched_nside512_lmax1024_b64_shader_counters.md"}
 
 
